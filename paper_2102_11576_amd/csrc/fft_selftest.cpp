@@ -274,6 +274,11 @@ int main() {
   worst = std::fmax(worst, run_case<4096, 16, double>(12));
   worst = std::fmax(worst, run_case<8192, 16, double>(16));
   worst = std::fmax(worst, run_case<1024, 8, double>(17));
+  worst = std::fmax(worst, run_case<8, 4, double>(18));
+  worst = std::fmax(worst, run_case<32, 4, double>(19));
+  worst = std::fmax(worst, run_case<128, 4, double>(20));
+  worst = std::fmax(worst, run_case<256, 4, double>(21));
+  worst = std::fmax(worst, run_case<256, 4, float>(22));
   worst = std::fmax(worst, run_case<128, 4, double>(13));
   worst = std::fmax(worst, run_case<256, 8, float>(14));
   worst = std::fmax(worst, run_case<4096, 16, float>(15));

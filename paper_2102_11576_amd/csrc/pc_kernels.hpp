@@ -58,7 +58,7 @@ struct PcCfg {
 };
 template <int L>
 struct PcColCfg {
-  using F = Fft<L, pc_cols_pts(L)>;
+  using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
   static constexpr int BC = (512 / TPF) > 16 ? 16 : ((512 / TPF) > 0 ? (512 / TPF) : 1);
   static constexpr int THR_C = BC * TPF;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_dst_cols(
   fft_forward<T, F, false, C::BC>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
-    const int f = fft_freq(L, pc_cols_pts(L), F::pos(F::NS - 1, tau, e));
+    const int f = fft_freq(L, fft_pts(L), F::pos(F::NS - 1, tau, e));
     if (valid && f >= 1 && f <= rows) {
       const size_t i = (size_t)(f - 1) * ld;
       outA[i + ca] = (T)-0.5 * reg[e].im;

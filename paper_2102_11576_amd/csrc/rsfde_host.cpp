@@ -1298,7 +1298,7 @@ std::vector<double> slot_eigs(const std::vector<double>& lx, int Lx) {
 // Column-pass eigenvalues in register-position order of the length-L FFT
 // (even in frequency; 0 at frequencies 0 and L/2).
 std::vector<double> pos_eigs(const std::vector<double>& ly, int L) {
-  const int n = (int)ly.size(), Py = pc_cols_pts(L);
+  const int n = (int)ly.size(), Py = fft_pts(L);
   std::vector<double> lam(L);
   for (int p = 0; p < L; ++p) {
     const int f = fft_freq(L, Py, p);
