@@ -214,18 +214,25 @@ hipError_t launch_norm(const double* v, size_t N, RedWork rw, HostStatus* hs, hi
 hipError_t launch_residual(const double* b, const double* w, double* r, size_t N,
                            RedWork rw, KrylovState* ks, HostStatus* hs, hipStream_t s,
                            const Members& mb = Members::one());
-// h_i = <v_i, w>, i < nv, into column j of H (second = false) or into ks->h2
-// (second = true: the reorthogonalisation pass).
+// h_i = <v_i, w>, i < nv.  finish: into column j of H (second = false) or into
+// ks->h2 (second = true: the reorthogonalisation pass); otherwise (nv <= kChunk)
+// the partials are left for the kernel that uses them.
 hipError_t launch_multidot(const double* V, size_t ldv, int nv, const double* w, size_t N,
-                           RedWork rw, KrylovState* ks, int j, bool second, hipStream_t s,
-                           const Members& mb = Members::one());
-// vout = w - sum_i c_i v_i with c = column j of H (second = false) or ks->h2;
-// finish = true also takes ||vout|| and does the Givens step (adding h2 into
-// column j first when second = true).
-hipError_t launch_axpy_givens(const double* V, size_t ldv, int nv, const double* w,
-                              double* vout, size_t N, RedWork rw, KrylovState* ks, int j,
-                              bool second, bool finish, HostStatus* hs, hipStream_t s,
-                              const Members& mb = Members::one());
+                           RedWork rw, KrylovState* ks, int j, bool second, bool finish,
+                           hipStream_t s, const Members& mb = Members::one());
+// The finishing kernel of one chunk's dots: dst[v0 + v] from nb partials each.
+hipError_t launch_multidot_finish(int nb, int nv, RedWork rw, KrylovState* ks, double* dst, int v0,
+                                  bool second, hipStream_t s, const Members& mb = Members::one());
+// The orthogonalisation of one Arnoldi step, vout = w - sum_{i<nv} h_i v_i by
+// one (reorth = false) or two passes of classical Gram-Schmidt: first the dots
+// of the first pass, then everything else: the updates, the second pass's dots,
+// ||vout||, the Givens step of column j and the residual estimate in hs.
+hipError_t launch_orth_dots(const double* V, size_t ldv, int nv, const double* w, size_t N,
+                            RedWork rw, KrylovState* ks, int j, hipStream_t s,
+                            const Members& mb = Members::one());
+hipError_t launch_orth_update(const double* V, size_t ldv, int nv, const double* w, double* vout,
+                              size_t N, RedWork rw, KrylovState* ks, int j, bool reorth,
+                              HostStatus* hs, hipStream_t s, const Members& mb = Members::one());
 // x += sum_{i<jc} y_i Z_i with R y = g; scaled = true multiplies y_i by
 // vscale[i] (Z = the unnormalised basis V: left preconditioning).
 // Batched: member slot k uses jc[k] vectors (jcs given; jc = their maximum).

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kRedThreads) void k_rhs(const double* __restrict__ 
     acc[0] += bi * bi;
     acc[1] += (isfinite(bi) && isfinite(xi)) ? 0.0 : 1.0;
   }
-  publish_partials<2>(acc, 2, rw, sh);
+  publish_partials<2>(acc, rw.partial, sh);
 }
 
 __global__ __launch_bounds__(kFinishThreads) void k_rhs_finish(RedWork rw, int nb, HostStatus* hs,
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kRedThreads) void k_residual(const double* __restri
     r[i] = ri;
     acc[0] += ri * ri;
   }
-  publish_partials<1>(acc, 1, rw, sh);
+  publish_partials<1>(acc, rw.partial, sh);
 }
 
 // Start of a restart cycle: beta = ||r||, g = (beta, 0, ...), vscale[0] = 1/beta.
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kRedThreads) void k_dot(const double* __restrict__ 
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
        i += (size_t)gridDim.x * blockDim.x)
     acc[0] += a[i] * b[i];
-  publish_partials<1>(acc, 1, rw, sh);
+  publish_partials<1>(acc, rw.partial, sh);
 }
 
 // hs->bnorm = sqrt(<a, a>) from k_dot partials

@@ -1,17 +1,18 @@
 // Fused multi-dot of the Arnoldi step (classical Gram-Schmidt projections):
-// h_i = vscale[i] * <V_i, w> for i < nv in one pass over the basis, written to
-// column j of the Hessenberg matrix.  The vector count is a template
-// parameter, so every basis load is unconditional and the loop unrolls: all
-// NV + 1 streams are in flight at once.  nv > kChunk runs in chunks.
-#include "krylov_common.hpp"
+// h_i = vscale[i] * <V_i, w> for i < nv in one pass over the basis.  The vector
+// count is a template parameter, so every basis load is unconditional and the
+// loop unrolls: all NV + 1 streams are in flight at once.  nv > kChunk runs in
+// chunks.  Short vectors leave their partials to the next kernel (krylov_orth.hpp);
+// long ones and chunks are finished into column j of the Hessenberg matrix.
+#include "krylov_orth.hpp"
 
 namespace rsfde {
 
-template <int NV>
+template <int NV, int W>
 __global__ __launch_bounds__(kRedThreads) void k_multidot(const double* __restrict__ V, size_t ldv,
                                                           const double* __restrict__ w, size_t N,
-                                                          RedWork rw, KrylovState* ks, int j,
-                                                          int v0, const Members mb) {
+                                                          RedWork rw, bool second,
+                                                          const Members mb) {
   __shared__ double sh[16 * NV];
   {  // member of a batched launch (grid dimension y)
     const size_t mo = mb.off(blockIdx.y);
@@ -22,30 +23,31 @@ __global__ __launch_bounds__(kRedThreads) void k_multidot(const double* __restri
   double acc[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-  const size_t N2 = N / 2;
-  const double2* w2 = reinterpret_cast<const double2*>(w);
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N2;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N / W;
        i += (size_t)gridDim.x * blockDim.x) {
-    const double2 wv = w2[i];
-    double2 x[NV];
+    Vals<W> wv, x[NV];
+    wv.load(w, i);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) x[v] = reinterpret_cast<const double2*>(V + (size_t)v * ldv)[i];
+    for (int v = 0; v < NV; ++v) x[v].load(V + (size_t)v * ldv, i);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] += x[v].x * wv.x + x[v].y * wv.y;
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int k = 0; k < W; ++k) acc[v] += x[v].v[k] * wv.v[k];
   }
-  if ((N & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (W == 2 && (N & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
     const double wl = w[N - 1];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] += V[(size_t)v * ldv + N - 1] * wl;
   }
-  publish_partials<NV>(acc, NV, rw, sh);
+  publish_partials<NV>(acc, orth_partials(rw, second), sh);
 }
 
 // dst[v0 + v] = vscale[v0 + v] * (sum of the partials of value v), v < nv;
 // dst is column j of H or the reorthogonalisation vector h2.
 __global__ __launch_bounds__(kFinishThreads) void k_multidot_finish(RedWork rw, int nb, int nv,
                                                                     KrylovState* ks, double* dst,
-                                                                    int v0, const Members mb) {
+                                                                    int v0, bool second,
+                                                                    const Members mb) {
   {
     const size_t mo = mb.off(blockIdx.y);
     rw.partial += mo;
@@ -53,42 +55,52 @@ __global__ __launch_bounds__(kFinishThreads) void k_multidot_finish(RedWork rw, 
     dst += mo;
   }
   const int lane = threadIdx.x & 63;
+  const RedWork part{orth_partials(rw, second)};
   for (int v = threadIdx.x >> 6; v < nv; v += kFinishThreads / 64) {
-    const double t = wave_total(rw, v, nb);
+    const double t = wave_total(part, v, nb);
     if (lane == 0) dst[v0 + v] = ks->vscale[v0 + v] * t;
   }
 }
 
-using MultidotFn = void (*)(const double*, size_t, const double*, size_t, RedWork, KrylovState*,
-                            int, int, const Members&, dim3, hipStream_t);
+using MultidotFn = void (*)(const double*, size_t, const double*, size_t, RedWork, bool,
+                            const Members&, dim3, hipStream_t);
 
-template <int NV>
+template <int NV, int W>
 static void run_multidot(const double* V, size_t ldv, const double* w, size_t N, RedWork rw,
-                         KrylovState* ks, int j, int v0, const Members& mb, dim3 g, hipStream_t s) {
-  hipLaunchKernelGGL(k_multidot<NV>, g, dim3(kRedThreads), 0, s, V, ldv, w, N, rw, ks, j, v0, mb);
+                         bool second, const Members& mb, dim3 g, hipStream_t s) {
+  hipLaunchKernelGGL((k_multidot<NV, W>), g, dim3(kRedThreads), 0, s, V, ldv, w, N, rw, second, mb);
 }
-template <int... I>
+template <int W, int... I>
 static constexpr std::array<MultidotFn, sizeof...(I)> multidot_table(std::integer_sequence<int, I...>) {
-  return {&run_multidot<I + 1>...};
+  return {&run_multidot<I + 1, W>...};
 }
-static const auto kMultidot = multidot_table(std::make_integer_sequence<int, kChunk>{});
+static const auto kMultidot1 = multidot_table<1>(std::make_integer_sequence<int, kChunk>{});
+static const auto kMultidot2 = multidot_table<2>(std::make_integer_sequence<int, kChunk>{});
 
 hipError_t launch_multidot(const double* V, size_t ldv, int nv, const double* w, size_t N,
-                           RedWork rw, KrylovState* ks, int j, bool second, hipStream_t s,
-                           const Members& mb) {
-  if (nv < 1 || nv > kMaxRestart) return hipErrorInvalidValue;
+                           RedWork rw, KrylovState* ks, int j, bool second, bool finish,
+                           hipStream_t s, const Members& mb) {
+  if (nv < 1 || nv > kMaxRestart || (!finish && nv > kChunk)) return hipErrorInvalidValue;
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
   double* dst = second ? ks->h2 : ks->H + (size_t)j * kLdH;
+  const int nb = orth_blocks(N);
   for (int v0 = 0; v0 < nv; v0 += kChunk) {
     const int n = nv - v0 < kChunk ? nv - v0 : kChunk;
-    const int nb = red_blocks(N);
-    kMultidot[n - 1](V + (size_t)v0 * ldv, ldv, w, N, rw, ks, j, v0, mb, dim3(nb, mb.n), s);
-    hipLaunchKernelGGL(k_multidot_finish, dim3(1, mb.n), dim3(kFinishThreads), 0, s, rw, nb, n, ks,
-                       dst, v0, mb);
+    (orth_small(N) ? kMultidot1 : kMultidot2)[n - 1](V + (size_t)v0 * ldv, ldv, w, N, rw, second,
+                                                     mb, dim3(nb, mb.n), s);
+    if (finish)
+      if (hipError_t e = launch_multidot_finish(nb, n, rw, ks, dst, v0, second, s, mb)) return e;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_multidot_finish(int nb, int nv, RedWork rw, KrylovState* ks, double* dst, int v0,
+                                  bool second, hipStream_t s, const Members& mb) {
+  hipLaunchKernelGGL(k_multidot_finish, dim3(1, mb.n), dim3(kFinishThreads), 0, s, rw, nb, nv, ks,
+                     dst, v0, second, mb);
+  return hipGetLastError();
 }
 
 }  // namespace rsfde

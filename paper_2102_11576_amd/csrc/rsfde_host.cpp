@@ -812,23 +812,11 @@ int solve_core(Plan* P, double* x, const rsfde_solver_opts* o, rsfde_stats* st, 
       double* vnext = P->V + (size_t)(j + 1) * ld;
       {
         ProfScope ps(P, s, kCatMultidot, 8.0 * (j + 2) * (double)N);
-        CK(launch_multidot(P->V, ld, j + 1, wv, N, P->rw, P->ks, j, false, s));
+        CK(launch_orth_dots(P->V, ld, j + 1, wv, N, P->rw, P->ks, j, s));
       }
-      {
-        ProfScope ps(P, s, kCatAxpy, 8.0 * (j + 3) * (double)N);
-        CK(launch_axpy_givens(P->V, ld, j + 1, wv, vnext, N, P->rw, P->ks, j, false, !reorth,
-                              P->hs_dev, s));
-      }
-      if (reorth) {  // classical Gram-Schmidt, second pass
-        {
-          ProfScope ps(P, s, kCatMultidot, 8.0 * (j + 2) * (double)N);
-          CK(launch_multidot(P->V, ld, j + 1, vnext, N, P->rw, P->ks, j, true, s));
-        }
-        {
-          ProfScope ps(P, s, kCatAxpy, 8.0 * (j + 3) * (double)N);
-          CK(launch_axpy_givens(P->V, ld, j + 1, vnext, vnext, N, P->rw, P->ks, j, true, true,
-                                P->hs_dev, s));
-        }
+      {  // per Gram-Schmidt pass: the basis and one vector read, one written
+        ProfScope ps(P, s, kCatAxpy, 8.0 * (reorth ? 2 * (j + 3) : j + 3) * (double)N);
+        CK(launch_orth_update(P->V, ld, j + 1, wv, vnext, N, P->rw, P->ks, j, reorth, P->hs_dev, s));
       }
       CK(hipEventRecord(P->ev[j & 1], s));
       // Look one iteration behind: the device runs step j while the host
@@ -2101,13 +2089,8 @@ int batch_solve(rsfde_batch_s* Bt, const rsfde_solver_opts* o, rsfde_stats* st, 
       double* zj = Zb + (size_t)j * ld;
       double* vnext = V + (size_t)(j + 1) * ld;
       if (int rc = batch_precond_any(Bt, o->precision, vj, &ks->vscale[j], zj, w, mi, s)) return rc;
-      CK(launch_multidot(V, ld, j + 1, w, N, rw, ks, j, false, s, mi));
-      CK(launch_axpy_givens(V, ld, j + 1, w, vnext, N, rw, ks, j, false, !reorth, Bt->hs_dev, s, mi));
-      if (reorth) {
-        CK(launch_multidot(V, ld, j + 1, vnext, N, rw, ks, j, true, s, mi));
-        CK(launch_axpy_givens(V, ld, j + 1, vnext, vnext, N, rw, ks, j, true, true, Bt->hs_dev, s,
-                              mi));
-      }
+      CK(launch_orth_dots(V, ld, j + 1, w, N, rw, ks, j, s, mi));
+      CK(launch_orth_update(V, ld, j + 1, w, vnext, N, rw, ks, j, reorth, Bt->hs_dev, s, mi));
       CK(hipEventRecord(Bt->ev, s));
       CK(hipEventSynchronize(Bt->ev));
       std::vector<int> still;

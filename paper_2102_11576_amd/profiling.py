@@ -31,7 +31,7 @@ CSRC = os.path.join(HERE, "csrc")
 # kernel-name pattern -> family used by rsfde_profile_read
 FAMILIES = [
     (r"k_multidot<", "multidot"),
-    (r"k_axpy_givens<", "axpy_givens"),
+    (r"k_axpy_(givens|dot)<", "axpy_givens"),
     (r"k_update<", "update"),
     (r"k_mv_rows<", "mv_rows"),
     (r"k_mv_cols<", "mv_cols"),
@@ -113,10 +113,10 @@ def stats(path: str) -> str:
 def _alg_bytes(name: str, n1: int, n2: int) -> float:
     """Algorithmic bytes of one launch (each operand read once, result written once)."""
     N, S = n1 * n2, (n1 + 1) * n2
-    m = re.search(r"k_multidot<(\d+)>", name)
+    m = re.search(r"k_multidot<(\d+), \d>", name)
     if m:
         return 8.0 * (int(m.group(1)) + 1) * N
-    m = re.search(r"k_axpy_givens<(\d+), true>", name)
+    m = re.search(r"k_axpy_(?:givens<(?=\d+, \d, true)|dot<)(\d+)", name)
     if m:
         return 8.0 * (int(m.group(1)) + 2) * N
     m = re.search(r"k_update<(\d+)>", name)
