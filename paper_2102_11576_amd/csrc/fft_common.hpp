@@ -97,7 +97,10 @@ constexpr bool exchange_in_wave() {
 // reordering the LDS accesses).
 template <typename T, class F, int TF, int TT, int ST = 1, int TW = 0>
 __device__ __forceinline__ void lds_exchange(cpx<T>* reg, int tau, T* lds, bool act = true) {
-  constexpr bool wave_local = TW > 0 && exchange_in_wave<F, TF, TT, TW>();
+  // (a transform whose TPF * ST threads are one aligned group inside a
+  // wavefront exchanges within it at every stage)
+  constexpr bool wave_local =
+      TW > 0 && (F::TPF * ST <= 64 || exchange_in_wave<F, TF, TT, TW>());
   auto sync = [] {
     if constexpr (wave_local) {
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");

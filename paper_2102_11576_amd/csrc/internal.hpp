@@ -45,6 +45,25 @@ struct Members {
 // mv_rows at 2047^2 (L = 4096) 59.6 -> 68.6 us, at 4095^2 (L = 8192) 322 -> 503.
 constexpr int fft_pts(int L) { return L <= 4 ? L : (L <= 256 ? 4 : (L <= 1024 ? 8 : 16)); }
 
+// Transforms per block of the row passes: one wavefront's worth, or one
+// transform where that takes more than a wavefront.  A transform inside one
+// wavefront needs no block barrier, and small grids spread over more CUs: with
+// 256-thread blocks 63^2 filled four of them (fused pass C 10.6 -> 7.7 us).
+// Long views gain or lose little (255^3: pass A 67 -> 62 us, mv_rows 89 -> 92).
+constexpr int row_ffts(int tpf) { return tpf >= 64 ? 1 : 64 / tpf; }
+
+// Column pairs per block of the column passes, where tpf threads run one
+// transform.  Large views: 512 threads (16 pairs at most), so that a block
+// reads whole lines of each row.  Views whose large blocks would not give every
+// CU one (kSmallGridBlocks): a wavefront's worth (at least 2 pairs).  At 63^2
+// pass B 8.4 -> 4.9 us and mv_cols 6.7 -> 3.9, at 256^2 mv_cols 9.0 -> 6.5;
+// beyond the line small blocks read part lines and lose (mv_cols at 255^3 +9 %).
+constexpr int kSmallGridBlocks = 256;
+constexpr int col_ffts_large(int tpf) {
+  return 512 / tpf > 16 ? 16 : (512 / tpf > 0 ? 512 / tpf : 1);
+}
+constexpr int col_ffts_small(int tpf) { return tpf >= 64 ? 2 : 64 / tpf; }
+
 // Values the device writes for the host after each Arnoldi step.  Lives in
 // pinned, device-visible host memory; the host reads it after an event.
 struct HostStatus {

@@ -27,16 +27,13 @@ struct MvCfg {
     return true;
   }
   static constexpr int TPF = F::TPF;
-  static constexpr int BR = (256 / TPF) > 0 ? (256 / TPF) : 1;             // FFTs per row block
+  static constexpr int BR = row_ffts(TPF);  // FFTs per row block
+  static constexpr int THR_R = BR * TPF;
   // column pairs per column block: two at L = 1024 and 2048 (two-dimensional
   // grids of 511 or 1023 columns: more, smaller blocks spread them over more
-  // CUs; the 3-D plans' many-column views keep the larger blocks), 512 / TPF
-  // otherwise
-  static constexpr int BC = (L >= 1024 && L <= 2048)
-                                ? 2
-                                : ((512 / TPF) > 16 ? 16 : ((512 / TPF) > 0 ? (512 / TPF) : 1));
-  static constexpr int THR_R = BR * TPF;
-  static constexpr int THR_C = BC * TPF;
+  // CUs); up to L = 512 by the size of the view
+  static constexpr int BCL = (L >= 1024 && L <= 2048) ? 2 : col_ffts_large(TPF);
+  static constexpr int BCS = L <= 512 ? col_ffts_small(TPF) : BCL;
 };
 
 // --------------------------------------------------------------------------
@@ -143,14 +140,14 @@ __global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu
 // compile-time mode keeps the epilogue's loads free of per-element branches,
 // which measured 10 % faster at n = 2047.
 // --------------------------------------------------------------------------
-template <int L, int MODE, bool TT, typename ZT = double>
-__global__ __launch_bounds__(MvCfg<L>::THR_C) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_cols(
+template <int L, int BC, int MODE, bool TT, typename ZT = double>
+__global__ __launch_bounds__(MvCfg<L>::TPF* BC) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_cols(
     const ZT* __restrict__ z, const double* __restrict__ t, double* __restrict__ out,
     const double* __restrict__ sym, const cpx<double>* __restrict__ tw, int n1, int n2,
     double coef, size_t bstride, const Members mb, const double* __restrict__ mk) {
   using C = MvCfg<L>;
   using F = typename C::F;
-  __shared__ double lds[C::BC * lds_len(L)];
+  __shared__ double lds[BC * lds_len(L)];
   {  // slice (grid dimension y) and member of a batched launch (dimension z)
     const size_t mo = mb.off(blockIdx.z);
     if (mk) coef = -mk[mo];
@@ -160,9 +157,9 @@ __global__ __launch_bounds__(MvCfg<L>::THR_C) __attribute__((amdgpu_waves_per_eu
     if constexpr (MODE == 0) t += off;
   }
   const int tid = threadIdx.x;
-  const int b = tid % C::BC, tau = tid / C::BC;
+  const int b = tid % BC, tau = tid / BC;
   const int strip = xcd_remap(blockIdx.x, gridDim.x);
-  const int cp = strip * C::BC + b;
+  const int cp = strip * BC + b;
   const int ca = 2 * cp, cb = 2 * cp + 1;
   const bool va = ca < n1, vb = cb < n1;
   cpx<double> reg[F::PP];
@@ -183,14 +180,14 @@ __global__ __launch_bounds__(MvCfg<L>::THR_C) __attribute__((amdgpu_waves_per_eu
     });
   }
   double* my = lds + b;  // regions interleaved (stride BC)
-  fft_forward<double, F, true, C::BC>(reg, tau, tw, my);
+  fft_forward<double, F, true, BC>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const double s = sym[F::pos(F::NS - 1, tau, e)] * coef;
     reg[e].re *= s;
     reg[e].im *= s;
   });
-  fft_inverse<double, F, true, C::BC>(reg, tau, tw, my);
+  fft_inverse<double, F, true, BC>(reg, tau, tw, my);
   const int hp = (n2 + 1) >> 1;
   const int cca = va ? ca : 0;
   if constexpr (MODE == 0 && TT) {
@@ -256,36 +253,48 @@ static hipError_t mv_rows_impl(const double* z, const uint8_t* mask, double* out
   return hipGetLastError();
 }
 
+template <int L, int BC>
+static hipError_t mv_cols_bc(const void* zv, const double* t, double* out, const double* sym,
+                             const cpx<double>* twc, int n1, int n2, double coef, int mode,
+                             hipStream_t s, int batch, size_t bstride, bool tiled,
+                             const Members& mb, const double* mk, bool z32) {
+  const double* z = (const double*)zv;
+  const int pairs = (n1 + 1) / 2;
+  const dim3 grid((pairs + BC - 1) / BC, batch, mb.n), thr(BC * MvCfg<L>::TPF);
+  if (z32)
+    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, true, float>), grid, thr, 0, s, (const float*)zv, t,
+                       out, sym, twc, n1, n2, coef, bstride, mb, mk);
+  else if (mode != 0)
+    hipLaunchKernelGGL((k_mv_cols<L, BC, 1, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+                       coef, bstride, mb, mk);
+  else if (tiled)
+    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, true>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+                       coef, bstride, mb, mk);
+  else
+    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+                       coef, bstride, mb, mk);
+  return hipGetLastError();
+}
+
 template <int L>
-static hipError_t mv_cols_impl(const void* zv, const double* t, double* out, const double* sym,
+static hipError_t mv_cols_impl(const void* z, const double* t, double* out, const double* sym,
                                const void* tw, int n1, int n2, double coef, int mode, hipStream_t s,
                                int batch, size_t bstride, bool tiled, const Members& mb,
                                const double* mk, bool z32) {
-  const double* z = (const double*)zv;
   using C = MvCfg<L>;
-  const int pairs = (n1 + 1) / 2;
-  const int blocks = (pairs + C::BC - 1) / C::BC;
   if (batch < 1 || batch > 65535) return hipErrorInvalidValue;
   if (tiled && (mode != 0 || batch != 1)) return hipErrorInvalidValue;
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
-  const dim3 grid(blocks, batch, mb.n), thr(C::THR_C);
+  if (z32 && (mode != 0 || !tiled)) return hipErrorInvalidValue;
   const cpx<double>* twc = (const cpx<double>*)tw;
-  if (z32) {
-    if (mode != 0 || !tiled) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_mv_cols<L, 0, true, float>), grid, thr, 0, s, (const float*)zv, t, out,
-                       sym, twc, n1, n2, coef, bstride, mb, mk);
-    return hipGetLastError();
+  if constexpr (C::BCS < C::BCL) {
+    const long blocks = (long)((n1 + 1) / 2 + C::BCL - 1) / C::BCL * batch * mb.n;
+    if (blocks < kSmallGridBlocks)
+      return mv_cols_bc<L, C::BCS>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride,
+                                   tiled, mb, mk, z32);
   }
-  if (mode != 0)
-    hipLaunchKernelGGL((k_mv_cols<L, 1, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
-                       coef, bstride, mb, mk);
-  else if (tiled)
-    hipLaunchKernelGGL((k_mv_cols<L, 0, true>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2, coef,
-                       bstride, mb, mk);
-  else
-    hipLaunchKernelGGL((k_mv_cols<L, 0, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
-                       coef, bstride, mb, mk);
-  return hipGetLastError();
+  return mv_cols_bc<L, C::BCL>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride, tiled,
+                               mb, mk, z32);
 }
 
 #define RSFDE_L_CASES(X) \

@@ -31,10 +31,14 @@ template <int L>
 struct CdCfg {
   using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
-  static constexpr int BR = (256 / TPF) > 0 ? (256 / TPF) : 1;  // lines per row block
-  static constexpr int BC = (256 / TPF) > 16 ? 16 : ((256 / TPF) > 0 ? (256 / TPF) : 1);
+  static constexpr int BR = row_ffts(TPF);  // lines per row block
+  static constexpr int BCL = (256 / TPF) > 16 ? 16 : ((256 / TPF) > 0 ? (256 / TPF) : 1);
+  static constexpr int BCS = L <= 512 && col_ffts_small(TPF) < BCL ? col_ffts_small(TPF) : BCL;
   static constexpr int THR_R = BR * TPF;
-  static constexpr int THR_C = BC * TPF;
+  // A view that the large column blocks cannot spread over the CUs.
+  static bool small_cols(long cols, long copies) {
+    return BCS < BCL && (cols + BCL - 1) / BCL * copies < kSmallGridBlocks;
+  }
 };
 
 // In: reg[e].re = x at sequence position pos(0, tau, e) (zero at positions >= n).
@@ -96,17 +100,17 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
 // Columns: W = S_y W1 column, then Y1 = S_y(W / E1) and Y2 = S_y(W / E2).
 // Thread layout (tau, b) with b fastest: a wavefront touches BC adjacent
 // columns of each row it reads.
-template <typename T, int L>
-__global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_cols(
+template <typename T, int L, int BC>
+__global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     const T* __restrict__ in, T* __restrict__ Y1, T* __restrict__ Y2,
     const double* __restrict__ lamx, const double* __restrict__ lamy,
     const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
     const cpx<T>* __restrict__ tw, int n1, int n2, double kx, double ky, double dpen) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BC * lds_len(L)];
-  const int b = threadIdx.x % C::BC, tau = threadIdx.x / C::BC;
-  const int c = xcd_remap(blockIdx.x, gridDim.x) * C::BC + b;
+  __shared__ T lds[BC * lds_len(L)];
+  const int b = threadIdx.x % BC, tau = threadIdx.x / BC;
+  const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < n1;
   T* my = lds + b;  // regions interleaved (stride BC)
   cpx<T> reg[F::PP];
@@ -116,7 +120,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_cols(
     reg[e].re = (vc && p < n2) ? in[(size_t)p * n1 + c] : T(0);
     reg[e].im = T(0);
   });
-  chirp_dst<T, F, C::BC>(reg, tau, chn, khat, tw, my, n2);
+  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
   const double ax = 1.0 - kx * (vc ? lamx[c] : 0.0);
   T w[F::PP];
   static_for<F::PP>([&](auto ee) {
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_cols(
     w[e] = p < n2 ? reg[e].re : T(0);
     reg[e].re = w[e] / e1;
   });
-  chirp_dst<T, F, C::BC>(reg, tau, chn, khat, tw, my, n2);
+  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_cols(
     const T e2 = (T)(ax + dpen - ky * (p < n2 ? lamy[p] : 0.0));
     reg[e].re = w[e] / e2;
   });
-  chirp_dst<T, F, C::BC>(reg, tau, chn, khat, tw, my, n2);
+  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -181,19 +185,19 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
 // S_y in for the columns c < ncol of `batch` slices [rows][ncol], slice b at
 // offset b * bstride; with inB given, grid dimension z = 1 transforms inB into
 // outB in the same launch.  in and out must not overlap.
-template <typename T, int L>
-__global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_dst_cols(
+template <typename T, int L, int BC>
+__global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_dst_cols(
     const T* __restrict__ inA, T* __restrict__ outA, const T* __restrict__ inB,
     T* __restrict__ outB, const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
     const cpx<T>* __restrict__ tw, int ncol, int rows, size_t bstride) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BC * lds_len(L)];
+  __shared__ T lds[BC * lds_len(L)];
   const size_t off = (size_t)blockIdx.y * bstride;
   const T* in = (blockIdx.z ? inB : inA) + off;
   T* out = (blockIdx.z ? outB : outA) + off;
-  const int b = threadIdx.x % C::BC, tau = threadIdx.x / C::BC;
-  const int c = xcd_remap(blockIdx.x, gridDim.x) * C::BC + b;
+  const int b = threadIdx.x % BC, tau = threadIdx.x / BC;
+  const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < ncol;
   T* my = lds + b;  // regions interleaved (stride BC)
   cpx<T> reg[F::PP];
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_C) void k_cd_dst_cols(
     reg[e].re = (vc && p < rows) ? in[(size_t)p * ncol + c] : T(0);
     reg[e].im = T(0);
   });
-  chirp_dst<T, F, C::BC>(reg, tau, chn, khat, tw, my, rows);
+  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, rows);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -241,10 +245,14 @@ hipError_t launch_cd_cols(int L, const T* in, T* Y1, T* Y2, const double* lamx,
 #define X(LL)                                                                                  \
   case LL: {                                                                                   \
     using C = CdCfg<LL>;                                                                       \
-    const int blocks = (n1 + C::BC - 1) / C::BC;                                               \
-    hipLaunchKernelGGL((k_cd_cols<T, LL>), dim3(blocks), dim3(C::THR_C), 0, s, in, Y1, Y2, lamx, \
-                       lamy, (const cpx<T>*)chn, (const cpx<T>*)khat, (const cpx<T>*)tw, n1, n2, \
-                       kx, ky, dpen);                                                          \
+    auto go = [&](auto bc) {                                                                   \
+      constexpr int BC = decltype(bc)::value;                                                  \
+      hipLaunchKernelGGL((k_cd_cols<T, LL, BC>), dim3((n1 + BC - 1) / BC), dim3(BC * C::TPF), 0, s, \
+                         in, Y1, Y2, lamx, lamy, (const cpx<T>*)chn, (const cpx<T>*)khat,      \
+                         (const cpx<T>*)tw, n1, n2, kx, ky, dpen);                             \
+    };                                                                                         \
+    if (C::small_cols(n1, 1)) go(std::integral_constant<int, C::BCS>{});                       \
+    else go(std::integral_constant<int, C::BCL>{});                                            \
     return hipGetLastError();                                                                  \
   }
     RSFDE_CD_CASES(X)
@@ -264,10 +272,15 @@ hipError_t launch_cd_dst_cols(int L, const T* inA, T* outA, const T* inB, T* out
 #define X(LL)                                                                                  \
   case LL: {                                                                                   \
     using C = CdCfg<LL>;                                                                       \
-    const dim3 grid((ncol + C::BC - 1) / C::BC, batch, inB ? 2 : 1);                           \
-    hipLaunchKernelGGL((k_cd_dst_cols<T, LL>), grid, dim3(C::THR_C), 0, s, inA, outA, inB,     \
-                       outB, (const cpx<T>*)chn, (const cpx<T>*)khat, (const cpx<T>*)tw, ncol, \
-                       rows, bstride);                                                         \
+    const int nz = inB ? 2 : 1;                                                                \
+    auto go = [&](auto bc) {                                                                   \
+      constexpr int BC = decltype(bc)::value;                                                  \
+      hipLaunchKernelGGL((k_cd_dst_cols<T, LL, BC>), dim3((ncol + BC - 1) / BC, batch, nz),    \
+                         dim3(BC * C::TPF), 0, s, inA, outA, inB, outB, (const cpx<T>*)chn,    \
+                         (const cpx<T>*)khat, (const cpx<T>*)tw, ncol, rows, bstride);         \
+    };                                                                                         \
+    if (C::small_cols(ncol, (long)batch * nz)) go(std::integral_constant<int, C::BCS>{});      \
+    else go(std::integral_constant<int, C::BCL>{});                                            \
     return hipGetLastError();                                                                  \
   }
     RSFDE_CD_CASES(X)

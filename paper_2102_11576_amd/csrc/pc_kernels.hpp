@@ -53,15 +53,15 @@ template <int L>
 struct PcCfg {
   using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
-  static constexpr int BR = (256 / TPF) > 0 ? (256 / TPF) : 1;
+  static constexpr int BR = row_ffts(TPF);
   static constexpr int THR_R = BR * TPF;
 };
 template <int L>
 struct PcColCfg {
   using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
-  static constexpr int BC = (512 / TPF) > 16 ? 16 : ((512 / TPF) > 0 ? (512 / TPF) : 1);
-  static constexpr int THR_C = BC * TPF;
+  static constexpr int BCL = col_ffts_large(TPF);
+  static constexpr int BCS = L <= 512 ? col_ffts_small(TPF) : BCL;
 };
 
 // --------------------------------------------------------------------------
@@ -160,15 +160,15 @@ __global__ __launch_bounds__(PcCfg<L>::THR_R) void k_pc_rows_fwd(
 // --------------------------------------------------------------------------
 // Pass B: slot-column pairs (ca, cb) of Q -> P1, P2 columns.
 // --------------------------------------------------------------------------
-template <typename T, int L, bool TL>
-__global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
+template <typename T, int L, int BC, bool TL>
+__global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     const T* __restrict__ Q, T* __restrict__ P1, T* __restrict__ P2,
     const T* __restrict__ lamx_slot, const T* __restrict__ lamy_pos,
     const cpx<T>* __restrict__ tw, int n1, int n2, T kx, T ky, T dpen, T halfK, const Members mb,
     const double* __restrict__ mk) {
   using C = PcColCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BC * lds_len(L)];
+  __shared__ T lds[BC * lds_len(L)];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     const size_t mt = mo * (sizeof(double) / sizeof(T));
@@ -181,15 +181,15 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
     }
   }
   const int tid = threadIdx.x;
-  const int b = tid % C::BC, tau = tid / C::BC;
+  const int b = tid % BC, tau = tid / BC;
   const int strip = xcd_remap(blockIdx.x, gridDim.x);
   // Column pair of FFT b.  Tiled: (2c, 2c+1), adjacent in one tile row.
   // Natural: (base + b, base + b + BC) of the block's 2 BC columns, so that
   // each inverse sweep writes BC adjacent columns of a row (with (2c, 2c+1)
   // every sweep wrote every other column and half-written lines doubled the
   // write traffic).
-  const int ca = TL ? 2 * (strip * C::BC + b) : 2 * C::BC * strip + b;
-  const int cb = TL ? ca + 1 : ca + C::BC;
+  const int ca = TL ? 2 * (strip * BC + b) : 2 * BC * strip + b;
+  const int cb = TL ? ca + 1 : ca + BC;
   const int ld = n1 + 1, hp = (n2 + 1) >> 1;
   const bool va = ca < ld, vb = cb < ld;  // tiled: ld and ca even, both or neither
   using V2 = typename Vec2<T>::type;
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
   });
   T* my = lds + b;  // regions interleaved (stride BC)
   // (no register materialisation between the sweeps here: it measured slower)
-  fft_forward<T, F, false, C::BC>(reg, tau, tw, my);
+  fft_forward<T, F, false, BC>(reg, tau, tw, my);
   // spectrum = 2 rho_b - 2i rho_a; keep rho_b for the second column
   const T lxa = va ? kx * lamx_slot[ca] : (T)0;
   const T lxb = vb ? kx * lamx_slot[cb] : (T)0;
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
     reg[e].re = r * e1;
     reg[e].im = -r * e2;
   });
-  fft_inverse<T, F, false, C::BC>(reg, tau, tw, my);
+  fft_inverse<T, F, false, BC>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
     reg[e].re = r * e1;
     reg[e].im = -r * e2;
   });
-  fft_inverse<T, F, false, C::BC>(reg, tau, tw2, my);
+  fft_inverse<T, F, false, BC>(reg, tau, tw2, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -289,14 +289,14 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_pc_cols(
 // real part, column cb of inB in the imaginary part, both odd-extended; the
 // spectrum is 2 sigma_b - 2i sigma_a, read at frequencies 1..rows.
 // --------------------------------------------------------------------------
-template <typename T, int L>
-__global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_dst_cols(
+template <typename T, int L, int BC>
+__global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
     const T* __restrict__ inA, const T* __restrict__ inB, T* __restrict__ outA,
     T* __restrict__ outB, const cpx<T>* __restrict__ tw, int ncol, int cstride, int coff,
     int rows, int ld, size_t bstride) {
   using C = PcColCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BC * lds_len(L)];
+  __shared__ T lds[BC * lds_len(L)];
   {
     const size_t off = (size_t)blockIdx.y * bstride;
     inA += off;
@@ -305,8 +305,8 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_dst_cols(
     outB += off;
   }
   const int tid = threadIdx.x;
-  const int b = tid % C::BC, tau = tid / C::BC;
-  const int c = xcd_remap(blockIdx.x, gridDim.x) * C::BC + b;
+  const int b = tid % BC, tau = tid / BC;
+  const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool valid = c < ncol;
   const int ca = c * cstride, cb = ca + coff;
   cpx<T> reg[F::PP];
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(PcColCfg<L>::THR_C) void k_dst_cols(
     reg[e].im = ok ? sgn * inB[(size_t)row * ld + cb] : (T)0;
   });
   T* my = lds + b;  // regions interleaved (stride BC)
-  fft_forward<T, F, false, C::BC>(reg, tau, tw, my);
+  fft_forward<T, F, false, BC>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int f = fft_freq(L, fft_pts(L), F::pos(F::NS - 1, tau, e));
@@ -567,17 +567,28 @@ static hipError_t pc_rows_fwd_impl(const double* v, const double* sig, T* Q, con
   return hipGetLastError();
 }
 
+// A view that the large column blocks cannot spread over the CUs.
+template <int L>
+static bool small_cols(long cols, long copies) {
+  using C = PcColCfg<L>;
+  return C::BCS < C::BCL && (cols + C::BCL - 1) / C::BCL * copies < kSmallGridBlocks;
+}
+
 template <typename T, int L, bool TL>
 static hipError_t pc_cols_impl(const T* Q, T* P1, T* P2, const T* lamx, const T* lamy,
                                const void* tw, int n1, int n2, double kx, double ky, double dpen,
                                double Kfac, hipStream_t s, const Members& mb, const double* mk) {
   using C = PcColCfg<L>;
   const int pairs = (n1 + 1) / 2;
-  const int blocks = (pairs + C::BC - 1) / C::BC;
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_pc_cols<T, L, TL>), dim3(blocks, 1, mb.n), dim3(C::THR_C), 0, s, Q, P1, P2,
-                     lamx, lamy, (const cpx<T>*)tw, n1, n2, (T)kx, (T)ky, (T)dpen,
-                     (T)(0.5 * Kfac), mb, mk);
+  auto go = [&](auto bc) {
+    constexpr int BC = decltype(bc)::value;
+    hipLaunchKernelGGL((k_pc_cols<T, L, BC, TL>), dim3((pairs + BC - 1) / BC, 1, mb.n),
+                       dim3(BC * C::TPF), 0, s, Q, P1, P2, lamx, lamy, (const cpx<T>*)tw, n1, n2,
+                       (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
+  };
+  if (small_cols<L>(pairs, mb.n)) go(std::integral_constant<int, C::BCS>{});
+  else go(std::integral_constant<int, C::BCL>{});
   return hipGetLastError();
 }
 
@@ -624,9 +635,14 @@ static hipError_t dst_cols_impl(const T* inA, const T* inB, T* outA, T* outB, co
                                 size_t bstride, hipStream_t s) {
   using C = PcColCfg<L>;
   if (L != 2 * (rows + 1) || batch < 1 || batch > 65535 || ncol < 1) return hipErrorInvalidValue;
-  const int blocks = (ncol + C::BC - 1) / C::BC;
-  hipLaunchKernelGGL((k_dst_cols<T, L>), dim3(blocks, batch), dim3(C::THR_C), 0, s, inA, inB, outA,
-                     outB, (const cpx<T>*)tw, ncol, cstride, coff, rows, ld, bstride);
+  auto go = [&](auto bc) {
+    constexpr int BC = decltype(bc)::value;
+    hipLaunchKernelGGL((k_dst_cols<T, L, BC>), dim3((ncol + BC - 1) / BC, batch), dim3(BC * C::TPF),
+                       0, s, inA, inB, outA, outB, (const cpx<T>*)tw, ncol, cstride, coff, rows, ld,
+                       bstride);
+  };
+  if (small_cols<L>(ncol, batch)) go(std::integral_constant<int, C::BCS>{});
+  else go(std::integral_constant<int, C::BCL>{});
   return hipGetLastError();
 }
 

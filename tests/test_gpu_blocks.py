@@ -1,0 +1,78 @@
+"""Column passes on both sides of the rule that picks their block size, and the
+row and column passes at the lengths where the points per thread change
+(L = 256 | 512 | 1024), against the oracle.
+
+The rule: a view whose large column blocks (512 threads) would number fewer
+than 256 takes small ones.  On 3-D plans the z pass sees n1 n2 columns and the
+y pass n3 slices of n1, so both sides are reached by small plans.  Bars as in
+the 3-D parity tests: product 1e-13 ||M||_inf ||z||_inf, FP64 preconditioner
+1e-12 and FP32 2e-5 of the result's largest value.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from bars import assert_precond
+from workloads.configs import domain_mask, SHAPES
+from workloads.three_d import ellipsoid_mask
+
+pytestmark = pytest.mark.gpu
+
+rsfde = pytest.importorskip("paper_2102_11576_amd")
+from paper_2102_11576_amd import RsfdePlan  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def _t(a):
+    return torch.as_tensor(np.ascontiguousarray(a), device=DEV).reshape(-1)
+
+
+# z views of 8001 and 8255 columns (L = 128: large from 8161 on, 16 pairs a
+# block); y views of 127 and 129 slices; L = 512 along y and z (8 pairs a
+# block: large from 4081 columns on); the chirp form on both sides
+@pytest.mark.parametrize("shape", [(127, 63, 63), (129, 64, 40), (65, 127, 63), (127, 15, 255),
+                                   (31, 255, 15), (63, 65, 200), (17, 255, 255), (63, 255, 7)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_operators3_across_block_rule(shape):
+    n1, n2, n3 = shape
+    box = (0.0, 1.0, -0.1, 1.2, 0.2, 1.1)
+    p = O.Problem3(n1, n2, n3, box, 1.55, 1.75, 1.85, 1.0, 0.8, 1.2, 1e-6, 1.0 / 16,
+                   ellipsoid_mask(n1, n2, n3))
+    rng = np.random.default_rng(n1 + 3 * n2 + 7 * n3)
+    V = rng.standard_normal(p.shape)
+    nm = 1.0 + p.d + 2 * sum(np.abs(c).sum() for c in (
+        p.cx * O.toeplitz_first_column(p.alpha1, n1), p.cy * O.toeplitz_first_column(p.alpha2, n2),
+        p.cz * O.toeplitz_first_column(p.alpha3, n3)))
+    ref = O.precond3_apply(p, V)
+    with RsfdePlan.setup3(shape, box, (p.alpha1, p.alpha2, p.alpha3), (p.kx, p.ky, p.kz),
+                          torch.as_tensor(p.mask), p.eta, p.dt, 2) as pl:
+        w = pl.matvec(_t(V)).cpu().numpy().reshape(p.shape)
+        z64 = pl.precond(_t(V)).cpu().numpy().reshape(p.shape)
+        z32 = pl.precond(_t(V), precision="fp32").cpu().numpy().reshape(p.shape)
+    assert np.abs(w - O.matvec3(p, V)).max() <= 1e-13 * nm * np.abs(V).max()
+    assert np.abs(z64 - ref).max() <= 1e-12 * np.abs(ref).max()
+    assert np.abs(z32 - ref).max() <= 2e-5 * np.abs(ref).max()
+
+
+# products: L = 2 next_pow2(n) per direction; chirp: L >= 2n - 1
+@pytest.mark.parametrize("n1,n2", [(1, 1), (2, 4), (5, 3), (64, 65), (128, 129), (129, 256),
+                                   (256, 257), (257, 513), (512, 128), (514, 300), (1024, 100),
+                                   (3, 1025), (1, 300), (300, 1)])
+def test_operators2_across_transform_lengths(n1, n2):
+    box = (0.0, 1.0, 0.0, 1.0)
+    mask = domain_mask(n1, n2, box, SHAPES["ellipse"](0.5, 0.5, 0.45, 0.3, 20.0))
+    p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+    V = np.random.default_rng(n1 + 5 * n2).standard_normal((n2, n1))
+    nm = 1.0 + p.d + 2 * np.abs(p.cx * O.toeplitz_first_column(p.alpha1, n1)).sum() \
+        + 2 * np.abs(p.cy * O.toeplitz_first_column(p.alpha2, n2)).sum()
+    with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2) as pl:
+        w = pl.matvec(_t(V)).cpu().numpy().reshape(n2, n1)
+        z64 = pl.precond(_t(V)).cpu().numpy().reshape(n2, n1)
+        z32 = pl.precond(_t(V), precision="fp32").cpu().numpy().reshape(n2, n1)
+    assert np.abs(w - O.matvec(p, V)).max() <= 1e-13 * nm * np.abs(V).max()
+    ref = O.precond_apply(p, V)
+    assert_precond(z64, ref, p, "fp64")
+    assert_precond(z32, ref, p, "fp32")
