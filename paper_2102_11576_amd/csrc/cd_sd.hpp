@@ -15,33 +15,29 @@
 // Only positions j <= n <= L/4 are read and written: of a group thread's 16
 // register positions (Sd::nat) those with m in 0..4 and 12..15.
 //
-// Passes and layouts (as the power-of-two passes, with natural positions in
-// place of slots):
-//   rows fwd: rows 2r, 2r + 1 share a transform; W1 strip-tiled (tile_index)
-//   columns:  columns 2c, 2c + 1 share the forward transform; then one transform
-//             per column of (w/E1, w/E2), stored as pairs (pair_index)
-//   rows inv: the pair (Y1, Y2) of a row is one transform; z = mask ? Y1 S : Y2 S
+// Passes, all intermediates strip-tiled (tile_index):
+//   rows fwd: rows 2r, 2r + 1 share a transform
+//   columns:  columns 2c, 2c + 1 share the forward transform, then one transform
+//             of w / E1 -> Y1 and one of w / E2 -> Y2
+//   rows inv: rows 2r, 2r + 1 of Y1 share one, of Y2 another; z from Y1 where
+//             mask = 1, from Y2 where mask = 0
+// The fields Y1 and Y2 never share a transform: Y1 is larger by up to dt/eta, and
+// its rounding would reach the penalty region's values (1.5e-12 of their largest
+// one on 2 x 4096 points, against 1e-15).
 //
-// Bound: at 1000 x 700 one round of blocks, so the serial time of a block's
-// transforms; at 2000^2 and beyond the FP64 unit and LDS.  Measured, plain
-// chirp form before: CDSD_NUMBERS
+// Bound: the FP64 unit and LDS of one block per CU (its region and, in the column
+// pass, the stash).  Whole preconditioner at 4000^2, plain form -> this one: FP64
+// 1859 -> 1122 us, FP32 1092 -> 738; cd_sym_length says where it is used and why.
 #pragma once
 
 #include "sd_kernels.hpp"
 
 namespace rsfde {
 
-// Threads and transforms per block: as the symmetric power-of-two passes; the
-// second and third transforms of a column pair run at once on two thread sets
-// up to L = kCdConcL (grids too small to fill the GPU).
-constexpr int kCdConcL = 4096;
 template <int L>
 struct CdSd {
   using S = Sd<L>;
-  static constexpr int ND = S::TS >= 16 ? 1 : 16 / S::TS;
-  static constexpr int THR_R = ND * S::TPD;
-  static constexpr bool CONC = L <= kCdConcL;
-  static constexpr int THR_C = (CONC ? 2 : 1) * S::TPD;
+  static constexpr int THR = S::TPD;  // one transform per block
   // register positions that reach j <= L/4
   static constexpr bool used(int m) { return m <= 4 || m >= 12; }
 };
@@ -59,14 +55,14 @@ __device__ __forceinline__ int cd_pos(int p, int m, int n, bool& neg) {
 template <typename T, int L, bool MAT>
 __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int tau, cpx<T> w1,
                                            const cpx<T>* __restrict__ khat,
-                                           const cpx<T>* __restrict__ twS, T* region, bool act) {
+                                           const cpx<T>* __restrict__ twS, T* region) {
   using S = Sd<L>;
   using Fs = typename S::Fs;
   constexpr int TWs = sd_tw<L, 1>();
   {
     Roots<T, Fs> rs;
     rs.load_fwd(tau, twS);
-    sd_forward<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region, act);
+    sd_forward<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
   }
   const cpx<T>* kr = khat + r * S::LS;
   static_for<16>([&](auto ee) {
@@ -76,8 +72,17 @@ __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int 
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region, act);
+    sd_inverse<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
   }
+}
+
+// A zero that the optimiser cannot see through, added to a table's pointer where
+// the table is read again later: the values are then loaded again instead of
+// being held in registers across a transform (k_cds_cols spilled 360 registers; an opaque pointer would lose its global address space).
+__device__ __forceinline__ int opaque_zero() {
+  int z = 0;
+  asm volatile("" : "+s"(z));
+  return z;
 }
 
 // v[m] *= c_j (premultiply, with the sign of the extension) for the used
@@ -130,21 +135,21 @@ __device__ __forceinline__ void cd_outputs(int p, int n, Fn&& f) {
 }
 
 template <typename T, int L>
-__global__ __launch_bounds__(CdSd<L>::THR_R) void k_cds_rows_fwd(
+__global__ __launch_bounds__(CdSd<L>::THR) void k_cds_rows_fwd(
     const double* __restrict__ v, const double* __restrict__ sig, T* __restrict__ Q,
     const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS, int n1, int n2) {
   using S = Sd<L>;
   using C = CdSd<L>;
-  __shared__ T lds[C::ND * S::LEN];
-  const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
-  const int ra = 2 * (blockIdx.x * C::ND + d), rb = ra + 1;
-  const bool va = ra < n2, vb = rb < n2;
+  __shared__ T lds[S::LEN];
+  const int tg = threadIdx.x;
+  const int ra = 2 * blockIdx.x, rb = ra + 1;
+  const bool vb = rb < n2;  // ra < n2 always
   const bool g = tg < S::NG;
   const int r = tg / S::TS, tau = tg % S::TS;
   const double sc = sig ? *sig : 1.0;
   const cpx<T> w1 = twL[g ? tg : 0];
-  const double* xa = v + (size_t)(va ? ra : 0) * n1;
+  const double* xa = v + (size_t)ra * n1;
   const double* xb = v + (size_t)(vb ? rb : 0) * n1;
   cpx<T> reg[16];
   if (g) {  // loads from clamped addresses, all in flight at once
@@ -155,17 +160,19 @@ __global__ __launch_bounds__(CdSd<L>::THR_R) void k_cds_rows_fwd(
         const int j = cd_pos<L>(tg, m, n1, neg);
         const int i = j ? j - 1 : 0;
         const double a = xa[i], b = xb[i];
-        reg[m].re = va ? (T)(sc * a) : (T)0;
+        reg[m].re = (T)(sc * a);
         reg[m].im = vb ? (T)(sc * b) : (T)0;
       }
     });
     cd_chirp_in<T, L>(reg, tg, n1, chn);
   }
-  cd_sd_conv<T, L, true>(reg, g, tg, r, tau, w1, khat, twS, lds + d * S::LEN, true);
-  if (!g || !va) return;
-  cd_chirp_out<T, L>(reg, tg, n1, chn);
+  cd_sd_conv<T, L, true>(reg, g, tg, r, tau, w1, khat, twS, lds);
+  if (!g) return;
+  int te = tg;  // the epilogue's positions are formed after the sweeps, not held across
+  asm volatile("" : "+v"(te));
+  cd_chirp_out<T, L>(reg, te, n1, chn + opaque_zero());
   const int hp = (n2 + 1) >> 1;
-  cd_outputs<L>(tg, n1, [&](auto mm, int j) {
+  cd_outputs<L>(te, n1, [&](auto mm, int j) {
     constexpr int m = decltype(mm)::value;
     const size_t i = tile_index(ra, j - 1, hp);  // row b of an odd n2: the zeros loaded for it
     Q[i] = reg[m].re;
@@ -174,29 +181,26 @@ __global__ __launch_bounds__(CdSd<L>::THR_R) void k_cds_rows_fwd(
 }
 
 template <typename T, int L>
-__global__ __launch_bounds__(CdSd<L>::THR_C) void k_cds_cols(
-    const T* __restrict__ Q, T* __restrict__ P, const double* __restrict__ lamx,
-    const double* __restrict__ lamy, const cpx<T>* __restrict__ chn,
-    const cpx<T>* __restrict__ khat, const cpx<T>* __restrict__ twL,
-    const cpx<T>* __restrict__ twS, int n1, int n2, double kx, double ky, double dpen) {
+__global__ __launch_bounds__(CdSd<L>::THR) void k_cds_cols(
+    const T* __restrict__ Q, T* __restrict__ Y1, T* __restrict__ Y2,
+    const double* __restrict__ lamx, const double* __restrict__ lamy,
+    const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
+    const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS, int n1, int n2, double kx,
+    double ky, double dpen) {
   using S = Sd<L>;
   using C = CdSd<L>;
   using V2 = typename Vec2<T>::type;
   constexpr int NU = 9;  // registers used: m = 0..4, 12..15
-  __shared__ T lds[(C::CONC ? 2 : 1) * S::LEN];
-  __shared__ T stash[NU * S::NG];  // the second column's coefficients
-  const int h = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
+  __shared__ T lds[S::LEN];
+  __shared__ T stash[2 * NU * S::NG];  // the pair's coefficients, for the second scaling
+  const int tg = threadIdx.x;
   const int c = xcd_remap(blockIdx.x, gridDim.x);
   const int ca = 2 * c, cb = ca + 1;
   const bool vb = cb < n1;  // ca < n1 always
   const int hp = (n2 + 1) >> 1;
-  const bool f0 = h == 0, g = tg < S::NG;
-  const int r = tg / S::TS, tau = tg % S::TS;
-  const cpx<T> w1 = twL[g ? tg : 0];
   const double lxa = 1.0 - kx * lamx[ca], lxb = 1.0 - kx * lamx[vb ? cb : ca];
-  T* region = lds + h * S::LEN;
   cpx<T> reg[16];
-  if (g && f0) {
+  if (tg < S::NG) {
     static_for<16>([&](auto mm) {
       constexpr int m = decltype(mm)::value;
       if constexpr (C::used(m)) {
@@ -210,62 +214,68 @@ __global__ __launch_bounds__(CdSd<L>::THR_C) void k_cds_cols(
     cd_chirp_in<T, L>(reg, tg, n2, chn);
   }
   // Three transforms by one copy of the code: the forward one of the column
-  // pair, then (w / E1, w / E2) of each column; the last two at once when CONC.
+  // pair, then w / E1 and w / E2.
 #pragma unroll 1
-  for (int q = 0; q < (C::CONC ? 2 : 3); ++q) {
-    cd_sd_conv<T, L, false>(reg, g && (f0 || q > 0), tg, r, tau, w1, khat, twS, region,
-                            f0 || q > 0);
-    if (g && (f0 || q > 0)) cd_chirp_out<T, L>(reg, tg, n2, chn);
-    const bool first = q == 0;
-    if (!first && g) {  // column 2c + h (CONC) or 2c + q - 1
-      const int cw = ca + (C::CONC ? h : q - 1);
-      if (cw < n1)
-        cd_outputs<L>(tg, n2, [&](auto mm, int j) {
-          constexpr int m = decltype(mm)::value;
-          *(V2*)(P + pair_index<T>(j - 1, cw, n2)) = V2{reg[m].re, reg[m].im};
-        });
-    }
-    if (first && g && f0) {
+  for (int q = 0; q < 3; ++q) {
+    // nothing per point is hoisted out of the loop: opaque thread index and tables
+    int th = tg;
+    asm volatile("" : "+v"(th));
+    const int zo = opaque_zero();
+    const bool g = th < S::NG;
+    cd_sd_conv<T, L, false>(reg, g, th, th / S::TS, th % S::TS, twL[g ? th : 0], khat + zo,
+                            twS + zo, lds);
+    if (!g) continue;  // (no barrier follows in this round)
+    cd_chirp_out<T, L>(reg, th, n2, chn + zo);
+    if (q == 0) {
       static_for<16>([&](auto mm) {
         constexpr int m = decltype(mm)::value;
-        if constexpr (C::used(m)) stash[(m <= 4 ? m : m - 7) * S::NG + tg] = reg[m].im;
-      });
-    }
-    if constexpr (C::CONC) __syncthreads();
-    if (g && q < (C::CONC ? 1 : 2)) {
-      const bool second = C::CONC ? !f0 : q == 1;
-      const double lx = second ? lxb : lxa;
-      static_for<16>([&](auto mm) {
-        constexpr int m = decltype(mm)::value;
+        constexpr int u = m <= 4 ? m : m - 7;
         if constexpr (C::used(m)) {
-          bool neg;
-          const int j = cd_pos<L>(tg, m, n2, neg);
-          const double e1 = lx - ky * lamy[j ? j - 1 : 0];
-          const T w = second ? stash[(m <= 4 ? m : m - 7) * S::NG + tg] : reg[m].re;
-          reg[m].re = w / (T)e1;
-          reg[m].im = w / (T)(e1 + dpen);
+          stash[(2 * u) * S::NG + th] = reg[m].re;
+          stash[(2 * u + 1) * S::NG + th] = reg[m].im;
         }
       });
-      cd_chirp_in<T, L>(reg, tg, n2, chn);
+    } else {
+      T* Y = q == 1 ? Y1 : Y2;
+      cd_outputs<L>(th, n2, [&](auto mm, int j) {  // (cb = n1: the padding column)
+        constexpr int m = decltype(mm)::value;
+        *(V2*)(Y + tile_index(j - 1, ca, hp)) = V2{reg[m].re, reg[m].im};
+      });
+    }
+    if (q < 2) {
+      const double pen = q == 0 ? 0.0 : dpen;
+      const double* ly = lamy + zo;
+      static_for<16>([&](auto mm) {
+        constexpr int m = decltype(mm)::value;
+        constexpr int u = m <= 4 ? m : m - 7;
+        if constexpr (C::used(m)) {
+          bool neg;
+          const int j = cd_pos<L>(th, m, n2, neg);
+          const double l = ky * ly[j ? j - 1 : 0];
+          reg[m].re = stash[(2 * u) * S::NG + th] / (T)(lxa + pen - l);
+          reg[m].im = stash[(2 * u + 1) * S::NG + th] / (T)(lxb + pen - l);
+        }
+      });
+      cd_chirp_in<T, L>(reg, th, n2, chn + zo);
     }
   }
 }
 
 template <typename T, int L>
-__global__ __launch_bounds__(CdSd<L>::THR_R) void k_cds_rows_inv(
-    const T* __restrict__ P, const uint8_t* __restrict__ mask, double* __restrict__ z,
-    const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
+__global__ __launch_bounds__(CdSd<L>::THR) void k_cds_rows_inv(
+    const T* __restrict__ Y1, const T* __restrict__ Y2, const uint8_t* __restrict__ mask,
+    double* __restrict__ z, const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS, int n1, int n2) {
   using S = Sd<L>;
   using C = CdSd<L>;
-  using V2 = typename Vec2<T>::type;
-  __shared__ T lds[C::ND * S::LEN];
-  const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
-  const int row = blockIdx.x * C::ND + d;
-  const bool vr = row < n2;
+  __shared__ T lds[S::LEN];
+  const int tg = threadIdx.x;
+  const int field = blockIdx.x & 1, ra = blockIdx.x & ~1, rb = ra + 1;
+  const bool vb = rb < n2;  // ra < n2 always
   const bool g = tg < S::NG;
   const int r = tg / S::TS, tau = tg % S::TS;
-  const int rr = vr ? row : 0;
+  const int hp = (n2 + 1) >> 1;
+  const T* Y = field ? Y2 : Y1;
   const cpx<T> w1 = twL[g ? tg : 0];
   cpx<T> reg[16];
   if (g) {
@@ -274,20 +284,25 @@ __global__ __launch_bounds__(CdSd<L>::THR_R) void k_cds_rows_inv(
       if constexpr (C::used(m)) {
         bool neg;
         const int j = cd_pos<L>(tg, m, n1, neg);
-        const V2 q = *(const V2*)(P + pair_index<T>(rr, j ? j - 1 : 0, n2));
-        reg[m].re = q.x;
-        reg[m].im = q.y;
+        const size_t i = tile_index(ra, j ? j - 1 : 0, hp);
+        const T a = Y[i], b = Y[i + 4];
+        reg[m].re = a;
+        reg[m].im = vb ? b : (T)0;
       }
     });
     cd_chirp_in<T, L>(reg, tg, n1, chn);
   }
-  cd_sd_conv<T, L, true>(reg, g, tg, r, tau, w1, khat, twS, lds + d * S::LEN, true);
-  if (!g || !vr) return;
-  cd_chirp_out<T, L>(reg, tg, n1, chn);
-  cd_outputs<L>(tg, n1, [&](auto mm, int j) {
+  cd_sd_conv<T, L, true>(reg, g, tg, r, tau, w1, khat, twS, lds);
+  if (!g) return;
+  int te = tg;  // the epilogue's positions are formed after the sweeps, not held across
+  asm volatile("" : "+v"(te));
+  cd_chirp_out<T, L>(reg, te, n1, chn + opaque_zero());
+  const bool want = field == 0;
+  cd_outputs<L>(te, n1, [&](auto mm, int j) {
     constexpr int m = decltype(mm)::value;
-    const size_t i = (size_t)row * n1 + (j - 1);
-    z[i] = mask[i] ? (double)reg[m].re : (double)reg[m].im;
+    const size_t i = (size_t)ra * n1 + (j - 1);
+    if ((mask[i] != 0) == want) z[i] = (double)reg[m].re;
+    if (vb && (mask[i + n1] != 0) == want) z[i + n1] = (double)reg[m].im;
   });
 }
 

@@ -287,6 +287,7 @@ int main() {
   worst = std::fmax(worst, run_sd_case<2048, double>(23));
   worst = std::fmax(worst, run_sd_case<4096, double>(24));
   worst = std::fmax(worst, run_sd_case<8192, double>(25));
+  worst = std::fmax(worst, run_sd_case<16384, double>(27));
   worst = std::fmax(worst, run_sd_case<4096, float>(26));
   if (worst >= 1e9) { printf("FAIL\n"); return 1; }
   printf("OK\n");

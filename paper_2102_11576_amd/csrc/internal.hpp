@@ -186,20 +186,34 @@ hipError_t launch_pc_rows_inv_mv(int L, const T* P1, const T* P2,
                                  const SdTabs& sd = SdTabs{});
 
 // Chirp (Bluestein) form of the same preconditioner for any n (n + 1 not a
-// power of two): T internals, tables chn (n entries) and khat (L entries, in
-// register-position order) per direction; W1 holds n1*n2 T values, Y1 and Y2
-// likewise.  L >= 2n - 1 is the convolution length of that direction.
+// power of two), T internals.  Per direction: chn (n chirp values), khat (the
+// convolution kernel's spectrum) and the twiddles of length L.  Plain form
+// (twS = NULL): L >= 2n - 1, khat in register-position order (L entries).
+// Symmetric form of long lines (cd_sd.hpp; tiled only): L >= 4n, twS the
+// twiddles of length L / 16, khat by block position (9 L / 16 entries).
+struct CdDir {
+  int L;
+  const void *chn, *khat, *tw, *twS;
+};
+// Length L of the symmetric form for lines of n points where it is used, 0 where
+// the plain form is: lines of more than 2048 points, whose plain transform is one
+// 8192-point FFT per block and reads single columns.  Whole preconditioner, plain
+// -> symmetric: 4000^2 FP64 1859 -> 1122 us, FP32 1092 -> 738; 3000 x 1000 FP64
+// 317 -> 247.  Below, the symmetric form has no lead: 2000^2 (L = 8192) 305 -> 313
+// us, 1000 x 700 (L = 4096) 82 -> 77 in FP64 and a larger FP32 error, 300 x 200 27
+// -> 32.
+constexpr int cd_sym_length(int n) { return n > 2048 ? 16384 : 0; }
+// W1, Y1, Y2: [n2][n1] arrays, or strip-tiled (tile_index).
 template <typename T>
-hipError_t launch_cd_rows_fwd(int L, const double* v, const double* sig, T* W1, const void* chn,
-                              const void* khat, const void* tw, int n1, int n2, hipStream_t s);
+hipError_t launch_cd_rows_fwd(const CdDir& d, const double* v, const double* sig, T* W1, int n1,
+                              int n2, bool tiled, hipStream_t s);
 template <typename T>
-hipError_t launch_cd_cols(int L, const T* W1, T* Y1, T* Y2, const double* lamx,
-                          const double* lamy, const void* chn, const void* khat, const void* tw,
-                          int n1, int n2, double kx, double ky, double dpen, hipStream_t s);
+hipError_t launch_cd_cols(const CdDir& d, const T* W1, T* Y1, T* Y2, const double* lamx,
+                          const double* lamy, int n1, int n2, double kx, double ky, double dpen,
+                          bool tiled, hipStream_t s);
 template <typename T>
-hipError_t launch_cd_rows_inv(int L, const T* Y1, const T* Y2, const uint8_t* mask, double* z,
-                              const void* chn, const void* khat, const void* tw, int n1, int n2,
-                              hipStream_t s);
+hipError_t launch_cd_rows_inv(const CdDir& d, const T* Y1, const T* Y2, const uint8_t* mask,
+                              double* z, int n1, int n2, bool tiled, hipStream_t s);
 // Three-dimensional plans: out = S in along the rows of `batch` slices of
 // [rows][ncol] T values (slice b at offset b * bstride, the columns c < ncol);
 // inB / outB (both or neither): a second array in the same launch.

@@ -19,11 +19,14 @@
 // odd-extension form, which the library uses whenever n + 1 is a power of two.
 //
 // Passes (T = double or float internals; v and z are FP64):
-//   rows:    W1 = rows of (sig * v) transformed along x           [n2][n1] T
+//   rows:    W1 = rows of (sig * v) transformed along x
 //   columns: W  = W1 transformed along y; Y1 = S_y(W / E1), Y2 = S_y(W / E2)
 //   rows:    z  = S_x of Y1 rows where mask = 1, of Y2 rows where mask = 0
+// Layouts: [rows][n1] arrays (TL = false); where one direction of a
+// two-dimensional grid takes the symmetric form (cd_sd.hpp), both use its layouts
+// (TL = true): W1, Y1 and Y2 strip-tiled.
 #pragma once
-#include "fft_common.hpp"
+#include "cd_sd.hpp"
 
 namespace rsfde {
 
@@ -70,7 +73,7 @@ __device__ __forceinline__ void chirp_dst(cpx<T>* reg, int tau, const cpx<T>* __
 }
 
 // Rows: W1[r] = S_x (sig * v[r]).
-template <typename T, int L>
+template <typename T, int L, bool TL>
 __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
     const double* __restrict__ v, const double* __restrict__ sig, T* __restrict__ out,
     const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
@@ -93,14 +96,14 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
-    if (vr && p < n1) out[(size_t)r * n1 + p] = reg[e].re;
+    if (vr && p < n1) out[TL ? tile_index(r, p, (n2 + 1) >> 1) : (size_t)r * n1 + p] = reg[e].re;
   });
 }
 
 // Columns: W = S_y W1 column, then Y1 = S_y(W / E1) and Y2 = S_y(W / E2).
 // Thread layout (tau, b) with b fastest: a wavefront touches BC adjacent
 // columns of each row it reads.
-template <typename T, int L, int BC>
+template <typename T, int L, int BC, bool TL>
 __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     const T* __restrict__ in, T* __restrict__ Y1, T* __restrict__ Y2,
     const double* __restrict__ lamx, const double* __restrict__ lamy,
@@ -113,43 +116,44 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
   const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < n1;
   T* my = lds + b;  // regions interleaved (stride BC)
+  const int hp = (n2 + 1) >> 1;
   cpx<T> reg[F::PP];
-  static_for<F::PP>([&](auto ee) {
-    constexpr int e = decltype(ee)::value;
-    const int p = F::pos(0, tau, e);
-    reg[e].re = (vc && p < n2) ? in[(size_t)p * n1 + c] : T(0);
-    reg[e].im = T(0);
-  });
-  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
-  const double ax = 1.0 - kx * (vc ? lamx[c] : 0.0);
   T w[F::PP];
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
-    const T e1 = (T)(ax - ky * (p < n2 ? lamy[p] : 0.0));
-    w[e] = p < n2 ? reg[e].re : T(0);
-    reg[e].re = w[e] / e1;
+    reg[e].re = (vc && p < n2) ? in[TL ? tile_index(p, c, hp) : (size_t)p * n1 + c] : T(0);
+    reg[e].im = T(0);
   });
-  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
-  static_for<F::PP>([&](auto ee) {
-    constexpr int e = decltype(ee)::value;
-    const int p = F::pos(0, tau, e);
-    if (vc && p < n2) Y1[(size_t)p * n1 + c] = reg[e].re;
-    const T e2 = (T)(ax + dpen - ky * (p < n2 ? lamy[p] : 0.0));
-    reg[e].re = w[e] / e2;
-  });
-  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, n2);
-  static_for<F::PP>([&](auto ee) {
-    constexpr int e = decltype(ee)::value;
-    const int p = F::pos(0, tau, e);
-    if (vc && p < n2) Y2[(size_t)p * n1 + c] = reg[e].re;
-  });
+  const double ax = 1.0 - kx * (vc ? lamx[c] : 0.0);
+  // The three transforms by one copy of the code (half the instructions to
+  // fetch; 256^2 13.9 -> 13.4 us): the forward one, then w / E1 and w / E2.
+#pragma unroll 1
+  for (int q = 0; q < 3; ++q) {
+    // opaque thread index and tables: nothing per point is hoisted out of the loop
+    int th = tau;
+    asm volatile("" : "+v"(th));
+    const int zo = opaque_zero();
+    const double* ly = lamy + zo;
+    chirp_dst<T, F, BC>(reg, th, chn + zo, khat + zo, tw + zo, my, n2);
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const int p = F::pos(0, th, e);
+      const bool in_range = p < n2;
+      if (q == 0) {
+        w[e] = in_range ? reg[e].re : T(0);
+      } else if (vc && in_range) {
+        (q == 1 ? Y1 : Y2)[TL ? tile_index(p, c, hp) : (size_t)p * n1 + c] = reg[e].re;
+      }
+      reg[e].re = w[e] / (T)(ax + (q == 0 ? 0.0 : dpen) - ky * (in_range ? ly[p] : 0.0));
+    });
+  }
 }
 
 // Rows: line u = 2r + k transforms row r of Y1 (k = 0) or Y2 (k = 1) along x
 // and writes z where the mask selects that branch; the two lines of a row
 // write disjoint points, so no combine step is needed.
-template <typename T, int L>
+template <typename T, int L, bool TL>
 __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
     const T* __restrict__ Y1, const T* __restrict__ Y2, const uint8_t* __restrict__ mask,
     double* __restrict__ z, const cpx<T>* __restrict__ chn, const cpx<T>* __restrict__ khat,
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
-    reg[e].re = (vr && p < n1) ? src[(size_t)r * n1 + p] : T(0);
+    reg[e].re = (vr && p < n1) ? src[TL ? tile_index(r, p, (n2 + 1) >> 1) : (size_t)r * n1 + p] : T(0);
     reg[e].im = T(0);
   });
   chirp_dst<T, F>(reg, tau, chn, khat, tw, lds + b * lds_len(L), n1);
@@ -218,17 +222,41 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_dst_cols(
 #define RSFDE_CD_CASES(X) \
   X(2) X(4) X(8) X(16) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096) X(8192)
 
+// The symmetric form's lengths (cd_sd.hpp).
+#define RSFDE_CDS_CASES(X) X(16384)
+
 template <typename T>
-hipError_t launch_cd_rows_fwd(int L, const double* v, const double* sig, T* out, const void* chn,
-                              const void* khat, const void* tw, int n1, int n2, hipStream_t s) {
-  switch (L) {
-#define X(LL)                                                                             \
-  case LL: {                                                                              \
-    using C = CdCfg<LL>;                                                                  \
-    const int blocks = (n2 + C::BR - 1) / C::BR;                                          \
-    hipLaunchKernelGGL((k_cd_rows_fwd<T, LL>), dim3(blocks), dim3(C::THR_R), 0, s, v, sig, \
-                       out, (const cpx<T>*)chn, (const cpx<T>*)khat, (const cpx<T>*)tw, n1, n2); \
-    return hipGetLastError();                                                             \
+hipError_t launch_cd_rows_fwd(const CdDir& d, const double* v, const double* sig, T* out, int n1,
+                              int n2, bool tiled, hipStream_t s) {
+  const cpx<T>*chn = (const cpx<T>*)d.chn, *khat = (const cpx<T>*)d.khat, *tw = (const cpx<T>*)d.tw;
+  if (d.twS) {
+    if (!tiled || 4 * n1 > d.L) return hipErrorInvalidValue;
+    switch (d.L) {
+#define X(LL)                                                                                   \
+  case LL: {                                                                                    \
+    using C = CdSd<LL>;                                                                         \
+    hipLaunchKernelGGL((k_cds_rows_fwd<T, LL>), dim3((n2 + 1) / 2), dim3(C::THR), 0, s, v,       \
+                       sig, out, chn, khat, tw, (const cpx<T>*)d.twS, n1, n2);         \
+    return hipGetLastError();                                                                   \
+  }
+      RSFDE_CDS_CASES(X)
+#undef X
+      default:
+        return hipErrorInvalidValue;
+    }
+  }
+  switch (d.L) {
+#define X(LL)                                                                                 \
+  case LL: {                                                                                  \
+    using C = CdCfg<LL>;                                                                      \
+    const dim3 g((n2 + C::BR - 1) / C::BR), t(C::THR_R);                                      \
+    if (tiled)                                                                                \
+      hipLaunchKernelGGL((k_cd_rows_fwd<T, LL, true>), g, t, 0, s, v, sig, out, chn, khat, tw, n1, \
+                         n2);                                                                 \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_cd_rows_fwd<T, LL, false>), g, t, 0, s, v, sig, out, chn, khat, tw, n1, \
+                         n2);                                                                 \
+    return hipGetLastError();                                                                 \
   }
     RSFDE_CD_CASES(X)
 #undef X
@@ -238,21 +266,40 @@ hipError_t launch_cd_rows_fwd(int L, const double* v, const double* sig, T* out,
 }
 
 template <typename T>
-hipError_t launch_cd_cols(int L, const T* in, T* Y1, T* Y2, const double* lamx,
-                          const double* lamy, const void* chn, const void* khat, const void* tw,
-                          int n1, int n2, double kx, double ky, double dpen, hipStream_t s) {
-  switch (L) {
+hipError_t launch_cd_cols(const CdDir& d, const T* in, T* Y1, T* Y2, const double* lamx,
+                          const double* lamy, int n1, int n2, double kx, double ky, double dpen,
+                          bool tiled, hipStream_t s) {
+  const cpx<T>*chn = (const cpx<T>*)d.chn, *khat = (const cpx<T>*)d.khat, *tw = (const cpx<T>*)d.tw;
+  if (d.twS) {
+    if (!tiled || 4 * n2 > d.L) return hipErrorInvalidValue;
+    switch (d.L) {
+#define X(LL)                                                                                    \
+  case LL: {                                                                                     \
+    using C = CdSd<LL>;                                                                          \
+    hipLaunchKernelGGL((k_cds_cols<T, LL>), dim3((n1 + 1) / 2), dim3(C::THR), 0, s, in, Y1, Y2, \
+                       lamx, lamy, chn, khat, tw, (const cpx<T>*)d.twS, n1, n2, kx, ky, dpen);         \
+    return hipGetLastError();                                                                    \
+  }
+      RSFDE_CDS_CASES(X)
+#undef X
+      default:
+        return hipErrorInvalidValue;
+    }
+  }
+  switch (d.L) {
 #define X(LL)                                                                                  \
   case LL: {                                                                                   \
     using C = CdCfg<LL>;                                                                       \
-    auto go = [&](auto bc) {                                                                   \
+    auto go = [&](auto bc, auto tl) {                                                          \
       constexpr int BC = decltype(bc)::value;                                                  \
-      hipLaunchKernelGGL((k_cd_cols<T, LL, BC>), dim3((n1 + BC - 1) / BC), dim3(BC * C::TPF), 0, s, \
-                         in, Y1, Y2, lamx, lamy, (const cpx<T>*)chn, (const cpx<T>*)khat,      \
-                         (const cpx<T>*)tw, n1, n2, kx, ky, dpen);                             \
+      constexpr bool TL = decltype(tl)::value;                                                 \
+      hipLaunchKernelGGL((k_cd_cols<T, LL, BC, TL>), dim3((n1 + BC - 1) / BC), dim3(BC * C::TPF), 0, \
+                         s, in, Y1, Y2, lamx, lamy, chn, khat, tw, n1, n2, kx, ky, dpen);      \
     };                                                                                         \
-    if (C::small_cols(n1, 1)) go(std::integral_constant<int, C::BCS>{});                       \
-    else go(std::integral_constant<int, C::BCL>{});                                            \
+    using S = std::integral_constant<int, C::BCS>;                                             \
+    using B = std::integral_constant<int, C::BCL>;                                             \
+    if (C::small_cols(n1, 1)) tiled ? go(S{}, std::true_type{}) : go(S{}, std::false_type{});  \
+    else tiled ? go(B{}, std::true_type{}) : go(B{}, std::false_type{});                       \
     return hipGetLastError();                                                                  \
   }
     RSFDE_CD_CASES(X)
@@ -291,17 +338,37 @@ hipError_t launch_cd_dst_cols(int L, const T* inA, T* outA, const T* inB, T* out
 }
 
 template <typename T>
-hipError_t launch_cd_rows_inv(int L, const T* Y1, const T* Y2, const uint8_t* mask, double* z,
-                              const void* chn, const void* khat, const void* tw, int n1, int n2,
-                              hipStream_t s) {
-  switch (L) {
-#define X(LL)                                                                                 \
-  case LL: {                                                                                  \
-    using C = CdCfg<LL>;                                                                      \
-    const int blocks = (2 * n2 + C::BR - 1) / C::BR;                                          \
-    hipLaunchKernelGGL((k_cd_rows_inv<T, LL>), dim3(blocks), dim3(C::THR_R), 0, s, Y1, Y2, mask, \
-                       z, (const cpx<T>*)chn, (const cpx<T>*)khat, (const cpx<T>*)tw, n1, n2);  \
-    return hipGetLastError();                                                                 \
+hipError_t launch_cd_rows_inv(const CdDir& d, const T* Y1, const T* Y2, const uint8_t* mask,
+                              double* z, int n1, int n2, bool tiled, hipStream_t s) {
+  const cpx<T>*chn = (const cpx<T>*)d.chn, *khat = (const cpx<T>*)d.khat, *tw = (const cpx<T>*)d.tw;
+  if (d.twS) {
+    if (!tiled || 4 * n1 > d.L) return hipErrorInvalidValue;
+    switch (d.L) {
+#define X(LL)                                                                                  \
+  case LL: {                                                                                   \
+    using C = CdSd<LL>;                                                                        \
+    hipLaunchKernelGGL((k_cds_rows_inv<T, LL>), dim3((n2 + 1) / 2 * 2), dim3(C::THR), 0, s, Y1, Y2, \
+                       mask, z, chn, khat, tw, (const cpx<T>*)d.twS, n1, n2);           \
+    return hipGetLastError();                                                                  \
+  }
+      RSFDE_CDS_CASES(X)
+#undef X
+      default:
+        return hipErrorInvalidValue;
+    }
+  }
+  switch (d.L) {
+#define X(LL)                                                                                     \
+  case LL: {                                                                                      \
+    using C = CdCfg<LL>;                                                                          \
+    const dim3 g((2 * n2 + C::BR - 1) / C::BR), t(C::THR_R);                                      \
+    if (tiled)                                                                                    \
+      hipLaunchKernelGGL((k_cd_rows_inv<T, LL, true>), g, t, 0, s, Y1, Y2, mask, z, chn, khat, tw, n1, \
+                         n2);                                                                     \
+    else                                                                                          \
+      hipLaunchKernelGGL((k_cd_rows_inv<T, LL, false>), g, t, 0, s, Y1, Y2, mask, z, chn, khat, tw, \
+                         n1, n2);                                                                 \
+    return hipGetLastError();                                                                     \
   }
     RSFDE_CD_CASES(X)
 #undef X

@@ -27,27 +27,9 @@
 // natural layout gives it 32-byte pieces of rows 8 (n+1) bytes apart; pass A
 // writes 64-byte pieces of Q and pass C reads whole 128-byte lines of pairs.
 #pragma once
-#include "fft_common.hpp"
+#include "sd_kernels.hpp"
 
 namespace rsfde {
-
-// Row-segment layout of the interleaved (P1, P2) pairs: segments of
-// W = 64 / sizeof(T) slots per row (one 128-byte line of pairs), the
-// segments of one W-slot strip stored row after row, strip after strip.
-// Within a segment the even slots fill the first half of the line and the odd
-// slots the second: pass B finishes the even slot of each column pair in its
-// first inverse sweep and the odd one in its second, so the blocks of one
-// strip complete a whole 64-byte half-line per sweep (a line written in two
-// halves at two times then leaves the L2 as two full halves).  Returns the
-// element of P1 (P2 follows it); the array holds 2 W ceil(slots / W) rows values.
-template <typename T>
-__device__ __forceinline__ size_t pair_index(int r, int c, int rows) {
-  constexpr int W = 64 / (int)sizeof(T);
-  const int q = c % W;
-  const int pos = (q & 1) * (W / 2) + (q >> 1);
-  return (((size_t)(c / W) * rows + r) * W + pos) * 2;
-}
-
 
 template <int L>
 struct PcCfg {
@@ -548,11 +530,6 @@ void k_pc_rows_inv_mv(const T* __restrict__ P1, const T* __restrict__ P2,
   });
 }
 
-}  // namespace rsfde
-
-#include "sd_kernels.hpp"
-
-namespace rsfde {
 
 // ------------------------------- launchers --------------------------------
 template <typename T, int L, bool TL>

@@ -69,8 +69,6 @@ struct Plan {
   double alpha3 = 0, kz = 0;
   int Lcz = 0, Ldz = 0;
   int Lgz = 0;               // chirp form (some n + 1 not a power of two): z length
-  void* chz[2] = {nullptr, nullptr};
-  void* khz[2] = {nullptr, nullptr};
   double* symz = nullptr;
   double* lamz64 = nullptr;  // z eigenvalues (unit kz), register-position order of Ldz
   float* lamz32 = nullptr;
@@ -105,10 +103,7 @@ struct Plan {
   // chirp-form preconditioner (n + 1 not a power of two)
   double* lamx_n = nullptr;  // tau eigenvalues, natural order, unit k
   double* lamy_n = nullptr;
-  void* chx[2] = {nullptr, nullptr};  // [0] FP64, [1] FP32 tables
-  void* khx[2] = {nullptr, nullptr};
-  void* chy[2] = {nullptr, nullptr};
-  void* khy[2] = {nullptr, nullptr};
+  CdDir cdx[2] = {}, cdy[2] = {}, cdz[2] = {};  // chirp tables per axis: [0] FP64, [1] FP32
   std::map<int, void*> tw64, tw32;
   // BF16 / MFMA preconditioner
   int n1p = 0, n2p = 0;
@@ -261,20 +256,22 @@ void fft_host(std::vector<std::complex<double>>& a) {
 //   khat[p] = sqrt(2/M) / L * K_f at f = freq(p), K = DFT_L of the even kernel
 //             k[m mod L] = exp(-i pi m^2 / (2M)), |m| < n.
 // Phases are reduced exactly: m^2 mod 4M in integers.
-void chirp_tables(int n, int L, std::vector<double>& chn, std::vector<double>& khat) {
-  const long long M4 = 4LL * (n + 1);
-  auto ang = [&](long long j) {
-    return kPi * (double)((j * j) % M4) / (2.0 * (double)(n + 1));
-  };
-  chn.assign(2 * (size_t)n, 0.0);
+double chirp_angle(int n, long long j) {
+  return kPi * (double)((j * j) % (4LL * (n + 1))) / (2.0 * (double)(n + 1));
+}
+std::vector<double> chirp_values(int n) {
+  std::vector<double> chn(2 * (size_t)n);
   for (int p = 0; p < n; ++p) {
-    const double a = ang(p + 1);
+    const double a = chirp_angle(n, p + 1);
     chn[2 * (size_t)p] = std::cos(a);
     chn[2 * (size_t)p + 1] = std::sin(a);
   }
+  return chn;
+}
+std::vector<double> chirp_khat(int n, int L) {
   std::vector<std::complex<double>> k(L, {0.0, 0.0});
   for (int m = 0; m < n; ++m) {
-    const double a = ang(m);
+    const double a = chirp_angle(n, m);
     const std::complex<double> c(std::cos(a), -std::sin(a));
     k[m] = c;
     if (m) k[L - m] = c;
@@ -282,11 +279,41 @@ void chirp_tables(int n, int L, std::vector<double>& chn, std::vector<double>& k
   fft_host(k);
   const double sc = std::sqrt(2.0 / (n + 1)) / (double)L;
   const int P = fft_pts(L);
-  khat.assign(2 * (size_t)L, 0.0);
+  std::vector<double> khat(2 * (size_t)L);
   for (int p = 0; p < L; ++p) {
     const std::complex<double> v = k[fft_freq(L, P, p)] * sc;
     khat[2 * (size_t)p] = v.real();
     khat[2 * (size_t)p + 1] = v.imag();
+  }
+  return khat;
+}
+
+// khat of the chirp's symmetric form (cd_sd.hpp), by block position P of Sd<L>:
+// -i/2 sqrt(2/M) / L * K_f at f = freq(P), K = DFT_L of the even kernel
+// k[m mod L] = exp(-i pi m^2 / (2M)), |m| <= 2n (2n <= L/2).
+template <int L>
+std::vector<double> chirp_sym_khat_L(int n) {
+  std::vector<std::complex<double>> k(L, {0.0, 0.0});
+  for (long long m = 0; m <= 2LL * n; ++m) {
+    const double a = chirp_angle(n, m);
+    const std::complex<double> c(std::cos(a), -std::sin(a));
+    k[m] = c;
+    if (m) k[L - m] = c;
+  }
+  fft_host(k);
+  const std::complex<double> sc(0.0, -0.5 * std::sqrt(2.0 / (n + 1)) / (double)L);
+  std::vector<double> out(2 * (size_t)Sd<L>::NPOS);
+  for (int P = 0; P < Sd<L>::NPOS; ++P) {
+    const std::complex<double> v = k[Sd<L>::freq(P)] * sc;
+    out[2 * (size_t)P] = v.real();
+    out[2 * (size_t)P + 1] = v.imag();
+  }
+  return out;
+}
+std::vector<double> chirp_sym_khat(int n, int L) {
+  switch (L) {
+    case 16384: return chirp_sym_khat_L<16384>(n);
+    default: return {};
   }
 }
 
@@ -341,6 +368,41 @@ hipError_t ensure_twiddles(Plan* P, int L, hipStream_t s) {
   if (e != hipSuccess) return e;
   P->tw64[L] = d;
   P->tw32[L] = f;
+  return hipSuccess;
+}
+
+// The chirp tables of an axis of n points in both precisions: the symmetric
+// form where it is allowed (two-dimensional plans) and used (cd_sym_length),
+// the plain form of length L elsewhere.
+hipError_t chirp_dir(Plan* P, int n, int L, bool sym, CdDir (&d)[2], hipStream_t s) {
+  const std::vector<double> ch = chirp_values(n);
+  const std::vector<float> chf(ch.begin(), ch.end());
+  double* c64 = nullptr;
+  float* c32 = nullptr;
+  hipError_t e;
+  if ((e = upload(P, &c64, ch, s)) != hipSuccess || (e = upload(P, &c32, chf, s)) != hipSuccess)
+    return e;
+  for (int t = 0; t < 2; ++t) {
+    const int Ls = sym ? cd_sym_length(n) : 0;
+    const int Lt = Ls ? Ls : L;
+    const std::vector<double> kh = Ls ? chirp_sym_khat(n, Ls) : chirp_khat(n, L);
+    if (kh.empty()) return hipErrorInvalidValue;
+    if ((e = ensure_twiddles(P, Lt, s)) != hipSuccess) return e;
+    if (Ls && (e = ensure_twiddles(P, Ls / 16, s)) != hipSuccess) return e;
+    auto& tw = t == 0 ? P->tw64 : P->tw32;
+    void* k = nullptr;
+    if (t == 0) {
+      double* k64 = nullptr;
+      if ((e = upload(P, &k64, kh, s)) != hipSuccess) return e;
+      k = k64;
+    } else {
+      float* k32 = nullptr;
+      if ((e = upload(P, &k32, std::vector<float>(kh.begin(), kh.end()), s)) != hipSuccess) return e;
+      k = k32;
+    }
+    d[t] = CdDir{Lt, t == 0 ? (const void*)c64 : (const void*)c32, k, tw[Lt],
+                 Ls ? tw[Ls / 16] : nullptr};
+  }
   return hipSuccess;
 }
 
@@ -400,24 +462,25 @@ int matvec_impl(Plan* P, const double* x, double* y, hipStream_t s, const double
 
 // Chirp-form P_hat^{-1} (any n): three passes with T internals.
 template <typename T>
-int precond_chirp(Plan* P, const double* r, const double* sig, double* z, int t,
-                  std::map<int, void*>& tw, hipStream_t s) {
+int precond_chirp(Plan* P, const double* r, const double* sig, double* z, hipStream_t s) {
+  constexpr int t = sizeof(T) == 8 ? 0 : 1;
+  // the symmetric form's layouts where either direction takes it (the plain form
+  // alone is faster on plain arrays: 1024^2 in FP32 59 us against 66)
+  const bool tiled = P->cdx[t].twS || P->cdy[t].twS;
   const double N = (double)P->N, ts = (double)sizeof(T);
   T *W = (T*)P->Q, *Y1 = (T*)P->P1, *Y2 = (T*)P->P2;
   {
     ProfScope ps(P, s, kCatCdRows, 8.0 * N + ts * N);
-    CK(launch_cd_rows_fwd<T>(P->Lgx, r, sig, W, P->chx[t], P->khx[t], tw[P->Lgx], P->n1, P->n2,
-                             s));
+    CK(launch_cd_rows_fwd<T>(P->cdx[t], r, sig, W, P->n1, P->n2, tiled, s));
   }
   {
     ProfScope ps(P, s, kCatCdCols, 3.0 * ts * N);
-    CK(launch_cd_cols<T>(P->Lgy, W, Y1, Y2, P->lamx_n, P->lamy_n, P->chy[t], P->khy[t],
-                         tw[P->Lgy], P->n1, P->n2, P->kx, P->ky, P->dpen, s));
+    CK(launch_cd_cols<T>(P->cdy[t], W, Y1, Y2, P->lamx_n, P->lamy_n, P->n1, P->n2, P->kx, P->ky,
+                         P->dpen, tiled, s));
   }
   {
     ProfScope ps(P, s, kCatCdRowsInv, 2.0 * ts * N + 9.0 * N);
-    CK(launch_cd_rows_inv<T>(P->Lgx, Y1, Y2, P->mask, z, P->chx[t], P->khx[t], tw[P->Lgx], P->n1,
-                             P->n2, s));
+    CK(launch_cd_rows_inv<T>(P->cdx[t], Y1, Y2, P->mask, z, P->n1, P->n2, tiled, s));
   }
   return RSFDE_OK;
 }
@@ -431,34 +494,34 @@ int precond_chirp(Plan* P, const double* r, const double* sig, double* z, int t,
 //   B3: W1 = S_y Y1, W2 = S_y Y2                         (per z slice)
 //   C:  z  = S_x W1 where mask = 1, S_x W2 where mask = 0  (all rows)
 template <typename T>
-int precond3_chirp(Plan* P, const double* r, const double* sig, double* z, int t,
-                   std::map<int, void*>& tw, hipStream_t s) {
+int precond3_chirp(Plan* P, const double* r, const double* sig, double* z, hipStream_t s) {
+  constexpr int t = sizeof(T) == 8 ? 0 : 1;
+  const CdDir& dy = P->cdy[t];
   const int n1 = P->n1, n2 = P->n2, n3 = P->n3, rows = n2 * n3, plane = n1 * n2;
   const double N = (double)P->N, ts = (double)sizeof(T);
   T *W1 = (T*)P->Q, *W2 = (T*)P->R3, *Y1 = (T*)P->P1, *Y2 = (T*)P->P2;
   {
     ProfScope ps(P, s, kCatCdRows, 8.0 * N + ts * N);
-    CK(launch_cd_rows_fwd<T>(P->Lgx, r, sig, W1, P->chx[t], P->khx[t], tw[P->Lgx], n1, rows, s));
+    CK(launch_cd_rows_fwd<T>(P->cdx[t], r, sig, W1, n1, rows, false, s));
   }
   {
     ProfScope ps(P, s, kCatCdCols, 2.0 * ts * N);
-    CK(launch_cd_dst_cols<T>(P->Lgy, W1, W2, nullptr, nullptr, P->chy[t], P->khy[t], tw[P->Lgy], n1,
-                             n2, n3, (size_t)plane, s));
-  }
-  {
-    ProfScope ps(P, s, kCatCdCols, 3.0 * ts * N);
-    CK(launch_cd_cols<T>(P->Lgz, W2, Y1, Y2, P->lamc64, P->lamz64, P->chz[t], P->khz[t],
-                         tw[P->Lgz], plane, n3, 1.0, P->kz, P->dpen, s));
-  }
-  {
-    ProfScope ps(P, s, kCatCdCols, 4.0 * ts * N);
-    CK(launch_cd_dst_cols<T>(P->Lgy, Y1, W1, Y2, W2, P->chy[t], P->khy[t], tw[P->Lgy], n1, n2, n3,
+    CK(launch_cd_dst_cols<T>(dy.L, W1, W2, nullptr, nullptr, dy.chn, dy.khat, dy.tw, n1, n2, n3,
                              (size_t)plane, s));
   }
   {
+    ProfScope ps(P, s, kCatCdCols, 3.0 * ts * N);
+    CK(launch_cd_cols<T>(P->cdz[t], W2, Y1, Y2, P->lamc64, P->lamz64, plane, n3, 1.0, P->kz, P->dpen,
+                         false, s));
+  }
+  {
+    ProfScope ps(P, s, kCatCdCols, 4.0 * ts * N);
+    CK(launch_cd_dst_cols<T>(dy.L, Y1, W1, Y2, W2, dy.chn, dy.khat, dy.tw, n1, n2, n3, (size_t)plane,
+                             s));
+  }
+  {
     ProfScope ps(P, s, kCatCdRowsInv, 2.0 * ts * N + 9.0 * N);
-    CK(launch_cd_rows_inv<T>(P->Lgx, W1, W2, P->mask, z, P->chx[t], P->khx[t], tw[P->Lgx], n1,
-                             rows, s));
+    CK(launch_cd_rows_inv<T>(P->cdx[t], W1, W2, P->mask, z, n1, rows, false, s));
   }
   return RSFDE_OK;
 }
@@ -477,7 +540,7 @@ int precond3(Plan* P, const double* r, const double* sig, double* z, std::map<in
              const T* lamc, const T* lamz, hipStream_t s, double* w, const double* sub,
              double theta) {
   if (P->Lgx) {  // chirp form, then the product unfused
-    const int rc = precond3_chirp<T>(P, r, sig, z, sizeof(T) == 8 ? 0 : 1, tw, s);
+    const int rc = precond3_chirp<T>(P, r, sig, z, s);
     if (rc != RSFDE_OK || !w) return rc;
     return matvec_impl(P, z, w, s, sub, theta);
   }
@@ -554,8 +617,8 @@ int precond_impl(Plan* P, const double* r, const double* sig, double* z, int pre
     return RSFDE_OK;
   }
   if (P->Lgx) {
-    if (precision == RSFDE_FP64) return precond_chirp<double>(P, r, sig, z, 0, P->tw64, s);
-    if (precision == RSFDE_FP32) return precond_chirp<float>(P, r, sig, z, 1, P->tw32, s);
+    if (precision == RSFDE_FP64) return precond_chirp<double>(P, r, sig, z, s);
+    if (precision == RSFDE_FP32) return precond_chirp<float>(P, r, sig, z, s);
     return RSFDE_EUNSUPPORTED;
   }
   const double Kfac = 4.0 / ((double)(P->n1 + 1) * (double)(P->n2 + 1));
@@ -1491,21 +1554,9 @@ int rsfde_setup(rsfde_plan* out, const rsfde_grid* grid, double alpha1, double a
     const std::vector<double> lx = tau_eigs(tx), ly = tau_eigs(ty);
     if (upload(P, &P->lamx_n, lx, s) != hipSuccess || upload(P, &P->lamy_n, ly, s) != hipSuccess)
       return failx(__LINE__, RSFDE_ENOMEM);
-    struct Dir { int n, L; void **ch, **kh; };
-    for (Dir d : {Dir{n1, P->Lgx, P->chx, P->khx}, Dir{n2, P->Lgy, P->chy, P->khy}}) {
-      std::vector<double> ch, kh;
-      chirp_tables(d.n, d.L, ch, kh);
-      const std::vector<float> chf(ch.begin(), ch.end()), khf(kh.begin(), kh.end());
-      double *a = nullptr, *b = nullptr;
-      float *c = nullptr, *e = nullptr;
-      if (upload(P, &a, ch, s) != hipSuccess || upload(P, &b, kh, s) != hipSuccess ||
-          upload(P, &c, chf, s) != hipSuccess || upload(P, &e, khf, s) != hipSuccess)
-        return failx(__LINE__, RSFDE_ENOMEM);
-      d.ch[0] = a;
-      d.kh[0] = b;
-      d.ch[1] = c;
-      d.kh[1] = e;
-    }
+    if (chirp_dir(P, n1, P->Lgx, true, P->cdx, s) != hipSuccess ||
+        chirp_dir(P, n2, P->Lgy, true, P->cdy, s) != hipSuccess)
+      return failx(__LINE__, RSFDE_ENOMEM);
   }
   // BF16 / MFMA preconditioner: padded sine matrices, natural-order eigenvalues
   {
@@ -1626,22 +1677,10 @@ int rsfde_setup3(rsfde_plan* out, const rsfde_grid3* grid, double alpha1, double
   for (int L : {P->Lcx, P->Lcy, P->Lcz, P->Ldx, P->Ldy, P->Ldz, P->Lgx, P->Lgy, P->Lgz})
     if (ensure_twiddles(P, L, s) != hipSuccess) return fail(RSFDE_ENOMEM);
   if (!pow2) {  // chirp tables per axis (FP64 and FP32)
-    struct Dir { int n, L; void **ch, **kh; };
-    for (Dir d : {Dir{n[0], P->Lgx, P->chx, P->khx}, Dir{n[1], P->Lgy, P->chy, P->khy},
-                  Dir{n[2], P->Lgz, P->chz, P->khz}}) {
-      std::vector<double> ch, kh;
-      chirp_tables(d.n, d.L, ch, kh);
-      const std::vector<float> chf(ch.begin(), ch.end()), khf(kh.begin(), kh.end());
-      double *a = nullptr, *b = nullptr;
-      float *c = nullptr, *e = nullptr;
-      if (upload(P, &a, ch, s) != hipSuccess || upload(P, &b, kh, s) != hipSuccess ||
-          upload(P, &c, chf, s) != hipSuccess || upload(P, &e, khf, s) != hipSuccess)
-        return fail(RSFDE_ENOMEM);
-      d.ch[0] = a;
-      d.kh[0] = b;
-      d.ch[1] = c;
-      d.kh[1] = e;
-    }
+    if (chirp_dir(P, n[0], P->Lgx, false, P->cdx, s) != hipSuccess ||
+        chirp_dir(P, n[1], P->Lgy, false, P->cdy, s) != hipSuccess ||
+        chirp_dir(P, n[2], P->Lgz, false, P->cdz, s) != hipSuccess)
+      return fail(RSFDE_ENOMEM);
   }
   // Section 4.1's eigenvalues: x in slot order folded with y into one value per
   // column of the [n3][(n1+1) n2] view (k included), z in position order (unit kz).

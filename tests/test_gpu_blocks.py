@@ -76,3 +76,22 @@ def test_operators2_across_transform_lengths(n1, n2):
     ref = O.precond_apply(p, V)
     assert_precond(z64, ref, p, "fp64")
     assert_precond(z32, ref, p, "fp32")
+
+
+# Lines around the changes of the chirp transforms' lengths and form (n <= 2^k <
+# n + 1; the symmetric form from 2049 points on, 4n = L at 4096), alone and mixed
+# with the other forms, odd and even counts
+@pytest.mark.parametrize("n1,n2", [(512, 513), (513, 512), (514, 33), (33, 515), (1023, 1000),
+                                   (1024, 601), (1025, 701), (2048, 6), (2049, 5), (7, 2050),
+                                   (2051, 514), (4096, 3), (2, 4096), (1, 600), (600, 1)])
+def test_chirp_forms(n1, n2):
+    box = (0.0, 1.0, 0.0, 1.0)
+    mask = domain_mask(n1, n2, box, SHAPES["ellipse"](0.5, 0.5, 0.45, 0.3, 20.0))
+    p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+    V = np.random.default_rng(n1 + 5 * n2).standard_normal((n2, n1))
+    with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2) as pl:
+        z64 = pl.precond(_t(V)).cpu().numpy().reshape(n2, n1)
+        z32 = pl.precond(_t(V), precision="fp32").cpu().numpy().reshape(n2, n1)
+    ref = O.precond_apply_fft(p, V)
+    assert_precond(z64, ref, p, "fp64")
+    assert_precond(z32, ref, p, "fp32")
