@@ -212,6 +212,19 @@ struct Vec2<float> {
   using type = float2;
 };
 
+// Two consecutive elements of a caller's array, at any element's address: one
+// load or store of twice the width, aligned like one element.
+template <typename T>
+struct PairU;
+template <>
+struct PairU<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <>
+struct PairU<float> {
+  typedef float type __attribute__((ext_vector_type(2), aligned(4)));
+};
+
 // Workgroups are dispatched round-robin over the 8 XCDs.  Remap the block
 // index so that consecutive logical tiles (adjacent column strips) run on the
 // same XCD and share its L2 lines.

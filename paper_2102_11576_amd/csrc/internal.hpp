@@ -153,15 +153,13 @@ hipError_t launch_pc_cols(int Ly, const T* Q, T* P1, T* P2, const T* lamx_slot,
                           hipStream_t s, const Members& mb = Members::one(),
                           const double* mk = nullptr, const SdTabs& sd = SdTabs{});
 // Raw sine transform (DST-I without normalisation) along the columns of
-// `batch` slices of [rows][ld] values (slice b at offset b * bstride):
-//   outA[k-1][ca] = sum_{p=1..rows} inA[p-1][ca] sin(pi k p / (rows + 1)), k = 1..rows,
-// and likewise inB column cb -> outB, with ca = c * cstride, cb = ca + coff for
-// c = 0..ncol-1 (cstride 2, coff 1: adjacent column pairs of one array;
-// cstride 1, coff 0: the same column of two arrays).  L = 2 (rows + 1).
+// `batch` slices of [rows][ncol] values (slice b at offset b * bstride), ncol even:
+//   out[k-1][c] = sum_{p=1..rows} in[p-1][c] sin(pi k p / (rows + 1)), k = 1..rows;
+// inB / outB (both or neither): a second array in the same launch.  in and out
+// must not overlap.  L = 2 (rows + 1).
 template <typename T>
-hipError_t launch_dst_cols(int L, const T* inA, const T* inB, T* outA, T* outB, const void* tw,
-                           int ncol, int cstride, int coff, int rows, int ld, int batch,
-                           size_t bstride, hipStream_t s);
+hipError_t launch_dst_cols(int L, const T* inA, T* outA, const T* inB, T* outB, const void* tw,
+                           int ncol, int rows, int batch, size_t bstride, hipStream_t s);
 // Pass C: inverse row transforms of P1, P2 and the mask combine -> z (FP64).
 template <typename T>
 hipError_t launch_pc_rows_inv(int Lx, const T* P1, const T* P2,

@@ -140,11 +140,11 @@ __global__ __launch_bounds__(PcCfg<L>::THR_R) void k_pc_rows_fwd(
 }
 
 // --------------------------------------------------------------------------
-// Pass B: slot-column pairs (ca, cb) of Q -> P1, P2 columns.
+// Pass B, tiled: slot-column pairs (2c, 2c + 1) of Q -> (P1, P2) pairs.
 // --------------------------------------------------------------------------
-template <typename T, int L, int BC, bool TL>
+template <typename T, int L, int BC>
 __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
-    const T* __restrict__ Q, T* __restrict__ P1, T* __restrict__ P2,
+    const T* __restrict__ Q, T* __restrict__ P1,
     const T* __restrict__ lamx_slot, const T* __restrict__ lamy_pos,
     const cpx<T>* __restrict__ tw, int n1, int n2, T kx, T ky, T dpen, T halfK, const Members mb,
     const double* __restrict__ mk) {
@@ -156,7 +156,6 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     const size_t mt = mo * (sizeof(double) / sizeof(T));
     Q += mt;
     P1 += mt;
-    if (P2) P2 += mt;
     if (mk) {
       kx = (T)mk[mo];
       ky = (T)mk[mo + 1];
@@ -165,15 +164,9 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
   const int tid = threadIdx.x;
   const int b = tid % BC, tau = tid / BC;
   const int strip = xcd_remap(blockIdx.x, gridDim.x);
-  // Column pair of FFT b.  Tiled: (2c, 2c+1), adjacent in one tile row.
-  // Natural: (base + b, base + b + BC) of the block's 2 BC columns, so that
-  // each inverse sweep writes BC adjacent columns of a row (with (2c, 2c+1)
-  // every sweep wrote every other column and half-written lines doubled the
-  // write traffic).
-  const int ca = TL ? 2 * (strip * BC + b) : 2 * BC * strip + b;
-  const int cb = TL ? ca + 1 : ca + BC;
+  const int ca = 2 * (strip * BC + b), cb = ca + 1;  // adjacent in one tile row
   const int ld = n1 + 1, hp = (n2 + 1) >> 1;
-  const bool va = ca < ld, vb = cb < ld;  // tiled: ld and ca even, both or neither
+  const bool va = ca < ld, vb = va;  // ld and ca even: both or neither
   using V2 = typename Vec2<T>::type;
   cpx<T> reg[F::PP];
   static_for<F::PP>([&](auto ee) {
@@ -187,16 +180,10 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
       row = L - p - 1;
       sgn = (T)-1;
     }
-    if constexpr (TL) {
-      // ca is even: (ca, cb) are adjacent elements of one tile row
-      const bool ok = vb && row >= 0;
-      const V2 q = ok ? *(const V2*)(Q + tile_index(row, ca, hp)) : V2{(T)0, (T)0};
-      reg[e].re = sgn * q.x;
-      reg[e].im = sgn * q.y;
-    } else {
-      reg[e].re = (va && row >= 0) ? sgn * Q[(size_t)row * ld + ca] : (T)0;
-      reg[e].im = (vb && row >= 0) ? sgn * Q[(size_t)row * ld + cb] : (T)0;
-    }
+    const bool ok = vb && row >= 0;
+    const V2 q = ok ? *(const V2*)(Q + tile_index(row, ca, hp)) : V2{(T)0, (T)0};
+    reg[e].re = sgn * q.x;
+    reg[e].im = sgn * q.y;
   });
   T* my = lds + b;  // regions interleaved (stride BC)
   // (no register materialisation between the sweeps here: it measured slower)
@@ -222,13 +209,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
     if (va && p >= 1 && p <= n2) {
-      if constexpr (TL) {
-        *(V2*)(P1 + pair_index<T>(p - 1, ca, n2)) = V2{reg[e].re, reg[e].im};
-      } else {
-        const size_t i = (size_t)(p - 1) * ld + ca;
-        P1[i] = reg[e].re;
-        P2[i] = reg[e].im;
-      }
+      *(V2*)(P1 + pair_index<T>(p - 1, ca, n2)) = V2{reg[e].re, reg[e].im};
     }
   });
   // Hide the table pointer from the optimiser so that the second sweep reloads
@@ -253,70 +234,128 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
     if (vb && p >= 1 && p <= n2) {
-      if constexpr (TL) {
-        *(V2*)(P1 + pair_index<T>(p - 1, cb, n2)) = V2{reg[e].re, reg[e].im};
-      } else {
-        const size_t i = (size_t)(p - 1) * ld + cb;
-        P1[i] = reg[e].re;
-        P2[i] = reg[e].im;
-      }
+      *(V2*)(P1 + pair_index<T>(p - 1, cb, n2)) = V2{reg[e].re, reg[e].im};
     }
   });
 }
 
 // --------------------------------------------------------------------------
-// Raw sine transform along columns (used between the x and z transforms of
-// the three-dimensional preconditioner, where the y transform stands alone).
-// One FFT of length L = 2(rows+1) per column pair: column ca of inA in the
-// real part, column cb of inB in the imaginary part, both odd-extended; the
-// spectrum is 2 sigma_b - 2i sigma_a, read at frequencies 1..rows.
+// Pass B on [n2][ld] arrays (the z pass of three-dimensional plans): columns 2c
+// and 2c + 1 share every transform, the forward one and one inverse per field,
+// so each load and store moves both columns and a wavefront whole lines (one
+// inverse per column, with its (P1, P2) pair, wrote half-lines at two times: 213
+// -> 169 us at 255^3, 3.1 TB/s of its 24 bytes a slot).  ld = n1 + 1 is even.
 // --------------------------------------------------------------------------
 template <typename T, int L, int BC>
-__global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
-    const T* __restrict__ inA, const T* __restrict__ inB, T* __restrict__ outA,
-    T* __restrict__ outB, const cpx<T>* __restrict__ tw, int ncol, int cstride, int coff,
-    int rows, int ld, size_t bstride) {
+__global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
+    const T* __restrict__ Q, T* __restrict__ P1, T* __restrict__ P2,
+    const T* __restrict__ lamx_slot, const T* __restrict__ lamy_pos,
+    const cpx<T>* __restrict__ tw, int n1, int n2, T kx, T ky, T dpen, T halfK) {
   using C = PcColCfg<L>;
   using F = typename C::F;
+  using V2 = typename Vec2<T>::type;
   __shared__ T lds[BC * lds_len(L)];
-  {
-    const size_t off = (size_t)blockIdx.y * bstride;
-    inA += off;
-    inB += off;
-    outA += off;
-    outB += off;
-  }
   const int tid = threadIdx.x;
   const int b = tid % BC, tau = tid / BC;
-  const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
-  const bool valid = c < ncol;
-  const int ca = c * cstride, cb = ca + coff;
+  const int ld = n1 + 1;
+  const int ca = 2 * (xcd_remap(blockIdx.x, gridDim.x) * BC + b);
+  const bool va = ca < ld;
+  const int cc = va ? ca : 0;
   cpx<T> reg[F::PP];
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
-    int row = -1;
-    T sgn = (T)1;
-    if (p >= 1 && p <= rows) {
-      row = p - 1;
-    } else if (p >= rows + 2) {
-      row = L - p - 1;
-      sgn = (T)-1;
-    }
-    const bool ok = valid && row >= 0;
-    reg[e].re = ok ? sgn * inA[(size_t)row * ld + ca] : (T)0;
-    reg[e].im = ok ? sgn * inB[(size_t)row * ld + cb] : (T)0;
+    // odd extension; clamped loads, all in flight at once
+    const bool up = p > n2;
+    const int row = up ? L - p - 1 : p - 1;
+    const bool ok = va && row >= 0 && row < n2;
+    const V2 q = *(const V2*)(Q + (size_t)(ok ? row : 0) * ld + cc);
+    const T sgn = ok ? (up ? (T)-1 : (T)1) : (T)0;
+    reg[e].re = sgn * q.x;
+    reg[e].im = sgn * q.y;
+  });
+  T* my = lds + b;  // regions interleaved (stride BC)
+  fft_forward<T, F, false, BC>(reg, tau, tw, my);
+  // spectrum = 2 rho_b - 2i rho_a; kept: K rho / (2 E1 E2) of both columns
+  const T lxa = kx * lamx_slot[cc], lxb = kx * lamx_slot[cc + 1];
+  cpx<T> rho[F::PP];
+  static_for<F::PP>([&](auto ee) {
+    constexpr int e = decltype(ee)::value;
+    const T ly = ky * lamy_pos[F::pos(F::NS - 1, tau, e)];
+    const T a1 = (T)1 - lxa - ly, a2 = a1 + dpen;
+    const T b1 = (T)1 - lxb - ly, b2 = b1 + dpen;
+    rho[e].re = halfK * ((T)-0.5 * reg[e].im) / (a1 * a2);
+    rho[e].im = halfK * ((T)0.5 * reg[e].re) / (b1 * b2);
+  });
+#pragma unroll 1
+  for (int f = 0; f < 2; ++f) {  // P1 (1 / E1), then P2 (1 / E2)
+    // opaque thread index and tables: nothing per point is hoisted out of the loop
+    int th = tau, z0 = 0;
+    asm volatile("" : "+v"(th), "+s"(z0));
+    const T* lamy = lamy_pos + z0;
+    const T add = f == 0 ? dpen : (T)0;
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const T ly = ky * lamy[F::pos(F::NS - 1, th, e)];
+      // rho / E1 = kept * E2, rho / E2 = kept * E1; (K/2) (rho_b - i rho_a) gives a + i b
+      reg[e].re = rho[e].im * ((T)1 - lxb - ly + add);
+      reg[e].im = -rho[e].re * ((T)1 - lxa - ly + add);
+    });
+    fft_inverse<T, F, false, BC>(reg, th, tw + z0, my);
+    T* out = f == 0 ? P1 : P2;
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const int p = F::pos(0, th, e);
+      if (va && p >= 1 && p <= n2) *(V2*)(out + (size_t)(p - 1) * ld + ca) = V2{reg[e].re, reg[e].im};
+    });
+  }
+}
+
+// --------------------------------------------------------------------------
+// Raw sine transform along columns (used between the x and z transforms of
+// the three-dimensional preconditioner, where the y transform stands alone).
+// One FFT of length L = 2(rows+1) per pair of adjacent columns 2c, 2c + 1 (real
+// and imaginary part), both odd-extended; the spectrum is 2 sigma_b - 2i sigma_a,
+// read at frequencies 1..rows.  Loads and stores move both columns (the same
+// column of two arrays per transform took 121 us a launch on average at 255^3, now
+// 91).  Grid dimension y:
+// slices; z: the array.  ncol is even.
+// --------------------------------------------------------------------------
+template <typename T, int L, int BC>
+__global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
+    const T* __restrict__ inA, T* __restrict__ outA, const T* __restrict__ inB,
+    T* __restrict__ outB, const cpx<T>* __restrict__ tw, int ncol, int rows, size_t bstride) {
+  using C = PcColCfg<L>;
+  using F = typename C::F;
+  using V2 = typename Vec2<T>::type;
+  __shared__ T lds[BC * lds_len(L)];
+  const size_t off = (size_t)blockIdx.y * bstride;
+  const T* in = (blockIdx.z ? inB : inA) + off;
+  T* out = (blockIdx.z ? outB : outA) + off;
+  const int tid = threadIdx.x;
+  const int b = tid % BC, tau = tid / BC;
+  const int ca = 2 * (xcd_remap(blockIdx.x, gridDim.x) * BC + b);
+  const bool valid = ca < ncol;
+  const int cc = valid ? ca : 0;
+  cpx<T> reg[F::PP];
+  static_for<F::PP>([&](auto ee) {
+    constexpr int e = decltype(ee)::value;
+    const int p = F::pos(0, tau, e);
+    const bool up = p > rows;
+    const int row = up ? L - p - 1 : p - 1;
+    const bool ok = valid && row >= 0 && row < rows;
+    const V2 q = *(const V2*)(in + (size_t)(ok ? row : 0) * ncol + cc);
+    const T sgn = ok ? (up ? (T)-1 : (T)1) : (T)0;
+    reg[e].re = sgn * q.x;
+    reg[e].im = sgn * q.y;
   });
   T* my = lds + b;  // regions interleaved (stride BC)
   fft_forward<T, F, false, BC>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int f = fft_freq(L, fft_pts(L), F::pos(F::NS - 1, tau, e));
-    if (valid && f >= 1 && f <= rows) {
-      const size_t i = (size_t)(f - 1) * ld;
-      outA[i + ca] = (T)-0.5 * reg[e].im;
-      outB[i + cb] = (T)0.5 * reg[e].re;
-    }
+    if (valid && f >= 1 && f <= rows)
+      *(V2*)(out + (size_t)(f - 1) * ncol + ca) = V2{(T)-0.5 * reg[e].im, (T)0.5 * reg[e].re};
   });
 }
 
@@ -551,18 +590,24 @@ static bool small_cols(long cols, long copies) {
   return C::BCS < C::BCL && (cols + C::BCL - 1) / C::BCL * copies < kSmallGridBlocks;
 }
 
-template <typename T, int L, bool TL>
+template <typename T, int L>
 static hipError_t pc_cols_impl(const T* Q, T* P1, T* P2, const T* lamx, const T* lamy,
                                const void* tw, int n1, int n2, double kx, double ky, double dpen,
-                               double Kfac, hipStream_t s, const Members& mb, const double* mk) {
+                               double Kfac, bool tiled, hipStream_t s, const Members& mb,
+                               const double* mk) {
   using C = PcColCfg<L>;
   const int pairs = (n1 + 1) / 2;
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
+  if (!tiled && ((n1 & 1) == 0 || mb.n != 1 || mk)) return hipErrorInvalidValue;
   auto go = [&](auto bc) {
     constexpr int BC = decltype(bc)::value;
-    hipLaunchKernelGGL((k_pc_cols<T, L, BC, TL>), dim3((pairs + BC - 1) / BC, 1, mb.n),
-                       dim3(BC * C::TPF), 0, s, Q, P1, P2, lamx, lamy, (const cpx<T>*)tw, n1, n2,
-                       (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
+    const dim3 g((pairs + BC - 1) / BC, 1, mb.n), t(BC * C::TPF);
+    if (tiled)
+      hipLaunchKernelGGL((k_pc_cols<T, L, BC>), g, t, 0, s, Q, P1, lamx, lamy, (const cpx<T>*)tw, n1,
+                         n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
+    else
+      hipLaunchKernelGGL((k_pc_cols_nat<T, L, BC>), g, t, 0, s, Q, P1, P2, lamx, lamy,
+                         (const cpx<T>*)tw, n1, n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac));
   };
   if (small_cols<L>(pairs, mb.n)) go(std::integral_constant<int, C::BCS>{});
   else go(std::integral_constant<int, C::BCL>{});
@@ -607,18 +652,20 @@ static hipError_t pc_rows_inv_mv_impl(const T* P1, const T* P2,
 }
 
 template <typename T, int L>
-static hipError_t dst_cols_impl(const T* inA, const T* inB, T* outA, T* outB, const void* tw,
-                                int ncol, int cstride, int coff, int rows, int ld, int batch,
-                                size_t bstride, hipStream_t s) {
+static hipError_t dst_cols_impl(const T* inA, T* outA, const T* inB, T* outB, const void* tw,
+                                int ncol, int rows, int batch, size_t bstride, hipStream_t s) {
   using C = PcColCfg<L>;
-  if (L != 2 * (rows + 1) || batch < 1 || batch > 65535 || ncol < 1) return hipErrorInvalidValue;
+  if (L != 2 * (rows + 1) || batch < 1 || batch > 65535 || ncol < 2 || (ncol & 1) ||
+      (!inB) != (!outB))
+    return hipErrorInvalidValue;
+  const int nz = inB ? 2 : 1;
   auto go = [&](auto bc) {
     constexpr int BC = decltype(bc)::value;
-    hipLaunchKernelGGL((k_dst_cols<T, L, BC>), dim3((ncol + BC - 1) / BC, batch), dim3(BC * C::TPF),
-                       0, s, inA, inB, outA, outB, (const cpx<T>*)tw, ncol, cstride, coff, rows, ld,
+    hipLaunchKernelGGL((k_dst_cols<T, L, BC>), dim3((ncol / 2 + BC - 1) / BC, batch, nz),
+                       dim3(BC * C::TPF), 0, s, inA, outA, inB, outB, (const cpx<T>*)tw, ncol, rows,
                        bstride);
   };
-  if (small_cols<L>(ncol, batch)) go(std::integral_constant<int, C::BCS>{});
+  if (small_cols<L>(ncol / 2, (long)batch * nz)) go(std::integral_constant<int, C::BCS>{});
   else go(std::integral_constant<int, C::BCL>{});
   return hipGetLastError();
 }
@@ -704,10 +751,7 @@ static hipError_t cols_any(const T* Q, T* P1, T* P2, const T* lamx, const T* lam
       return sd_cols_impl<T, L>(Q, P1, lamx, lamy, tw, sd.twS, n1, n2, kx, ky, dpen, Kfac, s, mb,
                                 mk);
   }
-  return tiled ? pc_cols_impl<T, L, true>(Q, P1, P2, lamx, lamy, tw, n1, n2, kx, ky, dpen, Kfac,
-                                          s, mb, mk)
-               : pc_cols_impl<T, L, false>(Q, P1, P2, lamx, lamy, tw, n1, n2, kx, ky, dpen, Kfac,
-                                           s, mb, mk);
+  return pc_cols_impl<T, L>(Q, P1, P2, lamx, lamy, tw, n1, n2, kx, ky, dpen, Kfac, tiled, s, mb, mk);
 }
 
 template <typename T, int L>
@@ -778,14 +822,12 @@ hipError_t launch_pc_cols(int Ly, const T* Q, T* P1, T* P2, const T* lamx_slot,
 }
 
 template <typename T>
-hipError_t launch_dst_cols(int L, const T* inA, const T* inB, T* outA, T* outB, const void* tw,
-                           int ncol, int cstride, int coff, int rows, int ld, int batch,
-                           size_t bstride, hipStream_t s) {
+hipError_t launch_dst_cols(int L, const T* inA, T* outA, const T* inB, T* outB, const void* tw,
+                           int ncol, int rows, int batch, size_t bstride, hipStream_t s) {
   switch (L) {
 #define X(LL) \
   case LL:    \
-    return dst_cols_impl<T, LL>(inA, inB, outA, outB, tw, ncol, cstride, coff, rows, ld, batch, \
-                                bstride, s);
+    return dst_cols_impl<T, LL>(inA, outA, inB, outB, tw, ncol, rows, batch, bstride, s);
     RSFDE_LD_CASES(X)
 #undef X
     default:

@@ -555,7 +555,7 @@ int precond3(Plan* P, const double* r, const double* sig, double* z, std::map<in
   }
   {
     ProfScope ps(P, s, kCatDstCols, 2.0 * ts * S);
-    CK(launch_dst_cols<T>(P->Ldy, Q, Q, R, R, tw[P->Ldy], ld / 2, 2, 1, n2, ld, n3, plane, s));
+    CK(launch_dst_cols<T>(P->Ldy, Q, R, nullptr, nullptr, tw[P->Ldy], ld, n2, n3, plane, s));
   }
   {
     ProfScope ps(P, s, kCatPcCols, 3.0 * ts * S);
@@ -564,7 +564,7 @@ int precond3(Plan* P, const double* r, const double* sig, double* z, std::map<in
   }
   {
     ProfScope ps(P, s, kCatDstCols, 4.0 * ts * S);
-    CK(launch_dst_cols<T>(P->Ldy, P1, P2, Q, R, tw[P->Ldy], ld, 1, 0, n2, ld, n3, plane, s));
+    CK(launch_dst_cols<T>(P->Ldy, P1, Q, P2, R, tw[P->Ldy], ld, n2, n3, plane, s));
   }
   if (!w || P->Ldx != P->Lcx) {  // unfused (n1 = 1: convolution and sine lengths differ)
     {

@@ -95,3 +95,39 @@ def test_chirp_forms(n1, n2):
     ref = O.precond_apply_fft(p, V)
     assert_precond(z64, ref, p, "fp64")
     assert_precond(z32, ref, p, "fp32")
+
+
+# Column pairs of the product with one load and store each: one column in all,
+# an odd last column, rows that start at odd addresses; a z view of one column
+# and of an odd number of columns
+@pytest.mark.parametrize("shape", [(1, 5, 0), (2, 5, 0), (3, 1, 0), (511, 9, 0), (5, 2047, 0),
+                                   (9, 4095, 0), (1, 1, 7), (1, 3, 5), (3, 3, 31), (7, 5, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_matvec_column_pairs(shape):
+    n1, n2, n3 = shape
+    rng = np.random.default_rng(sum(shape))
+    if n3:
+        box = (0.0, 1.0, -0.1, 1.2, 0.2, 1.1)
+        p = O.Problem3(n1, n2, n3, box, 1.55, 1.75, 1.85, 1.0, 0.8, 1.2, 1e-6, 1.0 / 16,
+                       ellipsoid_mask(n1, n2, n3))
+        pl = RsfdePlan.setup3(shape, box, (p.alpha1, p.alpha2, p.alpha3), (p.kx, p.ky, p.kz),
+                              torch.as_tensor(p.mask), p.eta, p.dt, 2)
+        V = rng.standard_normal(p.shape)
+        ref, cols = O.matvec3(p, V), ((p.cx, p.alpha1, n1), (p.cy, p.alpha2, n2), (p.cz, p.alpha3, n3))
+    else:
+        box = (0.0, 1.0, 0.0, 1.0)
+        mask = domain_mask(n1, n2, box, SHAPES["disk"](0.5, 0.5, 0.4))
+        p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+        pl = RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2)
+        V = rng.standard_normal((n2, n1))
+        ref, cols = O.matvec(p, V), ((p.cx, p.alpha1, n1), (p.cy, p.alpha2, n2))
+    nm = 1.0 + p.d + 2 * sum(np.abs(c * O.toeplitz_first_column(a, n)).sum() for c, a, n in cols)
+    with pl:
+        # an output 8 bytes off a 16-byte boundary, with guard values on both sides
+        x, out = torch.zeros(V.size + 3, dtype=torch.float64, device=DEV), None
+        x[1:1 + V.size] = _t(V)
+        out = torch.full((V.size + 3,), 7.0, dtype=torch.float64, device=DEV)
+        w = pl.matvec(x[1:1 + V.size], out[1:1 + V.size]).cpu().numpy().reshape(V.shape)
+        g = out.cpu().numpy()
+    assert np.abs(w - ref).max() <= 1e-13 * nm * np.abs(V).max()
+    assert g[0] == 7.0 and g[-2] == 7.0 and g[-1] == 7.0
