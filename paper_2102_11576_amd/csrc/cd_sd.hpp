@@ -65,7 +65,7 @@ __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int 
     sd_forward<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
   }
   const cpx<T>* kr = khat + r * S::LS;
-  static_for<16>([&](auto ee) {
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     v[e] = cmul(v[e], kr[Fs::pos(Fs::NS - 1, tau, e)]);
   });

@@ -150,16 +150,16 @@ static double run_sd_case(unsigned seed) {
   std::vector<std::array<cpx<T>, 16>> regs(S::TPD);
   for (int r = 0; r < 9; ++r) {
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) regs[r * S::TS + tau][e] = buf[r * LS + Fs::pos(0, tau, e)];
+      for (int e = 0; e < S::PS; ++e) regs[r * S::TS + tau][e] = buf[r * LS + Fs::pos(0, tau, e)];
     std::vector<cpx<T>> sb(LS);
     static_for<Fs::NS>([&](auto tt) {
       constexpr int t = decltype(tt)::value;
       for (int tau = 0; tau < S::TS; ++tau) Fs::template dif_stage<T, t>(regs[r * S::TS + tau].data(), tau, twS.data());
       if constexpr (t < Fs::NS - 1) {
         for (int tau = 0; tau < S::TS; ++tau)
-          for (int e = 0; e < 16; ++e) sb[Fs::pos(t, tau, e)] = regs[r * S::TS + tau][e];
+          for (int e = 0; e < S::PS; ++e) sb[Fs::pos(t, tau, e)] = regs[r * S::TS + tau][e];
         for (int tau = 0; tau < S::TS; ++tau)
-          for (int e = 0; e < 16; ++e) regs[r * S::TS + tau][e] = sb[Fs::pos(t + 1, tau, e)];
+          for (int e = 0; e < S::PS; ++e) regs[r * S::TS + tau][e] = sb[Fs::pos(t + 1, tau, e)];
       }
     });
   }
@@ -169,7 +169,7 @@ static double run_sd_case(unsigned seed) {
   std::vector<cpx<T>> slotv(L / 2);
   for (int r = 0; r < 9; ++r)
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < S::PS; ++e) {
         const int P = r * LS + Fs::pos(Fs::NS - 1, tau, e);
         const int f = S::freq(P), k = S::fold(f);
         const double sg = f <= L / 2 ? 1.0 : -1.0;
@@ -185,7 +185,7 @@ static double run_sd_case(unsigned seed) {
         err = std::fmax(err, std::fabs((double)v.im - zi));
         scale = std::fmax(scale, std::fabs(zr) + std::fabs(zi));
         const int c = S::slot(r, tau, e);
-        const bool lower = fft_freq(LS, 16, P % LS) < LS / 2;
+        const bool lower = fft_freq(LS, S::PS, P % LS) < LS / 2;
         if ((c < 0) != ((r == 0 || r == 8) && !lower)) { printf("sd L=%d: slot set wrong\n", L); return 1e9; }
         if (c >= 0) {
           if (c >= L / 2) { printf("sd L=%d: slot out of range\n", L); return 1e9; }
@@ -199,13 +199,13 @@ static double run_sd_case(unsigned seed) {
   std::vector<int> by_freq(L, -1);
   for (int r = 0; r < 9; ++r)
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < S::PS; ++e) {
         const int c = S::slot(r, tau, e);
         if (c >= 0) by_freq[S::freq(r * LS + Fs::pos(Fs::NS - 1, tau, e))] = c;
       }
   for (int r = 0; r < 9; ++r) {
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < S::PS; ++e) {
         const int c = S::slot(r, tau, e);
         const int f = S::freq(r * LS + Fs::pos(Fs::NS - 1, tau, e));
         cpx<T> v{(T)0, (T)0};
@@ -223,13 +223,13 @@ static double run_sd_case(unsigned seed) {
       for (int tau = 0; tau < S::TS; ++tau) Fs::template dit_stage<T, t>(regs[r * S::TS + tau].data(), tau, twS.data());
       if constexpr (t > 0) {
         for (int tau = 0; tau < S::TS; ++tau)
-          for (int e = 0; e < 16; ++e) sb[Fs::pos(t, tau, e)] = regs[r * S::TS + tau][e];
+          for (int e = 0; e < S::PS; ++e) sb[Fs::pos(t, tau, e)] = regs[r * S::TS + tau][e];
         for (int tau = 0; tau < S::TS; ++tau)
-          for (int e = 0; e < 16; ++e) regs[r * S::TS + tau][e] = sb[Fs::pos(t - 1, tau, e)];
+          for (int e = 0; e < S::PS; ++e) regs[r * S::TS + tau][e] = sb[Fs::pos(t - 1, tau, e)];
       }
     });
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) buf[r * LS + Fs::pos(0, tau, e)] = regs[r * S::TS + tau][e];
+      for (int e = 0; e < S::PS; ++e) buf[r * LS + Fs::pos(0, tau, e)] = regs[r * S::TS + tau][e];
   }
   std::vector<cpx<T>> y(n + 1, cpx<T>{(T)1e30, (T)1e30});
   for (int q = 0; q < S::NG; ++q) {

@@ -674,10 +674,7 @@ template <typename T, int L>
 static hipError_t sd_rows_fwd_impl(const double* v, const double* sig, T* Q, const void* twL,
                                    const void* twS, int n1, int n2, hipStream_t s,
                                    const Members& mb) {
-  using C = SdRows<L>;
-  const int pairs = (n2 + 1) / 2;
-  const int blocks = (pairs + C::ND - 1) / C::ND;
-  hipLaunchKernelGGL((k_sd_rows_fwd<T, L>), dim3(blocks, 1, mb.n), dim3(C::THR), 0, s, v, sig, Q,
+  hipLaunchKernelGGL((k_sd_rows_fwd<T, L>), dim3((n2 + 1) / 2, 1, mb.n), dim3(Sd<L>::TPD), 0, s, v, sig, Q,
                      (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, mb);
   return hipGetLastError();
 }
@@ -688,10 +685,7 @@ static hipError_t sd_cols_impl(const T* Q, T* P, const T* lamx, const T* lamy, c
                                double dpen, double Kfac, hipStream_t s, const Members& mb,
                                const double* mk) {
   using C = SdCols<L>;
-  constexpr int BC = C::BC;
-  const int pairs = (n1 + 1) / 2;
-  const int blocks = (pairs + BC - 1) / BC;
-  hipLaunchKernelGGL((k_sd_cols<T, L>), dim3(blocks, 1, mb.n), dim3(C::THR), 0, s, Q, P, lamx,
+  hipLaunchKernelGGL((k_sd_cols<T, L>), dim3((n1 + 1) / 2, 1, mb.n), dim3(C::THR), 0, s, Q, P, lamx,
                      lamy, (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, (T)kx, (T)ky, (T)dpen,
                      (T)(0.5 * Kfac), mb, mk);
   return hipGetLastError();
@@ -701,9 +695,7 @@ template <typename T, int L>
 static hipError_t sd_rows_inv_impl(const T* P, const uint8_t* mask, double* z, const void* twL,
                                    const void* twS, const int32_t* msl, int n1, int n2,
                                    hipStream_t s, const Members& mb) {
-  using C = SdRows<L>;
-  const int blocks = (n2 + C::ND - 1) / C::ND;
-  hipLaunchKernelGGL((k_sd_rows_inv<T, L>), dim3(blocks, 1, mb.n), dim3(C::THR), 0, s, P, mask, z,
+  hipLaunchKernelGGL((k_sd_rows_inv<T, L>), dim3(n2, 1, mb.n), dim3(Sd<L>::TPD), 0, s, P, mask, z,
                      (const cpx<T>*)twL, (const cpx<T>*)twS, msl, n1, n2, mb);
   return hipGetLastError();
 }

@@ -382,13 +382,13 @@ hipError_t chirp_dir(Plan* P, int n, int L, bool sym, CdDir (&d)[2], hipStream_t
   hipError_t e;
   if ((e = upload(P, &c64, ch, s)) != hipSuccess || (e = upload(P, &c32, chf, s)) != hipSuccess)
     return e;
+  const int Ls = sym ? cd_sym_length(n) : 0;
+  const int Lt = Ls ? Ls : L;
+  const std::vector<double> kh = Ls ? chirp_sym_khat(n, Ls) : chirp_khat(n, L);
+  if (kh.empty()) return hipErrorInvalidValue;
+  if ((e = ensure_twiddles(P, Lt, s)) != hipSuccess) return e;
+  if (Ls && (e = ensure_twiddles(P, Ls / 16, s)) != hipSuccess) return e;
   for (int t = 0; t < 2; ++t) {
-    const int Ls = sym ? cd_sym_length(n) : 0;
-    const int Lt = Ls ? Ls : L;
-    const std::vector<double> kh = Ls ? chirp_sym_khat(n, Ls) : chirp_khat(n, L);
-    if (kh.empty()) return hipErrorInvalidValue;
-    if ((e = ensure_twiddles(P, Lt, s)) != hipSuccess) return e;
-    if (Ls && (e = ensure_twiddles(P, Ls / 16, s)) != hipSuccess) return e;
     auto& tw = t == 0 ? P->tw64 : P->tw32;
     void* k = nullptr;
     if (t == 0) {
@@ -1376,7 +1376,7 @@ void sd_tables_L(const std::vector<double>& lam, std::vector<double>* by_slot,
   std::vector<int> slot_at(S::NPOS, -1), slot_of_freq(L, -1);
   for (int r = 0; r < 9; ++r)
     for (int tau = 0; tau < S::TS; ++tau)
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < S::PS; ++e) {
         const int P = r * S::LS + Fs::pos(Fs::NS - 1, tau, e);
         const int c = S::slot(r, tau, e);
         slot_at[P] = c;

@@ -37,11 +37,20 @@ namespace rsfde {
 // Smallest L handled by the symmetric form (sub-FFTs of at least 32 points).
 constexpr int kSdMinL = 512;
 
+// Points per thread of the sub-FFTs: 8 up to L = 2048, where a grid has at most
+// 512 transforms per pass and their serial time decides (twice the threads of 16
+// points; whole preconditioner 255^2 22.4 -> 17.6 us, 511^2 23.7 -> 20.4, 1023^2
+// 39.4 -> 36.9), 16 beyond, where one more register stage costs more than the
+// threads give (2047^2 with 8: 79.8 -> 101.7 us).  4 up to L = 1024: as 8 (511^2
+// 20.3 -> 20.1) but 9 % slower in batches.
+constexpr int sd_pts(int L) { return L <= 2048 ? 8 : 16; }
+
 template <int L>
 struct Sd {
   static constexpr int LS = L / 16;  // block (sub-FFT) length
   static_assert(LS >= 32 && (LS & (LS - 1)) == 0, "symmetric DST needs L >= 512, a power of two");
-  using Fs = Fft<LS, 16>;                    // sub-FFT engine, 16 points per thread
+  static constexpr int PS = sd_pts(L);       // points per thread of a sub-FFT
+  using Fs = Fft<LS, PS>;                    // sub-FFT engine
   static constexpr int TS = Fs::TPF;         // threads of one sub-FFT
   static constexpr int TPD = 9 * TS;         // block-stage threads of one transform
   static constexpr int NG = LS / 2 + 1;      // group-stage threads of one transform
@@ -76,7 +85,7 @@ struct Sd {
     return (r == 8 ? LS / 2 : 0) + lr * TS + tau;
   }
   // Frequency (0..L-1) held at block position P = r * LS + q after the forward sweep.
-  static RS_HD int freq(int P) { return P / LS + 16 * fft_freq(LS, 16, P % LS); }
+  static RS_HD int freq(int P) { return P / LS + 16 * fft_freq(LS, PS, P % LS); }
   // DST index (0..L/2) of a frequency of the odd spectrum.
   static constexpr RS_HD int fold(int f) { return f <= L / 2 ? f : L - f; }
 };

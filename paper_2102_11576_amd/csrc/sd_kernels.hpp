@@ -4,8 +4,7 @@
 // as the plain passes (Q strip-tiled, the (P1, P2) pairs in pair_index order),
 // but the x slots follow Sd<L>::slot, and pass B's y eigenvalues are indexed
 // by block position.  One transform takes 9 sub-FFTs of TS threads (TPD
-// threads); the row passes run ND transforms per block and pass B BC column
-// pairs, interleaved (SdRows, SdCols).
+// threads).
 #pragma once
 
 #include "fft_common.hpp"
@@ -30,24 +29,16 @@ __device__ __forceinline__ size_t pair_index(int r, int c, int rows) {
   return (((size_t)(c / W) * rows + r) * W + pos) * 2;
 }
 
-// Transforms per block of the row passes and column pairs per block of pass B
-// (one transform = 9 sub-FFTs of TS threads each): one from L = 4096 on and
-// up to L = 1024 (grids of at most 511 rows or columns: more, smaller blocks
-// spread them over more CUs), 16 / TS = 2 at L = 2048.  Small blocks keep
-// more of them resident per CU (pass B's pair takes 38 KB of LDS with its
-// stash at L = 4096), which hides more latency.
-template <int L>
-struct SdRows {
-  static constexpr int ND = (L <= 1024 || Sd<L>::TS >= 16) ? 1 : 16 / Sd<L>::TS;
-  static constexpr int THR = ND * Sd<L>::TPD;
-};
+// One transform (row passes) or column pair (pass B) per block: 9 sub-FFTs of TS
+// threads.  Small blocks keep more of them resident per CU (pass B's pair takes
+// 38 KB of LDS with its stash at L = 4096), which hides more latency, and spread
+// the smaller grids over more CUs.
 template <int L>
 struct SdCols {
-  static constexpr int BC = (L <= 1024 || Sd<L>::TS >= 16) ? 1 : 16 / Sd<L>::TS;
   // Up to L = 2048 the two inverse sweeps of a column pair run at once, on a
-  // second set of BC TPD threads (too few column pairs to fill the GPU there).
+  // second set of TPD threads (too few column pairs to fill the GPU there).
   static constexpr bool CONC = L <= 2048;
-  static constexpr int THR = (CONC ? 2 : 1) * BC * Sd<L>::TPD;
+  static constexpr int THR = (CONC ? 2 : 1) * Sd<L>::TPD;
 };
 // Threads of one sub-FFT inside one wavefront (ST: LDS interleave of the
 // transforms of a block): its exchanges then need no block barrier.
@@ -156,9 +147,9 @@ __device__ __forceinline__ void sd_load_spectrum(cpx<T>* v, const T* __restrict_
   const int mbase = r == 8 ? LS : 0;
   const int rr = vr ? row : 0;
   const T half = vr ? (T)0.5 : (T)0;
-  int c[16];
-  int sgn[16];  // odd-symmetry sign of the upper registers (0: frequency L/2)
-  static_for<16>([&](auto ee) {
+  int c[S::PS];
+  int sgn[S::PS];  // odd-symmetry sign of the upper registers (0: frequency L/2)
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     constexpr int lr = S::lower_rank(e);
     if constexpr (lr >= 0) {
@@ -169,7 +160,7 @@ __device__ __forceinline__ void sd_load_spectrum(cpx<T>* v, const T* __restrict_
       sgn[e] = edge ? (m >= 0 ? -1 : 0) : 1;
     }
   });
-  static_for<16>([&](auto ee) {
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const V2 q = *(const V2*)(P + pair_index<T>(rr, c[e], rows));
     T h = half;
@@ -215,25 +206,24 @@ __device__ __forceinline__ void sd_store_z(const cpx<T>* v, int q, int row, bool
 }
 
 // --------------------------------------------------------------------------
-// Pass A: row pairs (ra, rb) -> Q (strip-tiled), ND row pairs per block.
+// Pass A: row pairs (ra, rb) -> Q (strip-tiled), one row pair per block.
 // --------------------------------------------------------------------------
 template <typename T, int L>
-__global__ __launch_bounds__(SdRows<L>::THR) void k_sd_rows_fwd(
+__global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_fwd(
     const double* __restrict__ v, const double* __restrict__ sig, T* __restrict__ Q,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS, int n1, int n2,
     const Members mb) {
   using S = Sd<L>;
-  using C = SdRows<L>;
-  __shared__ T lds[C::ND * S::LEN];
+  __shared__ T lds[S::LEN];
   {  // member of a batched launch (grid dimension z); offsets in doubles
     const size_t mo = mb.off(blockIdx.z);
     v += mo;
     if (sig) sig += mo;
     Q += mo * (sizeof(double) / sizeof(T));
   }
-  const int tid = threadIdx.x;
-  const int d = tid / S::TPD, tg = tid % S::TPD;
-  const int pair = blockIdx.x * C::ND + d;
+  // (d = 0: the pair's index in a vector register, as in pass C)
+  const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
+  const int pair = blockIdx.x + d;
   const int ra = 2 * pair, rb = ra + 1;
   const bool va = ra < n2, vb = rb < n2;
   const bool g = tg < S::NG;
@@ -259,12 +249,12 @@ __global__ __launch_bounds__(SdRows<L>::THR) void k_sd_rows_fwd(
       reg[m].im = sb * b;
     });
   }
-  sd_forward<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds + d * S::LEN);
+  sd_forward<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds);
   if (!va) return;
   const T s = (T)(0.5 * (sig ? *sig : 1.0));
   const int hp = (n2 + 1) >> 1;
   // spectrum = 2 sigma_b - 2i sigma_a; row b of an odd n2 holds the zeros loaded for it
-  static_for<16>([&](auto ee) {
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int c = S::slot(r, tau, e);
     if (c >= 0) {
@@ -276,8 +266,8 @@ __global__ __launch_bounds__(SdRows<L>::THR) void k_sd_rows_fwd(
 }
 
 // --------------------------------------------------------------------------
-// Pass B: slot-column pairs (2c, 2c+1) of Q -> (P1, P2) pairs, ND column pairs
-// per block, interleaved (column pair fastest in the thread index).
+// Pass B: slot-column pairs (2c, 2c+1) of Q -> (P1, P2) pairs, one column pair
+// per block.
 // --------------------------------------------------------------------------
 template <typename T, int L>
 __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(3))) void k_sd_cols(
@@ -286,12 +276,11 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     const cpx<T>* __restrict__ twS, int n1, int n2, T kx, T ky, T dpen, T halfK,
     const Members mb, const double* __restrict__ mk) {
   using S = Sd<L>;
-  constexpr int BC = SdCols<L>::BC;
-  constexpr int TWs = sd_tw<L, BC>();
+  constexpr int TWs = sd_tw<L, 1>();
   using Fs = typename S::Fs;
   using V2 = typename Vec2<T>::type;
-  __shared__ T lds[(SdCols<L>::CONC ? 2 : 1) * BC * S::LEN];
-  __shared__ T stash[BC * 16 * S::TPD];  // rho_b between the two inverse sweeps
+  __shared__ T lds[(SdCols<L>::CONC ? 2 : 1) * S::LEN];
+  __shared__ T stash[S::PS * S::TPD];  // rho_b between the two inverse sweeps
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     const size_t mt = mo * (sizeof(double) / sizeof(T));
@@ -305,11 +294,9 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
   constexpr bool CONC = SdCols<L>::CONC;
   const int tid = threadIdx.x;
   // set h = 1 (CONC only) takes the second inverse sweep
-  const int h = CONC ? tid / (BC * S::TPD) : 0;
-  const int tl = tid - h * (BC * S::TPD);
-  const int b = tl % BC, tg = tl / BC;
-  const int strip = xcd_remap(blockIdx.x, gridDim.x);
-  const int ca = 2 * (strip * BC + b), cb = ca + 1;
+  const int h = CONC ? tid / S::TPD : 0;
+  const int tg = tid - h * S::TPD;
+  const int ca = 2 * xcd_remap(blockIdx.x, gridDim.x), cb = ca + 1;
   const int ld = n1 + 1, hp = (n2 + 1) >> 1;
   const bool va = ca < ld;  // ld even: both columns or neither
   const bool f0 = h == 0;   // threads of the forward sweep
@@ -332,28 +319,28 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
       reg[m].im = sgn * q.y;
     });
   }
-  T* my = lds + h * (BC * S::LEN) + b;  // regions interleaved (stride BC); one per set
+  T* my = lds + h * S::LEN;  // one region per set
   {
     Roots<T, Fs> rs;  // (loaded per sweep: held across the kernel they cost occupancy)
     rs.load_fwd(tau, twS);
-    sd_forward<T, L, BC, TWs, false>(reg, g && f0, tg, r, tau, w1, rs, my, f0);
+    sd_forward<T, L, 1, TWs, false>(reg, g && f0, tg, r, tau, w1, rs, my, f0);
   }
   // spectrum = 2 rho_b - 2i rho_a; rho_b waits in LDS for the second column
   // (in registers it would cost a wavefront of occupancy)
   // The y eigenvalues stay in registers for the second column (a block of
   // 2.25 wavefronts is held to 3 per SIMD by its LDS anyway).
   const T* lamy = lamy_blk + r * S::LS;
-  T* rb = stash + tg * BC + b;
-  T ly[16];
-  static_for<16>([&](auto ee) {
+  T* rb = stash + tg;
+  T ly[S::PS];
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     ly[e] = ky * lamy[Fs::pos(Fs::NS - 1, tau, e)];
   });
   if (f0) {
-    static_for<16>([&](auto ee) {
+    static_for<S::PS>([&](auto ee) {
       constexpr int e = decltype(ee)::value;
       const T rho_a = (T)-0.5 * reg[e].im;
-      rb[e * S::TPD * BC] = (T)0.5 * reg[e].re;
+      rb[e * S::TPD] = (T)0.5 * reg[e].re;
       const T e1 = (T)1 - lxa - ly[e];
       const T e2 = e1 + dpen;
       const T q = halfK * rho_a / (e1 * e2);
@@ -366,11 +353,11 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     // the second set takes rho_b from the stash and runs its sweep beside the first
     __syncthreads();
     if (!f0) {
-      static_for<16>([&](auto ee) {
+      static_for<S::PS>([&](auto ee) {
         constexpr int e = decltype(ee)::value;
         const T e1 = (T)1 - lxb - ly[e];
         const T e2 = e1 + dpen;
-        const T q = halfK * rb[e * S::TPD * BC] / (e1 * e2);
+        const T q = halfK * rb[e * S::TPD] / (e1 * e2);
         reg[e].re = q * e1;
         reg[e].im = -q * e2;
       });
@@ -378,7 +365,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     {
       Roots<T, Fs> rs;
       rs.load_inv(tau, twS);
-      sd_inverse<T, L, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+      sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
     }
     if (g && va) {
       const int cw = f0 ? ca : cb;
@@ -396,7 +383,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+    sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
   }
   if (g && va) {
     static_for<16>([&](auto mm) {
@@ -408,18 +395,18 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
             neg ? V2{-reg[m].re, -reg[m].im} : V2{reg[m].re, reg[m].im};
     });
   }
-  static_for<16>([&](auto ee) {
+  static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const T e1 = (T)1 - lxb - ly[e];
     const T e2 = e1 + dpen;
-    const T q = halfK * rb[e * S::TPD * BC] / (e1 * e2);
+    const T q = halfK * rb[e * S::TPD] / (e1 * e2);
     reg[e].re = q * e1;
     reg[e].im = -q * e2;
   });
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+    sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
   }
   if (g && va) {
     static_for<16>([&](auto mm) {
@@ -434,25 +421,25 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
 }
 
 // --------------------------------------------------------------------------
-// Pass C: one row per transform, ND rows per block; the inverse sweep of
+// Pass C: one row per transform and block; the inverse sweep of
 // P2/2 - i P1/2 gives (P1 S_x) + i (P2 S_x), combined by the mask into z.
 // --------------------------------------------------------------------------
 template <typename T, int L>
-__global__ __launch_bounds__(SdRows<L>::THR) void k_sd_rows_inv(
+__global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_inv(
     const T* __restrict__ P, const uint8_t* __restrict__ mask, double* __restrict__ z,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS,
     const int32_t* __restrict__ msl, int n1, int n2, const Members mb) {
   using S = Sd<L>;
-  using C = SdRows<L>;
-  __shared__ T lds[C::ND * S::LEN];
+  __shared__ T lds[S::LEN];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     P += mo * (sizeof(double) / sizeof(T));
     z += mo;
   }
-  const int tid = threadIdx.x;
-  const int d = tid / S::TPD, tg = tid % S::TPD;
-  const int row = blockIdx.x * C::ND + d;
+  // (d = 0: the row's index in a vector register; with a scalar one the compiler
+  // keeps fewer of the spectrum's loads in flight, 27.4 -> 28.1 us at 2047^2)
+  const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
+  const int row = blockIdx.x + d;
   const bool vr = row < n2;
   const bool g = tg < S::NG;
   const int r = tg / S::TS, tau = tg % S::TS;
@@ -461,7 +448,7 @@ __global__ __launch_bounds__(SdRows<L>::THR) void k_sd_rows_inv(
   Roots<T, typename S::Fs> rs;
   rs.load_inv(tau, twS);
   sd_load_spectrum<T, L>(reg, P, row, vr, r, tau, n2, msl);
-  sd_inverse<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds + d * S::LEN);
+  sd_inverse<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds);
   if (g) sd_store_z<T, L, double>(reg, tg, row, vr, n1, mask, z, nullptr);
 }
 
