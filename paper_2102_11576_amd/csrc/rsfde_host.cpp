@@ -2000,12 +2000,13 @@ struct rsfde_batch_s {
          o_Q = 0, o_P1 = 0;
   rsfde::HostStatus* hs = nullptr;      // pinned [B]
   rsfde::HostStatus* hs_dev = nullptr;
-  hipEvent_t ev = nullptr;
+  hipEvent_t ev[2] = {nullptr, nullptr};
   std::vector<double> kx, ky;
   ~rsfde_batch_s() {
     if (region) (void)hipFree(region);
     if (hs) (void)hipHostFree(hs);
-    if (ev) (void)hipEventDestroy(ev);
+    for (auto& e : ev)
+      if (e) (void)hipEventDestroy(e);
     if (plan) rsfde_destroy(plan);
   }
 };
@@ -2121,28 +2122,41 @@ int batch_solve(rsfde_batch_s* Bt, const rsfde_solver_opts* o, rsfde_stats* st, 
     }
     active = iterating;
     if (active.empty()) break;
-    std::vector<int> jc(B, 0);
-    for (int j = 0; j < o->restart && !iterating.empty(); ++j) {
-      const Members mi = members_of(Bt, iterating);
-      double* vj = V + (size_t)j * ld;
-      double* zj = Zb + (size_t)j * ld;
-      double* vnext = V + (size_t)(j + 1) * ld;
-      if (int rc = batch_precond_any(Bt, o->precision, vj, &ks->vscale[j], zj, w, mi, s)) return rc;
-      CK(launch_orth_dots(V, ld, j + 1, w, N, rw, ks, j, s, mi));
-      CK(launch_orth_update(V, ld, j + 1, w, vnext, N, rw, ks, j, reorth, Bt->hs_dev, s, mi));
-      CK(hipEventRecord(Bt->ev, s));
-      CK(hipEventSynchronize(Bt->ev));
-      std::vector<int> still;
-      for (int m : iterating) {
-        ++total[m];
-        const bool bad = (hs[m].flags & kFlagNonFinite) != 0;
-        if (bad || hs[m].est[j] <= thresh[m] || j + 1 == o->restart || total[m] >= o->max_iters)
-          jc[m] = j + 1;
-        else
-          still.push_back(m);
+    // The inner steps of the cycle, the host one step behind the device as in the
+    // single-plan form: step j is launched before the estimates of step j - 1 are
+    // read, so a member that had converged then runs one step more, whose column
+    // and vectors nothing uses.  A member stops at its limit in any case.
+    std::vector<int> jc(B, 0), launched;  // launched: members of step j - 1, not yet examined
+    auto limit = [&](int m) { return std::min(o->restart, o->max_iters - total[m]); };
+    for (int j = 0;; ++j) {
+      std::vector<int> now;
+      for (int m : iterating)
+        if (limit(m) > j) now.push_back(m);
+      if (!now.empty()) {
+        const Members mi = members_of(Bt, now);
+        double* vj = V + (size_t)j * ld;
+        double* zj = Zb + (size_t)j * ld;
+        double* vnext = V + (size_t)(j + 1) * ld;
+        if (int rc = batch_precond_any(Bt, o->precision, vj, &ks->vscale[j], zj, w, mi, s)) return rc;
+        CK(launch_orth_dots(V, ld, j + 1, w, N, rw, ks, j, s, mi));
+        CK(launch_orth_update(V, ld, j + 1, w, vnext, N, rw, ks, j, reorth, Bt->hs_dev, s, mi));
+        CK(hipEventRecord(Bt->ev[j & 1], s));
       }
-      iterating = still;
+      if (j > 0) {
+        CK(hipEventSynchronize(Bt->ev[(j - 1) & 1]));
+        for (int m : launched) {
+          const bool bad = (hs[m].flags & kFlagNonFinite) != 0;
+          if (bad || hs[m].est[j - 1] <= thresh[m] || limit(m) == j) {
+            jc[m] = j;
+            iterating.erase(std::find(iterating.begin(), iterating.end(), m));
+            now.erase(std::remove(now.begin(), now.end(), m), now.end());
+          }
+        }
+      }
+      launched = now;
+      if (launched.empty()) break;
     }
+    for (int m : active) total[m] += jc[m];
     std::vector<int32_t> jcs;
     int jmax = 0;
     for (int m : active) {
@@ -2239,7 +2253,8 @@ int rsfde_batch_setup(rsfde_batch* out, const rsfde_grid* grid, double alpha1, d
   }
   std::memset((void*)Bt->hs, 0, (size_t)count * sizeof(HostStatus));
   if (hipHostGetDevicePointer((void**)&Bt->hs_dev, Bt->hs, 0) != hipSuccess ||
-      hipEventCreateWithFlags(&Bt->ev, hipEventDisableTiming) != hipSuccess) {
+      hipEventCreateWithFlags(&Bt->ev[0], hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&Bt->ev[1], hipEventDisableTiming) != hipSuccess) {
     delete Bt;
     return RSFDE_EHIP;
   }
