@@ -6,10 +6,21 @@
 
 namespace rsfde {
 
+template <typename T>
+struct Vec2;
+template <>
+struct Vec2<double> {
+  using type = double2;
+};
+template <>
+struct Vec2<float> {
+  using type = float2;
+};
+
 // LDS slot of sequence position p: one pad word every 16 positions breaks the
 // power-of-two strides of the last stage across banks.
 __device__ __forceinline__ int lds_pad(int p) { return p + (p >> 4); }
-constexpr int lds_len(int L) { return L + (L >> 4) + 1; }
+constexpr int lds_len(int L, bool cx = false) { return (cx ? 2 : 1) * (L + (L >> 4) + 1); }
 
 // LDS slots of a stage layout.  For most stages the slot of register e is
 // slot(tau, 0) + delta(e) with delta independent of the thread (checked here
@@ -67,6 +78,26 @@ __device__ __forceinline__ void lds_get(cpx<T>* reg, int tau, const T* lds, bool
   }
 }
 
+// Both parts at once: slot s of the region is one complex value.
+template <typename T, class F, int t, int ST, bool PUT>
+__device__ __forceinline__ void lds_move(cpx<T>* reg, int tau, cpx<T>* lds) {
+  using LL = LdsLayout<F, t>;
+  cpx<T>* b = lds + (LL::linear ? lds_pad(F::pos(t, tau, 0)) * ST : 0);
+  static_for<F::PP>([&](auto ee) {
+    constexpr int e = decltype(ee)::value;
+    cpx<T>* q;
+    if constexpr (LL::linear) q = b + LL::delta(e) * ST;
+    else q = b + lds_pad(F::pos(t, tau, e)) * ST;
+    using V2 = typename Vec2<T>::type;
+    if constexpr (PUT) {
+      *(V2*)q = V2{reg[e].re, reg[e].im};
+    } else {
+      const V2 v = *(const V2*)q;
+      reg[e] = {v.x, v.y};
+    }
+  });
+}
+
 // Thread that holds sequence position p in the layout of stage t (inverse of
 // F::pos: p = (beta / s) bl + beta % s + m s, beta = tau + u TPF).
 template <class F>
@@ -95,7 +126,11 @@ constexpr bool exchange_in_wave() {
 // wavefront's LDS operations complete in order, and every wavefront only
 // rewrites the positions it reads (the fences keep the compiler from
 // reordering the LDS accesses).
-template <typename T, class F, int TF, int TT, int ST = 1, int TW = 0>
+//
+// CX: the region holds L complex values instead (lds_len(L, true) scalars), and
+// both parts go through it at once: half the waits and barriers for twice the
+// LDS.
+template <typename T, class F, int TF, int TT, int ST = 1, int TW = 0, bool CX = false>
 __device__ __forceinline__ void lds_exchange(cpx<T>* reg, int tau, T* lds, bool act = true) {
   // (a transform whose TPF * ST threads are one aligned group inside a
   // wavefront exchanges within it at every stage)
@@ -111,6 +146,14 @@ __device__ __forceinline__ void lds_exchange(cpx<T>* reg, int tau, T* lds, bool 
   };
   // act = false: a thread with no transform of its own still takes part in
   // every block barrier (the block's other transforms need them).
+  if constexpr (CX) {
+    cpx<T>* c = reinterpret_cast<cpx<T>*>(lds);
+    if (act) lds_move<T, F, TF, ST, true>(reg, tau, c);
+    sync();
+    if (act) lds_move<T, F, TT, ST, false>(reg, tau, c);
+    sync();
+    return;
+  }
   if (act) lds_put<T, F, TF, ST>(reg, tau, lds, false);
   sync();
   if (act) lds_get<T, F, TT, ST>(reg, tau, lds, false);
@@ -154,42 +197,42 @@ struct Roots {
 
 // Forward DIF sweep: natural order (stage-0 positions) in, digit-reversed
 // spectrum (last-stage positions) out.  rt: the roots (Roots::load_fwd).
-template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST>
+template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST, bool CX = false>
 __device__ __forceinline__ void fft_forward_r(cpx<T>* reg, int tau, const Roots<T, F>& rt,
                                               T* lds, bool act = true) {
   static_for<F::NS>([&](auto tt) {
     constexpr int t = decltype(tt)::value;
     if (act) F::template dif_stage_w<T, t>(reg, rt.at(t));
-    if constexpr (t < F::NS - 1) lds_exchange<T, F, t, t + 1, ST, TW>(reg, tau, lds, act);
+    if constexpr (t < F::NS - 1) lds_exchange<T, F, t, t + 1, ST, TW, CX>(reg, tau, lds, act);
   });
   if constexpr (MAT) materialize<T, F::PP>(reg);
 }
-template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST>
+template <typename T, class F, bool MAT = true, int ST = 1, bool CX = false, int TW = 64 / ST>
 __device__ __forceinline__ void fft_forward(cpx<T>* reg, int tau, const cpx<T>* __restrict__ tw,
                                             T* lds, bool act = true) {
   Roots<T, F> rt;
   rt.load_fwd(tau, tw);
-  fft_forward_r<T, F, MAT, ST, TW>(reg, tau, rt, lds, act);
+  fft_forward_r<T, F, MAT, ST, TW, CX>(reg, tau, rt, lds, act);
 }
 
 // Inverse DIT sweep: digit-reversed spectrum in, L * signal in natural order
 // out.  rt: the roots (Roots::load_inv).
-template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST>
+template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST, bool CX = false>
 __device__ __forceinline__ void fft_inverse_r(cpx<T>* reg, int tau, const Roots<T, F>& rt,
                                               T* lds, bool act = true) {
   static_for<F::NS>([&](auto tt) {
     constexpr int t = F::NS - 1 - decltype(tt)::value;
     if (act) F::template dit_stage_w<T, t>(reg, rt.at(t));
-    if constexpr (t > 0) lds_exchange<T, F, t, t - 1, ST, TW>(reg, tau, lds, act);
+    if constexpr (t > 0) lds_exchange<T, F, t, t - 1, ST, TW, CX>(reg, tau, lds, act);
   });
   if constexpr (MAT) materialize<T, F::PP>(reg);
 }
-template <typename T, class F, bool MAT = true, int ST = 1, int TW = 64 / ST>
+template <typename T, class F, bool MAT = true, int ST = 1, bool CX = false, int TW = 64 / ST>
 __device__ __forceinline__ void fft_inverse(cpx<T>* reg, int tau, const cpx<T>* __restrict__ tw,
                                             T* lds, bool act = true) {
   Roots<T, F> rt;
   rt.load_inv(tau, tw);
-  fft_inverse_r<T, F, MAT, ST, TW>(reg, tau, rt, lds, act);
+  fft_inverse_r<T, F, MAT, ST, TW, CX>(reg, tau, rt, lds, act);
 }
 
 // Strip-tiled layout of a [rows][cols] array of intermediates: tiles of
@@ -201,17 +244,6 @@ __device__ __forceinline__ void fft_inverse(cpx<T>* reg, int tau, const cpx<T>* 
 __device__ __forceinline__ size_t tile_index(int r, int c, int hp) {
   return ((size_t)(c >> 2) * hp + (r >> 1)) * 8 + (r & 1) * 4 + (c & 3);
 }
-template <typename T>
-struct Vec2;
-template <>
-struct Vec2<double> {
-  using type = double2;
-};
-template <>
-struct Vec2<float> {
-  using type = float2;
-};
-
 // Two consecutive elements of a caller's array, at any element's address: one
 // load or store of twice the width, aligned like one element.
 template <typename T>

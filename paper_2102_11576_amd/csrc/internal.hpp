@@ -45,6 +45,15 @@ struct Members {
 // mv_rows at 2047^2 (L = 4096) 59.6 -> 68.6 us, at 4095^2 (L = 8192) 322 -> 503.
 constexpr int fft_pts(int L) { return L <= 4 ? L : (L <= 256 ? 4 : (L <= 1024 ? 8 : 16)); }
 
+// Lengths whose exchanges may move both parts at once (lds_exchange, CX): at 4 and
+// 8 points per thread twice the LDS still leaves 16 wavefronts per CU.  Used where
+// registers or the grid hold a kernel to that anyway: pass B of 3-D plans (169 ->
+// 148 us at 255^3) and their raw sine transforms (91 -> 88), the convolution of the
+// fused pass, the chirp passes (200^2 22.5 -> 21.8 us) and the product's column
+// pass on small views.  The row passes lose wavefronts by it (255^3: pass A 66 ->
+// 77 us, pass C 101 -> 121).
+constexpr bool fft_cx(int L) { return L <= 1024; }
+
 // Transforms per block of the row passes: one wavefront's worth, or one
 // transform where that takes more than a wavefront.  A transform inside one
 // wavefront needs no block barrier, and small grids spread over more CUs: with

@@ -27,6 +27,10 @@ struct MvCfg {
     return true;
   }
   static constexpr int TPF = F::TPF;
+  // Column passes of small views exchange both parts at once (their LDS does not
+  // limit them): 511^2 15.2 -> 14.1 us a product.  Larger views and the row passes
+  // keep the smaller region (row pass at 255^3 93 -> 96 us).
+  static constexpr bool CXS = fft_cx(L);
   static constexpr int BR = row_ffts(TPF);  // FFTs per row block
   static constexpr int THR_R = BR * TPF;
   // column pairs per column block: two at L = 1024 and 2048 (two-dimensional
@@ -140,14 +144,14 @@ __global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu
 // compile-time mode keeps the epilogue's loads free of per-element branches,
 // which measured 10 % faster at n = 2047.
 // --------------------------------------------------------------------------
-template <int L, int BC, int MODE, bool TT, typename ZT = double>
+template <int L, int BC, bool CX, int MODE, bool TT, typename ZT = double>
 __global__ __launch_bounds__(MvCfg<L>::TPF* BC) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_cols(
     const ZT* __restrict__ z, const double* __restrict__ t, double* __restrict__ out,
     const double* __restrict__ sym, const cpx<double>* __restrict__ tw, int n1, int n2,
     double coef, size_t bstride, const Members mb, const double* __restrict__ mk) {
   using C = MvCfg<L>;
   using F = typename C::F;
-  __shared__ double lds[BC * lds_len(L)];
+  __shared__ __align__(16) double lds[BC * lds_len(L, CX)];
   {  // slice (grid dimension y) and member of a batched launch (dimension z)
     const size_t mo = mb.off(blockIdx.z);
     if (mk) coef = -mk[mo];
@@ -196,15 +200,15 @@ __global__ __launch_bounds__(MvCfg<L>::TPF* BC) __attribute__((amdgpu_waves_per_
   };
   if (n1 >= 2) load(std::true_type{});
   else load(std::false_type{});
-  double* my = lds + b;  // regions interleaved (stride BC)
-  fft_forward<double, F, true, BC>(reg, tau, tw, my);
+  double* my = lds + b * (CX ? 2 : 1);  // regions interleaved (stride BC)
+  fft_forward<double, F, true, BC, CX>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const double s = sym[F::pos(F::NS - 1, tau, e)] * coef;
     reg[e].re *= s;
     reg[e].im *= s;
   });
-  fft_inverse<double, F, true, BC>(reg, tau, tw, my);
+  fft_inverse<double, F, true, BC, CX>(reg, tau, tw, my);
   if constexpr (MODE == 0 && TT) {
     const int hp = (n2 + 1) >> 1;
     const int cca = va ? ca : 0;
@@ -291,7 +295,7 @@ static hipError_t mv_rows_impl(const double* z, const uint8_t* mask, double* out
   return hipGetLastError();
 }
 
-template <int L, int BC>
+template <int L, int BC, bool CX>
 static hipError_t mv_cols_bc(const void* zv, const double* t, double* out, const double* sym,
                              const cpx<double>* twc, int n1, int n2, double coef, int mode,
                              hipStream_t s, int batch, size_t bstride, bool tiled,
@@ -300,16 +304,16 @@ static hipError_t mv_cols_bc(const void* zv, const double* t, double* out, const
   const int pairs = (n1 + 1) / 2;
   const dim3 grid((pairs + BC - 1) / BC, batch, mb.n), thr(BC * MvCfg<L>::TPF);
   if (z32)
-    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, true, float>), grid, thr, 0, s, (const float*)zv, t,
+    hipLaunchKernelGGL((k_mv_cols<L, BC, CX, 0, true, float>), grid, thr, 0, s, (const float*)zv, t,
                        out, sym, twc, n1, n2, coef, bstride, mb, mk);
   else if (mode != 0)
-    hipLaunchKernelGGL((k_mv_cols<L, BC, 1, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+    hipLaunchKernelGGL((k_mv_cols<L, BC, CX, 1, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
                        coef, bstride, mb, mk);
   else if (tiled)
-    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, true>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+    hipLaunchKernelGGL((k_mv_cols<L, BC, CX, 0, true>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
                        coef, bstride, mb, mk);
   else
-    hipLaunchKernelGGL((k_mv_cols<L, BC, 0, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
+    hipLaunchKernelGGL((k_mv_cols<L, BC, CX, 0, false>), grid, thr, 0, s, z, t, out, sym, twc, n1, n2,
                        coef, bstride, mb, mk);
   return hipGetLastError();
 }
@@ -325,13 +329,13 @@ static hipError_t mv_cols_impl(const void* z, const double* t, double* out, cons
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
   if (z32 && (mode != 0 || !tiled)) return hipErrorInvalidValue;
   const cpx<double>* twc = (const cpx<double>*)tw;
-  if constexpr (C::BCS < C::BCL) {
+  if constexpr (C::BCS < C::BCL || C::CXS) {
     const long blocks = (long)((n1 + 1) / 2 + C::BCL - 1) / C::BCL * batch * mb.n;
     if (blocks < kSmallGridBlocks)
-      return mv_cols_bc<L, C::BCS>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride,
+      return mv_cols_bc<L, C::BCS, C::CXS>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride,
                                    tiled, mb, mk, z32);
   }
-  return mv_cols_bc<L, C::BCL>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride, tiled,
+  return mv_cols_bc<L, C::BCL, false>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride, tiled,
                                mb, mk, z32);
 }
 

@@ -34,6 +34,8 @@ template <int L>
 struct CdCfg {
   using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
+  static constexpr bool CX = fft_cx(L);
+  static constexpr int LEN = lds_len(L, CX);  // LDS scalars of one transform
   static constexpr int BR = row_ffts(TPF);  // lines per row block
   static constexpr int BCL = (256 / TPF) > 16 ? 16 : ((256 / TPF) > 0 ? (256 / TPF) : 1);
   static constexpr int BCS = L <= 512 && col_ffts_small(TPF) < BCL ? col_ffts_small(TPF) : BCL;
@@ -46,7 +48,7 @@ struct CdCfg {
 
 // In: reg[e].re = x at sequence position pos(0, tau, e) (zero at positions >= n).
 // Out: reg[e].re = (S x) at the same position (unspecified at positions >= n).
-template <typename T, class F, int ST = 1>
+template <typename T, class F, bool CX, int ST = 1>
 __device__ __forceinline__ void chirp_dst(cpx<T>* reg, int tau, const cpx<T>* __restrict__ chn,
                                           const cpx<T>* __restrict__ khat,
                                           const cpx<T>* __restrict__ tw, T* lds, int n) {
@@ -58,12 +60,12 @@ __device__ __forceinline__ void chirp_dst(cpx<T>* reg, int tau, const cpx<T>* __
     reg[e].re = x * c.re;
     reg[e].im = x * c.im;
   });
-  fft_forward<T, F, true, ST>(reg, tau, tw, lds);
+  fft_forward<T, F, true, ST, CX>(reg, tau, tw, lds);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     reg[e] = cmul(reg[e], khat[F::pos(F::NS - 1, tau, e)]);
   });
-  fft_inverse<T, F, true, ST>(reg, tau, tw, lds);
+  fft_inverse<T, F, true, ST, CX>(reg, tau, tw, lds);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
     const cpx<T>* __restrict__ tw, int n1, int n2) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BR * lds_len(L)];
+  __shared__ __align__(16) T lds[C::BR * C::LEN];
   const int b = threadIdx.x / F::TPF, tau = threadIdx.x % F::TPF;
   const int r = blockIdx.x * C::BR + b;
   const bool vr = r < n2;
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
     reg[e].re = (vr && p < n1) ? (T)(sc * v[(size_t)r * n1 + p]) : T(0);
     reg[e].im = T(0);
   });
-  chirp_dst<T, F>(reg, tau, chn, khat, tw, lds + b * lds_len(L), n1);
+  chirp_dst<T, F, C::CX>(reg, tau, chn, khat, tw, lds + b * C::LEN, n1);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -111,11 +113,11 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     const cpx<T>* __restrict__ tw, int n1, int n2, double kx, double ky, double dpen) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[BC * lds_len(L)];
+  __shared__ __align__(16) T lds[BC * C::LEN];
   const int b = threadIdx.x % BC, tau = threadIdx.x / BC;
   const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < n1;
-  T* my = lds + b;  // regions interleaved (stride BC)
+  T* my = lds + b * (C::CX ? 2 : 1);  // regions interleaved (stride BC)
   const int hp = (n2 + 1) >> 1;
   cpx<T> reg[F::PP];
   T w[F::PP];
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     asm volatile("" : "+v"(th));
     const int zo = opaque_zero();
     const double* ly = lamy + zo;
-    chirp_dst<T, F, BC>(reg, th, chn + zo, khat + zo, tw + zo, my, n2);
+    chirp_dst<T, F, C::CX, BC>(reg, th, chn + zo, khat + zo, tw + zo, my, n2);
     static_for<F::PP>([&](auto ee) {
       constexpr int e = decltype(ee)::value;
       const int p = F::pos(0, th, e);
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
     const cpx<T>* __restrict__ tw, int n1, int n2) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[C::BR * lds_len(L)];
+  __shared__ __align__(16) T lds[C::BR * C::LEN];
   const int b = threadIdx.x / F::TPF, tau = threadIdx.x % F::TPF;
   const int u = blockIdx.x * C::BR + b;
   const int r = u >> 1, k = u & 1;
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
     reg[e].re = (vr && p < n1) ? src[TL ? tile_index(r, p, (n2 + 1) >> 1) : (size_t)r * n1 + p] : T(0);
     reg[e].im = T(0);
   });
-  chirp_dst<T, F>(reg, tau, chn, khat, tw, lds + b * lds_len(L), n1);
+  chirp_dst<T, F, C::CX>(reg, tau, chn, khat, tw, lds + b * C::LEN, n1);
   const uint8_t want = k ? 0 : 1;
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
@@ -196,14 +198,14 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_dst_cols(
     const cpx<T>* __restrict__ tw, int ncol, int rows, size_t bstride) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[BC * lds_len(L)];
+  __shared__ __align__(16) T lds[BC * C::LEN];
   const size_t off = (size_t)blockIdx.y * bstride;
   const T* in = (blockIdx.z ? inB : inA) + off;
   T* out = (blockIdx.z ? outB : outA) + off;
   const int b = threadIdx.x % BC, tau = threadIdx.x / BC;
   const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < ncol;
-  T* my = lds + b;  // regions interleaved (stride BC)
+  T* my = lds + b * (C::CX ? 2 : 1);  // regions interleaved (stride BC)
   cpx<T> reg[F::PP];
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_dst_cols(
     reg[e].re = (vc && p < rows) ? in[(size_t)p * ncol + c] : T(0);
     reg[e].im = T(0);
   });
-  chirp_dst<T, F, BC>(reg, tau, chn, khat, tw, my, rows);
+  chirp_dst<T, F, C::CX, BC>(reg, tau, chn, khat, tw, my, rows);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);

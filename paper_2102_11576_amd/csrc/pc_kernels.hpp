@@ -42,6 +42,8 @@ template <int L>
 struct PcColCfg {
   using F = Fft<L, fft_pts(L)>;
   static constexpr int TPF = F::TPF;
+  static constexpr bool CX = fft_cx(L);
+  static constexpr int LEN = lds_len(L, CX);  // LDS scalars of one transform
   static constexpr int BCL = col_ffts_large(TPF);
   static constexpr int BCS = L <= 512 ? col_ffts_small(TPF) : BCL;
 };
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     const double* __restrict__ mk) {
   using C = PcColCfg<L>;
   using F = typename C::F;
-  __shared__ T lds[BC * lds_len(L)];
+  __shared__ __align__(16) T lds[BC * C::LEN];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     const size_t mt = mo * (sizeof(double) / sizeof(T));
@@ -185,9 +187,9 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     reg[e].re = sgn * q.x;
     reg[e].im = sgn * q.y;
   });
-  T* my = lds + b;  // regions interleaved (stride BC)
+  T* my = lds + b * (C::CX ? 2 : 1);  // regions interleaved (stride BC)
   // (no register materialisation between the sweeps here: it measured slower)
-  fft_forward<T, F, false, BC>(reg, tau, tw, my);
+  fft_forward<T, F, false, BC, C::CX>(reg, tau, tw, my);
   // spectrum = 2 rho_b - 2i rho_a; keep rho_b for the second column
   const T lxa = va ? kx * lamx_slot[ca] : (T)0;
   const T lxb = vb ? kx * lamx_slot[cb] : (T)0;
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     reg[e].re = r * e1;
     reg[e].im = -r * e2;
   });
-  fft_inverse<T, F, false, BC>(reg, tau, tw, my);
+  fft_inverse<T, F, false, BC, C::CX>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     reg[e].re = r * e1;
     reg[e].im = -r * e2;
   });
-  fft_inverse<T, F, false, BC>(reg, tau, tw2, my);
+  fft_inverse<T, F, false, BC, C::CX>(reg, tau, tw2, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int p = F::pos(0, tau, e);
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
   using C = PcColCfg<L>;
   using F = typename C::F;
   using V2 = typename Vec2<T>::type;
-  __shared__ T lds[BC * lds_len(L)];
+  __shared__ __align__(16) T lds[BC * C::LEN];
   const int tid = threadIdx.x;
   const int b = tid % BC, tau = tid / BC;
   const int ld = n1 + 1;
@@ -274,8 +276,8 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
     reg[e].re = sgn * q.x;
     reg[e].im = sgn * q.y;
   });
-  T* my = lds + b;  // regions interleaved (stride BC)
-  fft_forward<T, F, false, BC>(reg, tau, tw, my);
+  T* my = lds + b * (C::CX ? 2 : 1);  // regions interleaved (stride BC)
+  fft_forward<T, F, false, BC, C::CX>(reg, tau, tw, my);
   // spectrum = 2 rho_b - 2i rho_a; kept: K rho / (2 E1 E2) of both columns
   const T lxa = kx * lamx_slot[cc], lxb = kx * lamx_slot[cc + 1];
   cpx<T> rho[F::PP];
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
       reg[e].re = rho[e].im * ((T)1 - lxb - ly + add);
       reg[e].im = -rho[e].re * ((T)1 - lxa - ly + add);
     });
-    fft_inverse<T, F, false, BC>(reg, th, tw + z0, my);
+    fft_inverse<T, F, false, BC, C::CX>(reg, th, tw + z0, my);
     T* out = f == 0 ? P1 : P2;
     static_for<F::PP>([&](auto ee) {
       constexpr int e = decltype(ee)::value;
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
   using C = PcColCfg<L>;
   using F = typename C::F;
   using V2 = typename Vec2<T>::type;
-  __shared__ T lds[BC * lds_len(L)];
+  __shared__ __align__(16) T lds[BC * C::LEN];
   const size_t off = (size_t)blockIdx.y * bstride;
   const T* in = (blockIdx.z ? inB : inA) + off;
   T* out = (blockIdx.z ? outB : outA) + off;
@@ -349,8 +351,8 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
     reg[e].re = sgn * q.x;
     reg[e].im = sgn * q.y;
   });
-  T* my = lds + b;  // regions interleaved (stride BC)
-  fft_forward<T, F, false, BC>(reg, tau, tw, my);
+  T* my = lds + b * (C::CX ? 2 : 1);  // regions interleaved (stride BC)
+  fft_forward<T, F, false, BC, C::CX>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const int f = fft_freq(L, fft_pts(L), F::pos(F::NS - 1, tau, e));

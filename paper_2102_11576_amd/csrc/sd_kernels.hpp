@@ -476,6 +476,7 @@ struct SdMvCfg {
   // concurrent form to three waves per SIMD by their LDS, so its occupancy
   // hint asks for three; the smaller lengths compile the same either way.)
   static constexpr bool CONC = L <= 2048;
+  static constexpr bool CX = fft_cx(L);  // the convolution's exchanges
   static constexpr int TD = CONC ? 2 * S::TPD : S::TPD;
   static constexpr int THR = TD > F::TPF ? TD : F::TPF;
   // LDS in doubles.  Sequential: row a's staged z [0, L/2), then the transform
@@ -486,7 +487,7 @@ struct SdMvCfg {
   static constexpr int lds_doubles() {
     constexpr int a = CONC ? L + (2 * S::LEN * (int)sizeof(T) + 7) / 8
                            : L / 2 + (S::LEN * (int)sizeof(T) + 7) / 8;
-    constexpr int b = lds_len(L);
+    constexpr int b = lds_len(L, CX);
     return a > b ? a : b;
   }
   // register e of the convolution's first (last) stage is at or above L/2 for every thread
@@ -509,7 +510,7 @@ void k_sd_rows_inv_mv(
   using M = SdMvCfg<L>;
   using F = typename M::F;
   constexpr int TWs = sd_tw<L, 1>();
-  __shared__ double lds[M::template lds_doubles<T>()];
+  __shared__ __align__(16) double lds[M::template lds_doubles<T>()];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     P += mo * (sizeof(double) / sizeof(T));
@@ -585,7 +586,7 @@ void k_sd_rows_inv_mv(
     }
   });
   __syncthreads();  // the convolution's region overlays the staged z
-  fft_forward_r<double, F>(reg, tc, rcf, lds, act);
+  fft_forward_r<double, F, true, 1, 64, M::CX>(reg, tc, rcf, lds, act);
   if (act) {
     static_for<F::PP>([&](auto ee) {
       constexpr int e = decltype(ee)::value;
@@ -594,7 +595,7 @@ void k_sd_rows_inv_mv(
       reg[e].im *= sc;
     });
   }
-  fft_inverse_r<double, F>(reg, tc, rci, lds, act);
+  fft_inverse_r<double, F, true, 1, 64, M::CX>(reg, tc, rci, lds, act);
   if (!act) return;
   // Epilogue in groups of G registers: the group's loads (clamped addresses)
   // all in flight at once, then its stores.
