@@ -88,13 +88,8 @@ __device__ __forceinline__ void lds_move(cpx<T>* reg, int tau, cpx<T>* lds) {
     cpx<T>* q;
     if constexpr (LL::linear) q = b + LL::delta(e) * ST;
     else q = b + lds_pad(F::pos(t, tau, e)) * ST;
-    using V2 = typename Vec2<T>::type;
-    if constexpr (PUT) {
-      *(V2*)q = V2{reg[e].re, reg[e].im};
-    } else {
-      const V2 v = *(const V2*)q;
-      reg[e] = {v.x, v.y};
-    }
+    if constexpr (PUT) *q = reg[e];
+    else reg[e] = *q;
   });
 }
 

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(MvCfg<L>::TPF* BC) __attribute__((amdgpu_waves_per_
     double coef, size_t bstride, const Members mb, const double* __restrict__ mk) {
   using C = MvCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) double lds[BC * lds_len(L, CX)];
+  __shared__ double lds[BC * lds_len(L, CX)];
   {  // slice (grid dimension y) and member of a batched launch (dimension z)
     const size_t mo = mb.off(blockIdx.z);
     if (mk) coef = -mk[mo];

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_fwd(
     const cpx<T>* __restrict__ tw, int n1, int n2) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) T lds[C::BR * C::LEN];
+  __shared__ T lds[C::BR * C::LEN];
   const int b = threadIdx.x / F::TPF, tau = threadIdx.x % F::TPF;
   const int r = blockIdx.x * C::BR + b;
   const bool vr = r < n2;
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     const cpx<T>* __restrict__ tw, int n1, int n2, double kx, double ky, double dpen) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) T lds[BC * C::LEN];
+  __shared__ T lds[BC * C::LEN];
   const int b = threadIdx.x % BC, tau = threadIdx.x / BC;
   const int c = xcd_remap(blockIdx.x, gridDim.x) * BC + b;
   const bool vc = c < n1;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(CdCfg<L>::THR_R) void k_cd_rows_inv(
     const cpx<T>* __restrict__ tw, int n1, int n2) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) T lds[C::BR * C::LEN];
+  __shared__ T lds[C::BR * C::LEN];
   const int b = threadIdx.x / F::TPF, tau = threadIdx.x % F::TPF;
   const int u = blockIdx.x * C::BR + b;
   const int r = u >> 1, k = u & 1;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_dst_cols(
     const cpx<T>* __restrict__ tw, int ncol, int rows, size_t bstride) {
   using C = CdCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) T lds[BC * C::LEN];
+  __shared__ T lds[BC * C::LEN];
   const size_t off = (size_t)blockIdx.y * bstride;
   const T* in = (blockIdx.z ? inB : inA) + off;
   T* out = (blockIdx.z ? outB : outA) + off;

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
     const double* __restrict__ mk) {
   using C = PcColCfg<L>;
   using F = typename C::F;
-  __shared__ __align__(16) T lds[BC * C::LEN];
+  __shared__ T lds[BC * C::LEN];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     const size_t mt = mo * (sizeof(double) / sizeof(T));
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
   using C = PcColCfg<L>;
   using F = typename C::F;
   using V2 = typename Vec2<T>::type;
-  __shared__ __align__(16) T lds[BC * C::LEN];
+  __shared__ T lds[BC * C::LEN];
   const int tid = threadIdx.x;
   const int b = tid % BC, tau = tid / BC;
   const int ld = n1 + 1;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_dst_cols(
   using C = PcColCfg<L>;
   using F = typename C::F;
   using V2 = typename Vec2<T>::type;
-  __shared__ __align__(16) T lds[BC * C::LEN];
+  __shared__ T lds[BC * C::LEN];
   const size_t off = (size_t)blockIdx.y * bstride;
   const T* in = (blockIdx.z ? inB : inA) + off;
   T* out = (blockIdx.z ? outB : outA) + off;

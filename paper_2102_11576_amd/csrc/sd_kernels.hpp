@@ -68,6 +68,31 @@ __device__ __forceinline__ void sd_forward(cpx<T>* v, bool g, int p, int r, int 
   const bool mir = g && p != 0 && p != LS / 2;
   const int pd = lds_pad(p), pm = lds_pad(LS - p);
   constexpr int BL = LS + LS / 16;  // padded length of one block
+  if constexpr (S::CX) {
+    // Both parts at once.  A sub-FFT's threads read their own block only and are
+    // in one wavefront, so no barrier separates the reads from its exchanges.
+    static_assert(S::TS * ST <= 64, "a sub-FFT inside one wavefront");
+    cpx<T>* c = reinterpret_cast<cpx<T>*>(region);
+    if (g) {
+      static_for<9>([&](auto rr) {
+        constexpr int q = decltype(rr)::value;
+        c[(q * BL + pd) * ST] = v[q];
+      });
+    }
+    if (mir) {
+      c[pm * ST] = {-v[0].re, -v[0].im};
+      static_for<7>([&](auto rr) {
+        constexpr int q = decltype(rr)::value + 1;
+        c[(q * BL + pm) * ST] = v[16 - q];
+      });
+      c[(8 * BL + pm) * ST] = m8;
+    }
+    __syncthreads();
+    T* base = region + 2 * lds_pad(r * LS) * ST;
+    if (act) lds_move<T, Fs, 0, ST, false>(v, tau, reinterpret_cast<cpx<T>*>(base));
+    fft_forward_r<T, Fs, MAT, ST, TWs, true>(v, tau, rs, base, act);
+    return;
+  }
   T* base = region + lds_pad(r * LS) * ST;
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
@@ -105,9 +130,29 @@ __device__ __forceinline__ void sd_inverse(cpx<T>* v, bool g, int q, int r, int 
   using Fs = typename S::Fs;
   constexpr int LS = S::LS;
   constexpr int BL = LS + LS / 16;
+  const int qd = lds_pad(q), qm = lds_pad((LS - q) & (LS - 1));
+  if constexpr (S::CX) {  // both parts at once
+    T* base = region + 2 * lds_pad(r * LS) * ST;
+    fft_inverse_r<T, Fs, MAT, ST, TWs, true>(v, tau, rs, base, act);
+    if (act) lds_move<T, Fs, 0, ST, true>(v, tau, reinterpret_cast<cpx<T>*>(base));
+    __syncthreads();
+    const cpx<T>* c = reinterpret_cast<const cpx<T>*>(region);
+    if (g) {
+      static_for<9>([&](auto rr) {
+        constexpr int k = decltype(rr)::value;
+        v[k] = c[(k * BL + qd) * ST];
+      });
+      static_for<7>([&](auto rr) {
+        constexpr int k = decltype(rr)::value + 1;
+        v[16 - k] = c[(k * BL + qm) * ST];
+      });
+    }
+    __syncthreads();
+    if (g) sd_group_inv<T, L>(v, w1);
+    return;
+  }
   T* base = region + lds_pad(r * LS) * ST;
   fft_inverse_r<T, Fs, MAT, ST, TWs>(v, tau, rs, base, act);
-  const int qd = lds_pad(q), qm = lds_pad((LS - q) & (LS - 1));
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
     const bool im = part == 1;
@@ -510,7 +555,7 @@ void k_sd_rows_inv_mv(
   using M = SdMvCfg<L>;
   using F = typename M::F;
   constexpr int TWs = sd_tw<L, 1>();
-  __shared__ __align__(16) double lds[M::template lds_doubles<T>()];
+  __shared__ double lds[M::template lds_doubles<T>()];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     P += mo * (sizeof(double) / sizeof(T));
