@@ -132,8 +132,9 @@ typedef struct {
  * Any n1, n2 from 1 to 4096 (EUNSUPPORTED above).  When n1+1 and n2+1 are
  * powers of two the FP64 / FP32 preconditioner runs its sine transforms as
  * FFTs of the odd extension (length 2(n+1)); otherwise as chirp convolutions
- * (Bluestein) on power-of-two FFTs of length >= 2n-1, about four times the
- * arithmetic for the same result.
+ * (Bluestein) on power-of-two FFTs of length >= 2n-1 (symmetric sweeps of
+ * length >= 4n for n > 2048), about four times the arithmetic for the same
+ * result.
  * Errors: EINVAL, ENOMEM, EHIP, EUNSUPPORTED.
  */
 int rsfde_setup(rsfde_plan* out, const rsfde_grid* grid, double alpha1, double alpha2,

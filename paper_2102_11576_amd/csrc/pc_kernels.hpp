@@ -19,8 +19,8 @@
 // T = double or float sets the arithmetic of all three passes (the input and
 // output vectors are always FP64).
 //
-// Layout of the intermediates.  Natural (TL = false): Q, P1, P2 are
-// [rows][n+1] arrays.  Two-dimensional plans (TL = true): Q is strip-tiled
+// Layout of the intermediates.  Natural (TL = false; three-dimensional plans,
+// pass B is k_pc_cols_nat): Q, P1, P2 are [rows][n+1] arrays.  Two-dimensional plans (TL = true): Q is strip-tiled
 // (tile_index: [2 rows][4 slots] tiles, strip after strip), and the P1/P2
 // pairs are interleaved in one array of row segments (pair_index).  Pass B
 // then reads Q in whole strips and writes whole 32-byte sectors, where the

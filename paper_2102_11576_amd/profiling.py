@@ -36,19 +36,19 @@ FAMILIES = [
     (r"k_mv_rows<", "mv_rows"),
     (r"k_mv_cols<", "mv_cols"),
     (r"k_(pc|sd)_rows_fwd<", "pc_rows_fwd"),
-    (r"k_(pc|sd)_cols<", "pc_cols"),
+    (r"k_(pc|sd)_cols(_nat)?<", "pc_cols"),
     (r"k_(pc|sd)_rows_inv<", "pc_rows_inv"),
     (r"k_(pc|sd)_rows_inv_mv<", "pc_inv_mv_rows"),
-    (r"k_dst_cols<", "dst_cols"),
+    (r"k_(cd_)?dst_cols<", "dst_cols"),
     (r"k_gemm_bf16", "pc_gemm_bf16"),
     (r"k_residual\b", "residual"),
     (r"k_rhs\b", "rhs"),
     (r"k_dot\b", "dot"),
     (r"k_bgram<", "block_gram"),
     (r"k_bupd<", "block_update"),
-    (r"k_cd_rows_fwd<", "cd_rows_fwd"),
-    (r"k_cd_cols<", "cd_cols"),
-    (r"k_cd_rows_inv<", "cd_rows_inv"),
+    (r"k_cds?_rows_fwd<", "cd_rows_fwd"),
+    (r"k_cds?_cols<", "cd_cols"),
+    (r"k_cds?_rows_inv<", "cd_rows_inv"),
     (r"k_scale_copy", "other"),
 ]
 
@@ -129,7 +129,7 @@ def _alg_bytes(name: str, n1: int, n2: int) -> float:
     ts = 8.0 if "<double" in name else 4.0
     if re.search(r"k_(pc|sd)_rows_fwd<", name):
         return 8.0 * N + ts * S
-    if re.search(r"k_(pc|sd)_cols<", name):
+    if re.search(r"k_(pc|sd)_cols(_nat)?<", name):
         return 3.0 * ts * S
     if re.search(r"k_(pc|sd)_rows_inv<", name):
         return 2.0 * ts * S + 9.0 * N
