@@ -25,8 +25,11 @@ __device__ __forceinline__ void coefs(double* c, const RedWork& rw, int nb, bool
   }
 }
 
+// W = 2: scheduled for the two wavefronts per SIMD that its grid gives, as
+// k_multidot is (2047^2: 30 vectors 273 -> 202 us, 20 136 -> 140, 32 the same).
 template <int NV, int W, bool FINAL, bool GATHER>
-__global__ __launch_bounds__(kRedThreads) void k_axpy_givens(const double* __restrict__ V,
+__global__ __launch_bounds__(kRedThreads)
+__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8))) void k_axpy_givens(const double* __restrict__ V,
                                                              size_t ldv, const double* win,
                                                              double* vout, size_t N, RedWork rw,
                                                              double* coef, const double* vscale,

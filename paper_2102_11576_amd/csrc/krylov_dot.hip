@@ -8,8 +8,13 @@
 
 namespace rsfde {
 
+// Long vectors (W = 2) run 512 blocks, two wavefronts per SIMD, and are bound by
+// reading the basis: scheduled for that occupancy, all NV + 1 streams' loads are
+// in flight; scheduled for more wavefronts they go out in batches (2047^2: 24
+// vectors 213 -> 158 us, 32 vectors 283 -> 206 us, 5.4 TB/s; up to 16 the same).
 template <int NV, int W>
-__global__ __launch_bounds__(kRedThreads) void k_multidot(const double* __restrict__ V, size_t ldv,
+__global__ __launch_bounds__(kRedThreads)
+__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8))) void k_multidot(const double* __restrict__ V, size_t ldv,
                                                           const double* __restrict__ w, size_t N,
                                                           RedWork rw, bool second,
                                                           const Members mb) {
