@@ -26,7 +26,9 @@ __device__ __forceinline__ void coefs(double* c, const RedWork& rw, int nb, bool
 }
 
 // W = 2: scheduled for the two wavefronts per SIMD that its grid gives, as
-// k_multidot is (2047^2: 30 vectors 273 -> 202 us, 20 136 -> 140, 32 the same).
+// k_multidot is.  Left to itself the compiler's batches of loads suit some counts
+// and not others (2047^2: 21, 22, 25, 26, 29 and 30 vectors 195 to 273 us, now 148
+// to 202; the counts between lose 2 to 3 %: 20 136 -> 140, 28 186 -> 191).
 template <int NV, int W, bool FINAL, bool GATHER>
 __global__ __launch_bounds__(kRedThreads)
 __attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8))) void k_axpy_givens(const double* __restrict__ V,
