@@ -169,12 +169,11 @@ __device__ __forceinline__ void materialize(cpx<T>* r) {
   for (int e = 0; e < N; ++e) asm volatile("" : "+v"(r[e].re), "+v"(r[e].im));
 }
 
-// The twiddle roots of every stage of one sweep (one per stage but the last),
-// loaded up front so that their latency overlaps other work instead of
-// following each exchange.
+// The twiddle roots of every stage of one sweep but the last, loaded up front so
+// that their latency overlaps other work instead of following each exchange.
 template <typename T, class F>
 struct Roots {
-  cpx<T> w[F::NS > 1 ? F::NS - 1 : 1] = {};
+  typename F::template StageRoots<T> w[F::NS > 1 ? F::NS - 1 : 1] = {};
   __device__ __forceinline__ void load_fwd(int tau, const cpx<T>* __restrict__ tw) {
     static_for<F::NS - 1>([&](auto tt) {
       constexpr int t = decltype(tt)::value;
@@ -187,7 +186,9 @@ struct Roots {
       w[t] = F::template dit_root<T, t>(tau, tw);
     });
   }
-  __device__ __forceinline__ cpx<T> at(int t) const { return w[t < F::NS - 1 ? t : 0]; }
+  __device__ __forceinline__ const typename F::template StageRoots<T>& at(int t) const {
+    return w[t < F::NS - 1 ? t : 0];
+  }
 };
 
 // Forward DIF sweep: natural order (stage-0 positions) in, digit-reversed

@@ -215,6 +215,7 @@ RS_HD int fft_mirror_slot(int L, int P, int p) {
 // x[q] *= w^q for q = 1..R-1, with w^q built from the one loaded root w by
 // squarings and products (at most five roundings deep for R = 16) instead of
 // R-1 table loads: fewer live registers and one memory latency per butterfly.
+// (Stages of four points may load all three: Fft::StageRoots.)
 template <typename T, int R>
 RS_HD void apply_twiddles(cpx<T>* x, cpx<T> w1) {
   if constexpr (R >= 2) x[1] = cmul(x[1], w1);
@@ -270,41 +271,71 @@ struct Fft {
     return (beta / s) * blocklen(t) + (beta % s) + m * s;
   }
 
-  // Twiddle root of stage t for thread tau: stages before the last have radix
+  // Twiddle roots of stage t for thread tau: stages before the last have radix
   // PP, one butterfly per thread and one root (exp(-2 pi i k / L_t) forward;
   // the inverse indexes the mirrored entry instead of conjugating, which keeps
   // the compiler from holding the forward roots in registers until the
   // inverse sweep).  The sweeps load every root up front, so the loads'
   // latency overlaps the first stage instead of following each exchange.
+  //
+  // Four points per thread, FP32 up to L = 128 and FP64 up to L = 16: w, w^2 and
+  // w^3 are loaded, each rounded once.  With w^2 and w^3 as products, up to three
+  // stages of them, the FP32 preconditioner lay further from its FP64 value than
+  // with one stage of 16 points (2-norm inside the domain, 16 points / products /
+  // loads: 63^2 2.0e-7 / 2.9e-7 / 1.3e-7, 50^3 2.5e-7 / 4.2e-7 / 1.8e-7).  At L =
+  // 256 the products are the closer ones (127^2 0.7 of the 16 points' error), and
+  // the loads would take FP32 at 100^3 from 80 to 106 us; at L = 128 they take it
+  // from 22.0 to 22.6 us at 63^3 and from 28 to 30 at 50^3.
+  template <typename T>
+  static constexpr int NR = PP == 4 && L <= (sizeof(T) == 4 ? 128 : 16) ? 3 : 1;
+  template <typename T>
+  struct StageRoots {
+    cpx<T> w[NR<T>];
+  };
   template <typename T, int t>
-  static RS_HD cpx<T> dif_root(int tau, const cpx<T>* __restrict__ tw) {
+  static RS_HD StageRoots<T> dif_root(int tau, const cpx<T>* __restrict__ tw) {
     static_assert(t < NS - 1, "the last stage has no twiddles");
     constexpr int twsh = LOGL - ilog2(blocklen(t));
-    return tw[(tau % stride(t)) << twsh];
+    const int k = (tau % stride(t)) << twsh;  // < L / PP
+    StageRoots<T> r;
+    for (int q = 0; q < NR<T>; ++q) r.w[q] = tw[(q + 1) * k];
+    return r;
   }
   template <typename T, int t>
-  static RS_HD cpx<T> dit_root(int tau, const cpx<T>* __restrict__ tw) {
+  static RS_HD StageRoots<T> dit_root(int tau, const cpx<T>* __restrict__ tw) {
     static_assert(t < NS - 1, "the last stage has no twiddles");
     constexpr int twsh = LOGL - ilog2(blocklen(t));
-    return tw[(L - ((tau % stride(t)) << twsh)) & (L - 1)];
+    const int k = (tau % stride(t)) << twsh;
+    StageRoots<T> r;
+    for (int q = 0; q < NR<T>; ++q) r.w[q] = tw[(L - (q + 1) * k) & (L - 1)];
+    return r;
+  }
+  template <typename T, int R>
+  static RS_HD void twiddle(cpx<T>* x, const StageRoots<T>& r) {
+    if constexpr (NR<T> == 3) {
+      static_assert(R == 4, "stages before the last have radix PP");
+      for (int q = 0; q < 3; ++q) x[q + 1] = cmul(x[q + 1], r.w[q]);
+    } else {
+      apply_twiddles<T, R>(x, r.w[0]);
+    }
   }
 
-  // Stage t with its root w (ignored for the last stage).
+  // Stage t with its roots w (ignored for the last stage).
   template <typename T, int t>
-  static RS_HD void dif_stage_w(cpx<T>* reg, cpx<T> w) {
+  static RS_HD void dif_stage_w(cpx<T>* reg, const StageRoots<T>& w) {
     constexpr int R = radix(t);
     static_for<PP / R>([&](auto uu) {
       constexpr int u = decltype(uu)::value;
       Dft<T, R, -1>::run(reg + u * R);
-      if constexpr (t < NS - 1) apply_twiddles<T, R>(reg + u * R, w);
+      if constexpr (t < NS - 1) twiddle<T, R>(reg + u * R, w);
     });
   }
   template <typename T, int t>
-  static RS_HD void dit_stage_w(cpx<T>* reg, cpx<T> w) {
+  static RS_HD void dit_stage_w(cpx<T>* reg, const StageRoots<T>& w) {
     constexpr int R = radix(t);
     static_for<PP / R>([&](auto uu) {
       constexpr int u = decltype(uu)::value;
-      if constexpr (t < NS - 1) apply_twiddles<T, R>(reg + u * R, w);
+      if constexpr (t < NS - 1) twiddle<T, R>(reg + u * R, w);
       Dft<T, R, +1>::run(reg + u * R);
     });
   }
@@ -312,12 +343,12 @@ struct Fft {
   template <typename T, int t>
   static RS_HD void dif_stage(cpx<T>* reg, int tau, const cpx<T>* __restrict__ tw) {
     if constexpr (t < NS - 1) dif_stage_w<T, t>(reg, dif_root<T, t>(tau, tw));
-    else dif_stage_w<T, t>(reg, cpx<T>{(T)1, (T)0});
+    else dif_stage_w<T, t>(reg, StageRoots<T>{});
   }
   template <typename T, int t>
   static RS_HD void dit_stage(cpx<T>* reg, int tau, const cpx<T>* __restrict__ tw) {
     if constexpr (t < NS - 1) dit_stage_w<T, t>(reg, dit_root<T, t>(tau, tw));
-    else dit_stage_w<T, t>(reg, cpx<T>{(T)1, (T)0});
+    else dit_stage_w<T, t>(reg, StageRoots<T>{});
   }
 };
 

@@ -258,6 +258,55 @@ static double run_sd_case(unsigned seed) {
   return (rel > tol || err2 > tol) ? 1e9 : rel;
 }
 
+// Root-mean-square error of the FP32 forward sweep against the DFT definition,
+// relative to the spectrum, over random inputs.
+template <int L, int P>
+static double run_rms_case(unsigned seed) {
+  using F = Fft<L, P>;
+  const std::vector<cpx<float>> tw = twiddles<float>(L);
+  std::vector<cpx<float>> x(L), buf(L);
+  std::vector<std::array<cpx<float>, F::PP>> regs(F::TPF);
+  srand(seed);
+  double num = 0, den = 0;
+  for (int rep = 0; rep < 50; ++rep) {
+    for (auto& v : x) v = {(float)(rand() / (double)RAND_MAX - 0.5), (float)(rand() / (double)RAND_MAX - 0.5)};
+    for (int tau = 0; tau < F::TPF; ++tau)
+      for (int e = 0; e < F::PP; ++e) regs[tau][e] = x[F::pos(0, tau, e)];
+    static_for<F::NS>([&](auto tt) {
+      constexpr int t = decltype(tt)::value;
+      for (int tau = 0; tau < F::TPF; ++tau) F::template dif_stage<float, t>(regs[tau].data(), tau, tw.data());
+      if constexpr (t < F::NS - 1) {
+        for (int tau = 0; tau < F::TPF; ++tau)
+          for (int e = 0; e < F::PP; ++e) buf[F::pos(t, tau, e)] = regs[tau][e];
+        for (int tau = 0; tau < F::TPF; ++tau)
+          for (int e = 0; e < F::PP; ++e) regs[tau][e] = buf[F::pos(t + 1, tau, e)];
+      }
+    });
+    for (int tau = 0; tau < F::TPF; ++tau)
+      for (int e = 0; e < F::PP; ++e) {
+        const int f = fft_freq(L, P, F::pos(F::NS - 1, tau, e));
+        double sr = 0, si = 0;
+        for (int j = 0; j < L; ++j) {
+          const double a = -2.0 * 3.14159265358979323846 * (((long long)j * f) % L) / L;
+          sr += x[j].re * std::cos(a) - x[j].im * std::sin(a);
+          si += x[j].re * std::sin(a) + x[j].im * std::cos(a);
+        }
+        num += (regs[tau][e].re - sr) * (regs[tau][e].re - sr) + (regs[tau][e].im - si) * (regs[tau][e].im - si);
+        den += sr * sr + si * si;
+      }
+  }
+  const double rms = std::sqrt(num / den);
+  printf("L=%5d P=%2d f32 rms rel err %.2e\n", L, P, rms);
+  return rms;
+}
+
+// Four points per thread in FP32: no more than the error of an FFT whose roots are
+// each rounded once, 0.6 u sqrt(log2 L) on average (u = 2^-24).
+template <int L>
+static bool rms_ok(unsigned seed) {
+  return run_rms_case<L, 4>(seed) <= 0.6 * std::ldexp(1.0, -24) * std::sqrt((double)ilog2(L));
+}
+
 int main() {
   double worst = 0;
   worst = std::fmax(worst, run_case<2, 16, double>(1));
@@ -290,6 +339,10 @@ int main() {
   worst = std::fmax(worst, run_sd_case<16384, double>(27));
   worst = std::fmax(worst, run_sd_case<4096, float>(26));
   if (worst >= 1e9) { printf("FAIL\n"); return 1; }
+  if (!(rms_ok<16>(32) & rms_ok<32>(33) & rms_ok<64>(34) & rms_ok<128>(35))) {
+    printf("FAIL: rounding of the roots\n");
+    return 1;
+  }
   printf("OK\n");
   return 0;
 }

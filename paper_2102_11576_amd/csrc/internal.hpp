@@ -32,18 +32,18 @@ struct Members {
   }
 };
 
-// Points per thread of the register-resident FFT of length L: 4 up to L = 256,
-// 8 up to L = 1024, 16 above.  A pass over short lines is bound by one block's
-// serial time (instruction fetch of the unrolled sweep, one radix butterfly
-// after the other) on small grids and by the waves in flight on large ones;
-// fewer points halve the code and the registers.  Measured, 16 points before:
+// Points per thread of the register-resident FFT of length L: all up to L = 8 (no
+// rounded roots at all), 4 up to L = 256, 8 up to L = 1024, 16 above.  A pass
+// over short lines is bound by one block's serial time (instruction fetch of the
+// unrolled sweep, one radix butterfly after the other) on small grids and by the
+// waves in flight on large ones; fewer points halve the code and the registers.  Measured, 16 points before:
 // fused pass C 22.0 -> 11.2 us and pass A 10.5 -> 5.0 us at 63^2 (L = 128),
 // chirp column pass 26.9 -> 15.0 us at 256^2 (L = 512), mv_rows 101 -> 89 us
 // and z pass of the preconditioner 257 -> 213 us at 255^3 (L = 512).  8 points
 // up to L = 256: fused pass 14.4, pass A 6.6 us.  From L = 2048 on the extra
 // register stage costs more than the registers give: 8 points took mv_cols +
 // mv_rows at 2047^2 (L = 4096) 59.6 -> 68.6 us, at 4095^2 (L = 8192) 322 -> 503.
-constexpr int fft_pts(int L) { return L <= 4 ? L : (L <= 256 ? 4 : (L <= 1024 ? 8 : 16)); }
+constexpr int fft_pts(int L) { return L <= 8 ? L : (L <= 256 ? 4 : (L <= 1024 ? 8 : 16)); }
 
 // Lengths whose exchanges may move both parts at once (lds_exchange, CX): at 4 and
 // 8 points per thread twice the LDS still leaves 16 wavefronts per CU.  Used where
