@@ -58,11 +58,11 @@ __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int 
                                            const cpx<T>* __restrict__ twS, T* region) {
   using S = Sd<L>;
   using Fs = typename S::Fs;
-  constexpr int TWs = sd_tw<L, 1>();
+  constexpr int TWs = sd_tw<S, 1>();
   {
     Roots<T, Fs> rs;
     rs.load_fwd(tau, twS);
-    sd_forward<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
+    sd_forward<T, S, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
   }
   const cpx<T>* kr = khat + r * S::LS;
   static_for<S::PS>([&](auto ee) {
@@ -72,7 +72,7 @@ __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int 
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
+    sd_inverse<T, S, 1, TWs, MAT>(v, g, p, r, tau, w1, rs, region);
   }
 }
 

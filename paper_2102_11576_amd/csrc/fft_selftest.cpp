@@ -116,9 +116,9 @@ static double run_case(unsigned seed) {
 // Symmetric DST-I (sd_engine.hpp): forward against the sine sums, slot and
 // mirror maps, and the inverse returning L x.  Every thread of one transform
 // is simulated in turn with the LDS exchange as a plain array.
-template <int L, typename T>
+template <int L, typename T, int Pts = sd_pts(L)>
 static double run_sd_case(unsigned seed) {
-  using S = Sd<L>;
+  using S = Sd<L, Pts>;
   using Fs = typename S::Fs;
   constexpr int LS = S::LS, n = L / 2 - 1;
   std::vector<cpx<T>> twL = twiddles<T>(L), twS = twiddles<T>(LS);
@@ -334,6 +334,7 @@ int main() {
   worst = std::fmax(worst, run_sd_case<512, double>(21));
   worst = std::fmax(worst, run_sd_case<1024, double>(22));
   worst = std::fmax(worst, run_sd_case<2048, double>(23));
+  worst = std::fmax(worst, run_sd_case<kSdManyL, double, 16>(28));
   worst = std::fmax(worst, run_sd_case<4096, double>(24));
   worst = std::fmax(worst, run_sd_case<8192, double>(25));
   worst = std::fmax(worst, run_sd_case<16384, double>(27));

@@ -138,6 +138,7 @@ hipError_t launch_mv_cols(int L, const void* z, const double* t, double* out,
 struct SdTabs {
   const void* twS = nullptr;
   const int32_t* msl = nullptr;
+  bool many = false;  // L = kSdManyL with 16 points per thread (sd_many)
 };
 
 // Sine-transform preconditioner, three passes; T = float or double internally.

@@ -672,51 +672,53 @@ static hipError_t dst_cols_impl(const T* inA, T* outA, const T* inB, T* outB, co
   return hipGetLastError();
 }
 
-template <typename T, int L>
+template <typename T, class S>
 static hipError_t sd_rows_fwd_impl(const double* v, const double* sig, T* Q, const void* twL,
                                    const void* twS, int n1, int n2, hipStream_t s,
                                    const Members& mb) {
-  hipLaunchKernelGGL((k_sd_rows_fwd<T, L>), dim3((n2 + 1) / 2, 1, mb.n), dim3(Sd<L>::TPD), 0, s, v, sig, Q,
-                     (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, mb);
+  constexpr int ND = sd_per_block<S>();
+  hipLaunchKernelGGL((k_sd_rows_fwd<T, S>), dim3(((n2 + 1) / 2 + ND - 1) / ND, 1, mb.n), dim3(ND * S::TPD),
+                     0, s, v, sig, Q, (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, mb);
   return hipGetLastError();
 }
 
-template <typename T, int L>
+template <typename T, class S>
 static hipError_t sd_cols_impl(const T* Q, T* P, const T* lamx, const T* lamy, const void* twL,
                                const void* twS, int n1, int n2, double kx, double ky,
                                double dpen, double Kfac, hipStream_t s, const Members& mb,
                                const double* mk) {
-  using C = SdCols<L>;
-  hipLaunchKernelGGL((k_sd_cols<T, L>), dim3((n1 + 1) / 2, 1, mb.n), dim3(C::THR), 0, s, Q, P, lamx,
-                     lamy, (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, (T)kx, (T)ky, (T)dpen,
+  using C = SdCols<S>;
+  hipLaunchKernelGGL((k_sd_cols<T, S>), dim3(((n1 + 1) / 2 + C::BC - 1) / C::BC, 1, mb.n),
+                     dim3(C::THR), 0, s, Q, P, lamx, lamy, (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, (T)kx, (T)ky, (T)dpen,
                      (T)(0.5 * Kfac), mb, mk);
   return hipGetLastError();
 }
 
-template <typename T, int L>
+template <typename T, class S>
 static hipError_t sd_rows_inv_impl(const T* P, const uint8_t* mask, double* z, const void* twL,
                                    const void* twS, const int32_t* msl, int n1, int n2,
                                    hipStream_t s, const Members& mb) {
-  hipLaunchKernelGGL((k_sd_rows_inv<T, L>), dim3(n2, 1, mb.n), dim3(Sd<L>::TPD), 0, s, P, mask, z,
-                     (const cpx<T>*)twL, (const cpx<T>*)twS, msl, n1, n2, mb);
+  constexpr int ND = sd_per_block<S>();
+  hipLaunchKernelGGL((k_sd_rows_inv<T, S>), dim3((n2 + ND - 1) / ND, 1, mb.n), dim3(ND * S::TPD), 0, s,
+                     P, mask, z, (const cpx<T>*)twL, (const cpx<T>*)twS, msl, n1, n2, mb);
   return hipGetLastError();
 }
 
-template <typename T, int L>
+template <typename T, class S>
 static hipError_t sd_rows_inv_mv_impl(const T* P, const uint8_t* mask, void* z, bool z32,
                                       double* t, const void* twL, const void* twS,
                                       const int32_t* msl, const void* tw64, const double* sym,
                                       double coef, double dpen, const double* sub, double theta,
                                       int n1, int n2, hipStream_t s, const Members& mb,
                                       const double* mk) {
-  using M = SdMvCfg<L>;
+  using M = SdMvCfg<S>;
   const int blocks = (n2 + 1) / 2;
   if (z32)
-    hipLaunchKernelGGL((k_sd_rows_inv_mv<T, L, float>), dim3(blocks, 1, mb.n), dim3(M::THR), 0, s,
+    hipLaunchKernelGGL((k_sd_rows_inv_mv<T, S, float>), dim3(blocks, 1, mb.n), dim3(M::THR), 0, s,
                        P, mask, (float*)z, t, (const cpx<T>*)twL, (const cpx<T>*)twS, msl,
                        (const cpx<double>*)tw64, sym, coef, dpen, sub, theta, n1, n2, mb, mk);
   else
-    hipLaunchKernelGGL((k_sd_rows_inv_mv<T, L>), dim3(blocks, 1, mb.n), dim3(M::THR), 0, s, P,
+    hipLaunchKernelGGL((k_sd_rows_inv_mv<T, S>), dim3(blocks, 1, mb.n), dim3(M::THR), 0, s, P,
                        mask, (double*)z, t, (const cpx<T>*)twL, (const cpx<T>*)twS, msl,
                        (const cpx<double>*)tw64, sym, coef, dpen, sub, theta, n1, n2, mb, mk);
   return hipGetLastError();
@@ -724,12 +726,23 @@ static hipError_t sd_rows_inv_mv_impl(const T* P, const uint8_t* mask, void* z, 
 
 // Pass selection: the symmetric form for the tiled layouts when its tables are
 // given and L >= kSdMinL, the plain FFT form otherwise.
+// f(Sd<L, points per thread>) for the points that the tables were made for.
+template <int L, class Fn>
+static hipError_t sd_form(const SdTabs& sd, Fn&& f) {
+  if constexpr (L == kSdManyL) {
+    if (sd.many) return f(Sd<L, 16>{});
+  }
+  return f(Sd<L>{});
+}
 template <typename T, int L>
 static hipError_t rows_fwd_any(const double* v, const double* sig, T* Q, const void* tw, int n1,
                                int n2, bool tiled, hipStream_t s, const Members& mb,
                                const SdTabs& sd) {
   if constexpr (L >= kSdMinL) {
-    if (tiled && sd.twS) return sd_rows_fwd_impl<T, L>(v, sig, Q, tw, sd.twS, n1, n2, s, mb);
+    if (tiled && sd.twS)
+      return sd_form<L>(sd, [&](auto f) {
+        return sd_rows_fwd_impl<T, decltype(f)>(v, sig, Q, tw, sd.twS, n1, n2, s, mb);
+      });
   }
   return tiled ? pc_rows_fwd_impl<T, L, true>(v, sig, Q, tw, n1, n2, s, mb)
                : pc_rows_fwd_impl<T, L, false>(v, sig, Q, tw, n1, n2, s, mb);
@@ -742,8 +755,10 @@ static hipError_t cols_any(const T* Q, T* P1, T* P2, const T* lamx, const T* lam
                            const SdTabs& sd) {
   if constexpr (L >= kSdMinL) {
     if (tiled && sd.twS)
-      return sd_cols_impl<T, L>(Q, P1, lamx, lamy, tw, sd.twS, n1, n2, kx, ky, dpen, Kfac, s, mb,
-                                mk);
+      return sd_form<L>(sd, [&](auto f) {
+        return sd_cols_impl<T, decltype(f)>(Q, P1, lamx, lamy, tw, sd.twS, n1, n2, kx, ky, dpen,
+                                            Kfac, s, mb, mk);
+      });
   }
   return pc_cols_impl<T, L>(Q, P1, P2, lamx, lamy, tw, n1, n2, kx, ky, dpen, Kfac, tiled, s, mb, mk);
 }
@@ -754,7 +769,9 @@ static hipError_t rows_inv_any(const T* P1, const T* P2, const uint8_t* mask, do
                                const Members& mb, const SdTabs& sd) {
   if constexpr (L >= kSdMinL) {
     if (tiled && sd.twS)
-      return sd_rows_inv_impl<T, L>(P1, mask, z, tw, sd.twS, sd.msl, n1, n2, s, mb);
+      return sd_form<L>(sd, [&](auto f) {
+        return sd_rows_inv_impl<T, decltype(f)>(P1, mask, z, tw, sd.twS, sd.msl, n1, n2, s, mb);
+      });
   }
   return tiled ? pc_rows_inv_impl<T, L, true>(P1, P2, mask, z, tw, n1, n2, s, mb)
                : pc_rows_inv_impl<T, L, false>(P1, P2, mask, z, tw, n1, n2, s, mb);
@@ -768,9 +785,10 @@ static hipError_t rows_inv_mv_any(const T* P1, const T* P2, const uint8_t* mask,
                                   const Members& mb, const double* mk, const SdTabs& sd) {
   if constexpr (L >= kSdMinL) {
     if (tiled && sd.twS)
-      return sd_rows_inv_mv_impl<T, L>(P1, mask, z, z32, t, twT, sd.twS, sd.msl, tw64,
-                                       sym, coef, dpen, sub, theta, n1, n2,
-                                       s, mb, mk);
+      return sd_form<L>(sd, [&](auto f) {
+        return sd_rows_inv_mv_impl<T, decltype(f)>(P1, mask, z, z32, t, twT, sd.twS, sd.msl, tw64, sym,
+                                                   coef, dpen, sub, theta, n1, n2, s, mb, mk);
+      });
   }
   return tiled ? pc_rows_inv_mv_impl<T, L, true>(P1, P2, mask, z, z32, t, twT, tw64, sym, coef,
                                                  dpen, sub, theta, n1, n2, s, mb, mk)

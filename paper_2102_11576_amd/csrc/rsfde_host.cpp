@@ -97,9 +97,11 @@ struct Plan {
   float* lamx32 = nullptr;
   float* lamy32 = nullptr;
   // symmetric sine transform (two-dimensional passes, L >= kSdMinL): used along
-  // x / y, and the mirror slots of the x transform
+  // x / y; per precision ([0] FP64, [1] FP32) whether it is the form for many
+  // lines (sd_many), and the mirror slots of the x transform
   bool sdx = false, sdy = false;
-  int32_t* msl = nullptr;
+  bool manyx[2] = {}, manyy[2] = {};
+  int32_t* msl[2] = {nullptr, nullptr};
   // chirp-form preconditioner (n + 1 not a power of two)
   double* lamx_n = nullptr;  // tau eigenvalues, natural order, unit k
   double* lamy_n = nullptr;
@@ -586,18 +588,15 @@ int precond3(Plan* P, const double* r, const double* sig, double* z, std::map<in
 // precision of T (empty where the plain FFT form is used).
 template <typename T>
 SdTabs sd_x(Plan* P) {
-  SdTabs t;
-  if (P->sdx) {
-    t.twS = (sizeof(T) == 8 ? P->tw64 : P->tw32)[P->Ldx / 16];
-    t.msl = P->msl;
-  }
-  return t;
+  constexpr int t = sizeof(T) == 8 ? 0 : 1;
+  if (!P->sdx) return SdTabs{};
+  return SdTabs{(t == 0 ? P->tw64 : P->tw32)[P->Ldx / 16], P->msl[t], P->manyx[t]};
 }
 template <typename T>
 SdTabs sd_y(Plan* P) {
-  SdTabs t;
-  if (P->sdy) t.twS = (sizeof(T) == 8 ? P->tw64 : P->tw32)[P->Ldy / 16];
-  return t;
+  constexpr int t = sizeof(T) == 8 ? 0 : 1;
+  if (!P->sdy) return SdTabs{};
+  return SdTabs{(t == 0 ? P->tw64 : P->tw32)[P->Ldy / 16], nullptr, P->manyy[t]};
 }
 
 int precond_impl(Plan* P, const double* r, const double* sig, double* z, int precision,
@@ -1359,14 +1358,14 @@ std::vector<double> pos_eigs(const std::vector<double>& ly, int L) {
   return lam;
 }
 
-// Tables of the symmetric sine transform of length L (sd_engine.hpp) for the
+// Tables of the symmetric sine transform S (sd_engine.hpp) for the
 // eigenvalues lam (natural order, lam[k-1] at DST index k): in slot order
 // (x direction), in block-position order (y direction, 9 L/16 entries), and
 // the mirror slots of the upper halves of blocks 0 and 8 (-1 at frequency L/2).
-template <int L>
-void sd_tables_L(const std::vector<double>& lam, std::vector<double>* by_slot,
+template <class S>
+void sd_tables_S(const std::vector<double>& lam, std::vector<double>* by_slot,
                  std::vector<double>* by_pos, std::vector<int32_t>* msl) {
-  using S = Sd<L>;
+  constexpr int L = S::L;
   using Fs = typename S::Fs;
   const int n = (int)lam.size();
   auto lam_of = [&](int f) {
@@ -1403,14 +1402,19 @@ void sd_tables_L(const std::vector<double>& lam, std::vector<double>* by_slot,
   }
 }
 
-bool sd_tables(int L, const std::vector<double>& lam, std::vector<double>* by_slot,
+bool sd_tables(int L, bool many, const std::vector<double>& lam, std::vector<double>* by_slot,
                std::vector<double>* by_pos, std::vector<int32_t>* msl) {
+  if (many) {
+    if (L != kSdManyL) return false;
+    sd_tables_S<Sd<kSdManyL, 16>>(lam, by_slot, by_pos, msl);
+    return true;
+  }
   switch (L) {
-    case 512: sd_tables_L<512>(lam, by_slot, by_pos, msl); return true;
-    case 1024: sd_tables_L<1024>(lam, by_slot, by_pos, msl); return true;
-    case 2048: sd_tables_L<2048>(lam, by_slot, by_pos, msl); return true;
-    case 4096: sd_tables_L<4096>(lam, by_slot, by_pos, msl); return true;
-    case 8192: sd_tables_L<8192>(lam, by_slot, by_pos, msl); return true;
+    case 512: sd_tables_S<Sd<512>>(lam, by_slot, by_pos, msl); return true;
+    case 1024: sd_tables_S<Sd<1024>>(lam, by_slot, by_pos, msl); return true;
+    case 2048: sd_tables_S<Sd<2048>>(lam, by_slot, by_pos, msl); return true;
+    case 4096: sd_tables_S<Sd<4096>>(lam, by_slot, by_pos, msl); return true;
+    case 8192: sd_tables_S<Sd<8192>>(lam, by_slot, by_pos, msl); return true;
     default: return false;
   }
 }
@@ -1530,25 +1534,33 @@ int rsfde_setup(rsfde_plan* out, const rsfde_grid* grid, double alpha1, double a
   if (P->Ldx && P->Ldy) {
     P->sdx = P->Ldx >= kSdMinL;
     P->sdy = P->Ldy >= kSdMinL;
-    std::vector<double> lamx, lamy;
-    std::vector<int32_t> msl;
-    if (P->sdx) {
-      if (!sd_tables(P->Ldx, tau_eigs(tx), &lamx, nullptr, &msl)) return failx(__LINE__, RSFDE_EUNSUPPORTED);
-      if (upload(P, &P->msl, msl, s) != hipSuccess || ensure_twiddles(P, P->Ldx / 16, s) != hipSuccess)
-        return failx(__LINE__, RSFDE_ENOMEM);
-    } else {
-      lamx = slot_eigs(tau_eigs(tx), P->Ldx);
-    }
-    if (P->sdy) {
-      if (!sd_tables(P->Ldy, tau_eigs(ty), nullptr, &lamy, nullptr)) return failx(__LINE__, RSFDE_EUNSUPPORTED);
-      if (ensure_twiddles(P, P->Ldy / 16, s) != hipSuccess) return failx(__LINE__, RSFDE_ENOMEM);
-    } else {
-      lamy = pos_eigs(tau_eigs(ty), P->Ldy);
-    }
-    std::vector<float> lamx_f(lamx.begin(), lamx.end()), lamy_f(lamy.begin(), lamy.end());
-    if (upload(P, &P->lamx64, lamx, s) != hipSuccess || upload(P, &P->lamy64, lamy, s) != hipSuccess ||
-        upload(P, &P->lamx32, lamx_f, s) != hipSuccess || upload(P, &P->lamy32, lamy_f, s) != hipSuccess)
+    if ((P->sdx && ensure_twiddles(P, P->Ldx / 16, s) != hipSuccess) ||
+        (P->sdy && ensure_twiddles(P, P->Ldy / 16, s) != hipSuccess))
       return failx(__LINE__, RSFDE_ENOMEM);
+    const std::vector<double> lx = tau_eigs(tx), ly = tau_eigs(ty);
+    for (int t = 0; t < 2; ++t) {  // FP64, FP32
+      std::vector<double> lamx, lamy;
+      std::vector<int32_t> msl;
+      P->manyx[t] = P->sdx && sd_many(P->Ldx, n2, t == 1);
+      P->manyy[t] = P->sdy && sd_many(P->Ldy, n1, t == 1);
+      if (P->sdx) {
+        if (!sd_tables(P->Ldx, P->manyx[t], lx, &lamx, nullptr, &msl))
+          return failx(__LINE__, RSFDE_EUNSUPPORTED);
+        if (upload(P, &P->msl[t], msl, s) != hipSuccess) return failx(__LINE__, RSFDE_ENOMEM);
+      } else {
+        lamx = slot_eigs(lx, P->Ldx);
+      }
+      if (P->sdy) {
+        if (!sd_tables(P->Ldy, P->manyy[t], ly, nullptr, &lamy, nullptr))
+          return failx(__LINE__, RSFDE_EUNSUPPORTED);
+      } else {
+        lamy = pos_eigs(ly, P->Ldy);
+      }
+      const std::vector<float> fx(lamx.begin(), lamx.end()), fy(lamy.begin(), lamy.end());
+      if ((t == 0 ? upload(P, &P->lamx64, lamx, s) : upload(P, &P->lamx32, fx, s)) != hipSuccess ||
+          (t == 0 ? upload(P, &P->lamy64, lamy, s) : upload(P, &P->lamy32, fy, s)) != hipSuccess)
+        return failx(__LINE__, RSFDE_ENOMEM);
+    }
   }
   if (P->Lgx) {  // chirp-form tables
     const std::vector<double> lx = tau_eigs(tx), ly = tau_eigs(ty);

@@ -37,19 +37,33 @@ namespace rsfde {
 // Smallest L handled by the symmetric form (sub-FFTs of at least 32 points).
 constexpr int kSdMinL = 512;
 
-// Points per thread of the sub-FFTs: 8 up to L = 2048, where a grid has at most
-// 512 transforms per pass and their serial time decides (twice the threads of 16
-// points; whole preconditioner 255^2 22.4 -> 17.6 us, 511^2 23.7 -> 20.4, 1023^2
-// 39.4 -> 36.9), 16 beyond, where one more register stage costs more than the
-// threads give (2047^2 with 8: 79.8 -> 101.7 us).  4 up to L = 1024: as 8 (511^2
-// 20.3 -> 20.1) but 9 % slower in batches.
+// Points per thread of the sub-FFTs: 8 up to L = 2048, where a pass over few lines
+// is decided by the serial time of one transform (twice the threads of 16 points;
+// whole preconditioner 255^2 22.4 -> 17.6 us, 511^2 23.7 -> 20.4, 1023^2 39.4 ->
+// 36.9), 16 beyond, where one more register stage costs more than the threads
+// give (2047^2 with 8: 79.8 -> 101.7 us).  4 up to L = 1024: as 8 (511^2 20.3 ->
+// 20.1) but 9 % slower in batches.
 constexpr int sd_pts(int L) { return L <= 2048 ? 8 : 16; }
 
-template <int L>
+// At L = 2048 an axis of many lines (rows or columns of the other axis) takes 16
+// points all the same, two transforms per block: with more blocks than the GPU
+// holds at once their number of stages counts again, in FP32 (half the memory
+// traffic to hide it) sooner.  Preconditioner, 8 / 16 points per thread: FP64
+// 1023 x 511 26.3 / 27.9 us, 1023^2 37.0 / 39.3, 2047 x 1023 58.3 / 54.5, 4095 x
+// 1023 110.7 / 105.7; FP32 1023 x 511 22.6 / 23.2, 1023^2 34.1 / 31.8, 4095 x
+// 1023 68.6 / 57.0.  A step of 1023 x 2047 points (s-step GMRES) takes 10.5 / 8.9
+// ms in FP64, one of 1023^2 with the FP32 preconditioner 5.09 / 5.12.
+constexpr int kSdManyL = 2048;
+constexpr bool sd_many(int L, int lines, bool fp32) {
+  return L == kSdManyL && lines > (fp32 ? 511 : 1023);
+}
+
+template <int Len, int Pts = sd_pts(Len)>
 struct Sd {
+  static constexpr int L = Len;
   static constexpr int LS = L / 16;  // block (sub-FFT) length
   static_assert(LS >= 32 && (LS & (LS - 1)) == 0, "symmetric DST needs L >= 512, a power of two");
-  static constexpr int PS = sd_pts(L);       // points per thread of a sub-FFT
+  static constexpr int PS = Pts;             // points per thread of a sub-FFT
   using Fs = Fft<LS, PS>;                    // sub-FFT engine
   static constexpr int TS = Fs::TPF;         // threads of one sub-FFT
   static constexpr int TPD = 9 * TS;         // block-stage threads of one transform

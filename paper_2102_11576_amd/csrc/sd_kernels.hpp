@@ -29,23 +29,29 @@ __device__ __forceinline__ size_t pair_index(int r, int c, int rows) {
   return (((size_t)(c / W) * rows + r) * W + pos) * 2;
 }
 
-// One transform (row passes) or column pair (pass B) per block: 9 sub-FFTs of TS
-// threads.  Small blocks keep more of them resident per CU (pass B's pair takes
-// 38 KB of LDS with its stash at L = 4096), which hides more latency, and spread
-// the smaller grids over more CUs.
-template <int L>
+// Transforms per block of the row passes and column pairs per block of pass B
+// (9 sub-FFTs of TS threads each).  One: small blocks keep more of them resident
+// per CU (pass B's pair takes 38 KB of LDS with its stash at L = 4096), which
+// hides more latency, and spread the smaller grids over more CUs.  Two where one
+// would be 72 threads (L = 2048 with 16 points per thread).
+template <class S>
+constexpr int sd_per_block() {
+  return S::L >= 2048 && S::TS < 16 ? 16 / S::TS : 1;
+}
+template <class S>
 struct SdCols {
+  static constexpr int BC = sd_per_block<S>();
   // Up to L = 2048 the two inverse sweeps of a column pair run at once, on a
-  // second set of TPD threads (too few column pairs to fill the GPU there).
-  static constexpr bool CONC = L <= 2048;
-  static constexpr int THR = (CONC ? 2 : 1) * Sd<L>::TPD;
+  // second set of BC TPD threads (too few column pairs to fill the GPU there).
+  static constexpr bool CONC = S::L <= 2048;
+  static constexpr int THR = (CONC ? 2 : 1) * BC * S::TPD;
 };
 // Threads of one sub-FFT inside one wavefront (ST: LDS interleave of the
 // transforms of a block): its exchanges then need no block barrier.
-template <int L, int ST>
+template <class S, int ST>
 constexpr int sd_tw() {
-  static_assert(Sd<L>::TS * ST <= 64 || (Sd<L>::TS * ST) % 64 == 0, "sub-FFT thread groups");
-  return (Sd<L>::TS * ST <= 64) ? Sd<L>::TS : 64 / ST;
+  static_assert(S::TS * ST <= 64 || (S::TS * ST) % 64 == 0, "sub-FFT thread groups");
+  return (S::TS * ST <= 64) ? S::TS : 64 / ST;
 }
 
 // Forward symmetric sweep of one transform.  Group-stage threads (g, group p)
@@ -56,15 +62,14 @@ constexpr int sd_tw() {
 // transform) hold the spectrum of block r in v[] (sub-FFT DIF order).  The
 // group stage's 18 outputs go through the transform's LDS region one part at
 // a time (real, then imaginary), so v[] serves both roles.
-template <typename T, int L, int ST, int TWs, bool MAT>
+template <typename T, class S, int ST, int TWs, bool MAT>
 __device__ __forceinline__ void sd_forward(cpx<T>* v, bool g, int p, int r, int tau, cpx<T> w1,
-                                           const Roots<T, typename Sd<L>::Fs>& rs, T* region,
+                                           const Roots<T, typename S::Fs>& rs, T* region,
                                            bool act = true) {
-  using S = Sd<L>;
   using Fs = typename S::Fs;
   constexpr int LS = S::LS;
   cpx<T> m8{(T)0, (T)0};
-  if (g) sd_group_fwd<T, L>(v, w1, m8);
+  if (g) sd_group_fwd<T, S::L>(v, w1, m8);
   const bool mir = g && p != 0 && p != LS / 2;
   const int pd = lds_pad(p), pm = lds_pad(LS - p);
   constexpr int BL = LS + LS / 16;  // padded length of one block
@@ -122,11 +127,10 @@ __device__ __forceinline__ void sd_forward(cpx<T>* v, bool g, int p, int r, int 
 // r in v[] (sub-FFT DIF order); afterwards group-stage threads (g, group q)
 // hold L times the odd extension at positions q + LS m in v[].  w1 = W_L^q and
 // rs (the sub-FFT roots, Roots::load_inv) are loaded by the caller up front.
-template <typename T, int L, int ST, int TWs, bool MAT>
+template <typename T, class S, int ST, int TWs, bool MAT>
 __device__ __forceinline__ void sd_inverse(cpx<T>* v, bool g, int q, int r, int tau, cpx<T> w1,
-                                           const Roots<T, typename Sd<L>::Fs>& rs, T* region,
+                                           const Roots<T, typename S::Fs>& rs, T* region,
                                            bool act = true) {
-  using S = Sd<L>;
   using Fs = typename S::Fs;
   constexpr int LS = S::LS;
   constexpr int BL = LS + LS / 16;
@@ -148,7 +152,7 @@ __device__ __forceinline__ void sd_inverse(cpx<T>* v, bool g, int q, int r, int 
       });
     }
     __syncthreads();
-    if (g) sd_group_inv<T, L>(v, w1);
+    if (g) sd_group_inv<T, S::L>(v, w1);
     return;
   }
   T* base = region + lds_pad(r * LS) * ST;
@@ -170,7 +174,7 @@ __device__ __forceinline__ void sd_inverse(cpx<T>* v, bool g, int q, int r, int 
     }
     __syncthreads();
   }
-  if (g) sd_group_inv<T, L>(v, w1);
+  if (g) sd_group_inv<T, S::L>(v, w1);
 }
 
 // Spectrum of one row from the pairs of pass B (pair_index layout): P2/2 - i P1/2
@@ -178,11 +182,10 @@ __device__ __forceinline__ void sd_inverse(cpx<T>* v, bool g, int q, int r, int 
 // (msl, -1 where the frequency is L/2) with the sign of odd symmetry.  Every
 // load is unconditional (clamped to a valid address, the value then selected
 // or scaled by 0), so that all of them are in flight at once.
-template <typename T, int L>
+template <typename T, class S>
 __device__ __forceinline__ void sd_load_spectrum(cpx<T>* v, const T* __restrict__ P, int row,
                                                  bool vr, int r, int tau, int rows,
                                                  const int32_t* __restrict__ msl) {
-  using S = Sd<L>;
   using Fs = typename S::Fs;
   using V2 = typename Vec2<T>::type;
   constexpr int LS = S::LS, TS = S::TS;
@@ -219,11 +222,10 @@ __device__ __forceinline__ void sd_load_spectrum(cpx<T>* v, const T* __restrict_
 // the duplicates of the self-mirrored groups 0 and LS/2), stored as ZT; with
 // st given, the stored values are also staged there (index j - 1).  The mask
 // bytes are loaded first, all at once.
-template <typename T, int L, typename ZT>
+template <typename T, class S, typename ZT>
 __device__ __forceinline__ void sd_store_z(const cpx<T>* v, int q, int row, bool vr, int n1,
                                            const uint8_t* __restrict__ mask, ZT* __restrict__ z,
                                            double* st) {
-  using S = Sd<L>;
   const size_t rb = (size_t)(vr ? row : 0) * n1;
   static_for<2>([&](auto hh) {  // two halves of 8 registers
     constexpr int m0 = decltype(hh)::value * 8;
@@ -253,22 +255,22 @@ __device__ __forceinline__ void sd_store_z(const cpx<T>* v, int q, int row, bool
 // --------------------------------------------------------------------------
 // Pass A: row pairs (ra, rb) -> Q (strip-tiled), one row pair per block.
 // --------------------------------------------------------------------------
-template <typename T, int L>
-__global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_fwd(
+template <typename T, class S>
+__global__ __launch_bounds__(sd_per_block<S>() * S::TPD) void k_sd_rows_fwd(
     const double* __restrict__ v, const double* __restrict__ sig, T* __restrict__ Q,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS, int n1, int n2,
     const Members mb) {
-  using S = Sd<L>;
-  __shared__ T lds[S::LEN];
+  constexpr int ND = sd_per_block<S>();
+  __shared__ T lds[ND * S::LEN];
   {  // member of a batched launch (grid dimension z); offsets in doubles
     const size_t mo = mb.off(blockIdx.z);
     v += mo;
     if (sig) sig += mo;
     Q += mo * (sizeof(double) / sizeof(T));
   }
-  // (d = 0: the pair's index in a vector register, as in pass C)
+  // (ND = 1: d = 0, the pair's index in a vector register as in pass C)
   const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
-  const int pair = blockIdx.x + d;
+  const int pair = blockIdx.x * ND + d;
   const int ra = 2 * pair, rb = ra + 1;
   const bool va = ra < n2, vb = rb < n2;
   const bool g = tg < S::NG;
@@ -294,7 +296,8 @@ __global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_fwd(
       reg[m].im = sb * b;
     });
   }
-  sd_forward<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds);
+  sd_forward<T, S, 1, sd_tw<S, 1>(), true>(reg, g, tg, r, tau, w1, rs,
+                                           lds + (ND > 1 ? d * S::LEN : 0));
   if (!va) return;
   const T s = (T)(0.5 * (sig ? *sig : 1.0));
   const int hp = (n2 + 1) >> 1;
@@ -314,18 +317,18 @@ __global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_fwd(
 // Pass B: slot-column pairs (2c, 2c+1) of Q -> (P1, P2) pairs, one column pair
 // per block.
 // --------------------------------------------------------------------------
-template <typename T, int L>
-__global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(3))) void k_sd_cols(
+template <typename T, class S>
+__global__ __launch_bounds__(SdCols<S>::THR) __attribute__((amdgpu_waves_per_eu(3))) void k_sd_cols(
     const T* __restrict__ Q, T* __restrict__ P, const T* __restrict__ lamx_slot,
     const T* __restrict__ lamy_blk, const cpx<T>* __restrict__ twL,
     const cpx<T>* __restrict__ twS, int n1, int n2, T kx, T ky, T dpen, T halfK,
     const Members mb, const double* __restrict__ mk) {
-  using S = Sd<L>;
-  constexpr int TWs = sd_tw<L, 1>();
+  constexpr int BC = SdCols<S>::BC;
+  constexpr int TWs = sd_tw<S, BC>();
   using Fs = typename S::Fs;
   using V2 = typename Vec2<T>::type;
-  __shared__ T lds[(SdCols<L>::CONC ? 2 : 1) * S::LEN];
-  __shared__ T stash[S::PS * S::TPD];  // rho_b between the two inverse sweeps
+  __shared__ T lds[(SdCols<S>::CONC ? 2 : 1) * BC * S::LEN];
+  __shared__ T stash[BC * S::PS * S::TPD];  // rho_b between the two inverse sweeps
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     const size_t mt = mo * (sizeof(double) / sizeof(T));
@@ -336,12 +339,13 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
       ky = (T)mk[mo + 1];
     }
   }
-  constexpr bool CONC = SdCols<L>::CONC;
+  constexpr bool CONC = SdCols<S>::CONC;
   const int tid = threadIdx.x;
   // set h = 1 (CONC only) takes the second inverse sweep
-  const int h = CONC ? tid / S::TPD : 0;
-  const int tg = tid - h * S::TPD;
-  const int ca = 2 * xcd_remap(blockIdx.x, gridDim.x), cb = ca + 1;
+  const int h = CONC ? tid / (BC * S::TPD) : 0;
+  const int tl = tid - h * (BC * S::TPD);
+  const int b = tl % BC, tg = tl / BC;
+  const int ca = 2 * (xcd_remap(blockIdx.x, gridDim.x) * BC + b), cb = ca + 1;
   const int ld = n1 + 1, hp = (n2 + 1) >> 1;
   const bool va = ca < ld;  // ld even: both columns or neither
   const bool f0 = h == 0;   // threads of the forward sweep
@@ -364,18 +368,18 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
       reg[m].im = sgn * q.y;
     });
   }
-  T* my = lds + h * S::LEN;  // one region per set
+  T* my = lds + h * (BC * S::LEN) + b;  // regions interleaved (stride BC), one group per set
   {
     Roots<T, Fs> rs;  // (loaded per sweep: held across the kernel they cost occupancy)
     rs.load_fwd(tau, twS);
-    sd_forward<T, L, 1, TWs, false>(reg, g && f0, tg, r, tau, w1, rs, my, f0);
+    sd_forward<T, S, BC, TWs, false>(reg, g && f0, tg, r, tau, w1, rs, my, f0);
   }
   // spectrum = 2 rho_b - 2i rho_a; rho_b waits in LDS for the second column
   // (in registers it would cost a wavefront of occupancy)
   // The y eigenvalues stay in registers for the second column (a block of
   // 2.25 wavefronts is held to 3 per SIMD by its LDS anyway).
   const T* lamy = lamy_blk + r * S::LS;
-  T* rb = stash + tg;
+  T* rb = stash + tg * BC + b;
   T ly[S::PS];
   static_for<S::PS>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     static_for<S::PS>([&](auto ee) {
       constexpr int e = decltype(ee)::value;
       const T rho_a = (T)-0.5 * reg[e].im;
-      rb[e * S::TPD] = (T)0.5 * reg[e].re;
+      rb[e * S::TPD * BC] = (T)0.5 * reg[e].re;
       const T e1 = (T)1 - lxa - ly[e];
       const T e2 = e1 + dpen;
       const T q = halfK * rho_a / (e1 * e2);
@@ -402,7 +406,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
         constexpr int e = decltype(ee)::value;
         const T e1 = (T)1 - lxb - ly[e];
         const T e2 = e1 + dpen;
-        const T q = halfK * rb[e * S::TPD] / (e1 * e2);
+        const T q = halfK * rb[e * S::TPD * BC] / (e1 * e2);
         reg[e].re = q * e1;
         reg[e].im = -q * e2;
       });
@@ -410,7 +414,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     {
       Roots<T, Fs> rs;
       rs.load_inv(tau, twS);
-      sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+      sd_inverse<T, S, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
     }
     if (g && va) {
       const int cw = f0 ? ca : cb;
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+    sd_inverse<T, S, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
   }
   if (g && va) {
     static_for<16>([&](auto mm) {
@@ -444,14 +448,14 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
     constexpr int e = decltype(ee)::value;
     const T e1 = (T)1 - lxb - ly[e];
     const T e2 = e1 + dpen;
-    const T q = halfK * rb[e * S::TPD] / (e1 * e2);
+    const T q = halfK * rb[e * S::TPD * BC] / (e1 * e2);
     reg[e].re = q * e1;
     reg[e].im = -q * e2;
   });
   {
     Roots<T, Fs> rs;
     rs.load_inv(tau, twS);
-    sd_inverse<T, L, 1, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
+    sd_inverse<T, S, BC, TWs, false>(reg, g, tg, r, tau, w1, rs, my);
   }
   if (g && va) {
     static_for<16>([&](auto mm) {
@@ -469,22 +473,22 @@ __global__ __launch_bounds__(SdCols<L>::THR) __attribute__((amdgpu_waves_per_eu(
 // Pass C: one row per transform and block; the inverse sweep of
 // P2/2 - i P1/2 gives (P1 S_x) + i (P2 S_x), combined by the mask into z.
 // --------------------------------------------------------------------------
-template <typename T, int L>
-__global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_inv(
+template <typename T, class S>
+__global__ __launch_bounds__(sd_per_block<S>() * S::TPD) void k_sd_rows_inv(
     const T* __restrict__ P, const uint8_t* __restrict__ mask, double* __restrict__ z,
     const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS,
     const int32_t* __restrict__ msl, int n1, int n2, const Members mb) {
-  using S = Sd<L>;
-  __shared__ T lds[S::LEN];
+  constexpr int ND = sd_per_block<S>();
+  __shared__ T lds[ND * S::LEN];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     P += mo * (sizeof(double) / sizeof(T));
     z += mo;
   }
-  // (d = 0: the row's index in a vector register; with a scalar one the compiler
+  // (ND = 1: d = 0, the row's index in a vector register; with a scalar one the compiler
   // keeps fewer of the spectrum's loads in flight, 27.4 -> 28.1 us at 2047^2)
   const int d = threadIdx.x / S::TPD, tg = threadIdx.x % S::TPD;
-  const int row = blockIdx.x + d;
+  const int row = blockIdx.x * ND + d;
   const bool vr = row < n2;
   const bool g = tg < S::NG;
   const int r = tg / S::TS, tau = tg % S::TS;
@@ -492,9 +496,10 @@ __global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_inv(
   const cpx<T> w1 = twL[g ? tg : 0];
   Roots<T, typename S::Fs> rs;
   rs.load_inv(tau, twS);
-  sd_load_spectrum<T, L>(reg, P, row, vr, r, tau, n2, msl);
-  sd_inverse<T, L, 1, sd_tw<L, 1>(), true>(reg, g, tg, r, tau, w1, rs, lds);
-  if (g) sd_store_z<T, L, double>(reg, tg, row, vr, n1, mask, z, nullptr);
+  sd_load_spectrum<T, S>(reg, P, row, vr, r, tau, n2, msl);
+  sd_inverse<T, S, 1, sd_tw<S, 1>(), true>(reg, g, tg, r, tau, w1, rs,
+                                           lds + (ND > 1 ? d * S::LEN : 0));
+  if (g) sd_store_z<T, S, double>(reg, tg, row, vr, n1, mask, z, nullptr);
 }
 
 // --------------------------------------------------------------------------
@@ -508,9 +513,9 @@ __global__ __launch_bounds__(Sd<L>::TPD) void k_sd_rows_inv(
 // and above L/2 are zero on input and unused on output, known at compile time.
 // ZT: storage type of z (FP32 storage rounds z before the product uses it).
 // --------------------------------------------------------------------------
-template <int L>
+template <class S>
 struct SdMvCfg {
-  using S = Sd<L>;
+  static constexpr int L = S::L;
   using F = Fft<L, fft_pts(L)>;  // convolution engine
   // Up to L = 2048 (grids of at most 1023 rows, too few row pairs to fill the
   // GPU) the two sine transforms of a row pair run at once, on 2 TPD
@@ -543,18 +548,18 @@ struct SdMvCfg {
   }
 };
 
-template <typename T, int L, typename ZT = double>
-__global__ __launch_bounds__(SdMvCfg<L>::THR) __attribute__((amdgpu_waves_per_eu(SdMvCfg<L>::CONC ? 3 : 4)))
+template <typename T, class S, typename ZT = double>
+__global__ __launch_bounds__(SdMvCfg<S>::THR) __attribute__((amdgpu_waves_per_eu(SdMvCfg<S>::CONC ? 3 : 4)))
 void k_sd_rows_inv_mv(
     const T* __restrict__ P, const uint8_t* __restrict__ mask, ZT* __restrict__ z,
     double* __restrict__ t, const cpx<T>* __restrict__ twL, const cpx<T>* __restrict__ twS,
     const int32_t* __restrict__ msl, const cpx<double>* __restrict__ tw64,
     const double* __restrict__ sym, double coef, double dpen, const double* __restrict__ sub,
     double theta, int n1, int n2, const Members mb, const double* __restrict__ mk) {
-  using S = Sd<L>;
-  using M = SdMvCfg<L>;
+  constexpr int L = S::L;
+  using M = SdMvCfg<S>;
   using F = typename M::F;
-  constexpr int TWs = sd_tw<L, 1>();
+  constexpr int TWs = sd_tw<S, 1>();
   __shared__ double lds[M::template lds_doubles<T>()];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
@@ -582,9 +587,9 @@ void k_sd_rows_inv_mv(
     const cpx<T> w1 = twL[g ? th : 0];
     Roots<T, typename S::Fs> rs;
     rs.load_inv(tau, twS);
-    if (act) sd_load_spectrum<T, L>(reg, P, row, vr, r, tau, n2, msl);
-    sd_inverse<T, L, 1, TWs, true>(reg, g, th, r, tau, w1, rs, region, act);
-    if (g) sd_store_z<T, L, ZT>(reg, th, row, vr, n1, mask, z, lds + h * (L / 2));
+    if (act) sd_load_spectrum<T, S>(reg, P, row, vr, r, tau, n2, msl);
+    sd_inverse<T, S, 1, TWs, true>(reg, g, th, r, tau, w1, rs, region, act);
+    if (g) sd_store_z<T, S, ZT>(reg, th, row, vr, n1, mask, z, lds + h * (L / 2));
     __syncthreads();
   } else {
     const bool act = tid < S::TPD;
@@ -605,10 +610,10 @@ void k_sd_rows_inv_mv(
       const cpx<T> w1 = twL[g ? th : 0];
       Roots<T, typename S::Fs> rs;
       rs.load_inv(tau, twS);
-      if (act) sd_load_spectrum<T, L>(reg, P, row, vr, r, tau, n2, msl);
-      sd_inverse<T, L, 1, TWs, true>(reg, g, th, r, tau, w1, rs, region, act);
+      if (act) sd_load_spectrum<T, S>(reg, P, row, vr, r, tau, n2, msl);
+      sd_inverse<T, S, 1, TWs, true>(reg, g, th, r, tau, w1, rs, region, act);
       // (sd_inverse ends with a barrier: row b's staged z may replace the region)
-      if (g) sd_store_z<T, L, ZT>(reg, th, row, vr, n1, mask, z, lds + h * (L / 2));
+      if (g) sd_store_z<T, S, ZT>(reg, th, row, vr, n1, mask, z, lds + h * (L / 2));
     }
     __syncthreads();
   }

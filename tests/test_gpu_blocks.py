@@ -21,7 +21,7 @@ from workloads.three_d import ellipsoid_mask
 pytestmark = pytest.mark.gpu
 
 rsfde = pytest.importorskip("paper_2102_11576_amd")
-from paper_2102_11576_amd import RsfdePlan  # noqa: E402
+from paper_2102_11576_amd import RsfdePlan, make_opts  # noqa: E402
 
 DEV = "cuda:0"
 
@@ -131,3 +131,27 @@ def test_matvec_column_pairs(shape):
         g = out.cpu().numpy()
     assert np.abs(w - ref).max() <= 1e-13 * nm * np.abs(V).max()
     assert g[0] == 7.0 and g[-2] == 7.0 and g[-1] == 7.0
+
+
+# The symmetric transform of 2048 points: 8 points per thread up to 1023 lines
+# (511 in FP32), 16 beyond, in either direction, with an odd last row pair and
+# column pair in both forms; and a product fused behind the last pass (a step)
+@pytest.mark.parametrize("n1,n2", [(1023, 511), (511, 1023), (1023, 1023), (1023, 2047),
+                                   (2047, 1023), (1023, 1), (1, 1023)])
+def test_sine_transform_of_many_lines(n1, n2):
+    box = (0.0, 1.0, 0.0, 1.0)
+    mask = domain_mask(n1, n2, box, SHAPES["ellipse"](0.5, 0.5, 0.45, 0.3, 20.0))
+    p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+    V = np.random.default_rng(n1 + 5 * n2).standard_normal((n2, n1))
+    ref = O.precond_apply_fft(p, V)
+    b = O.rhs(p, np.abs(V) * mask, O.F_LOGISTIC)
+    with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16) as pl:
+        z64 = pl.precond(_t(V)).cpu().numpy().reshape(n2, n1)
+        z32 = pl.precond(_t(V), precision="fp32").cpu().numpy().reshape(n2, n1)
+        outs = [pl.step(_t(np.abs(V) * mask), None, O.F_LOGISTIC,
+                        make_opts(30, 10000, 1e-8, precision))[0].cpu().numpy().reshape(n2, n1)
+                for precision in ("fp64", "fp32")]
+    assert_precond(z64, ref, p, "fp64")
+    assert_precond(z32, ref, p, "fp32")
+    for u in outs:
+        assert np.linalg.norm(b - O.matvec_fast(p, u)) <= (1e-8 + 1e-12) * np.linalg.norm(b)
