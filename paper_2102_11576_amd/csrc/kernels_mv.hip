@@ -27,10 +27,14 @@ struct MvCfg {
     return true;
   }
   static constexpr int TPF = F::TPF;
-  // Column passes of small views exchange both parts at once (their LDS does not
-  // limit them): 511^2 15.2 -> 14.1 us a product.  Larger views and the row passes
-  // keep the smaller region (row pass at 255^3 93 -> 96 us).
+  // Exchanges of both parts at once where twice the LDS does not limit the pass:
+  // column passes of small views (511^2 15.2 -> 14.1 us a product), and every pass
+  // up to L = 256, whose four points per thread take three exchanges where 16
+  // points took one (127^3 49.4 -> 43.8 us, 46.4 with 16 points; 100^3 36.9 -> 32.0).
+  // Longer row passes and columns of large views keep the smaller region (row pass
+  // at 255^3 93 -> 96 us, column passes 302 -> 317 us a product).
   static constexpr bool CXS = fft_cx(L);
+  static constexpr bool CX = L <= 256;
   static constexpr int BR = row_ffts(TPF);  // FFTs per row block
   static constexpr int THR_R = BR * TPF;
   // column pairs per column block: two at L = 1024 and 2048 (two-dimensional
@@ -52,7 +56,7 @@ __global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu
     const Members mb, const double* __restrict__ mk) {
   using C = MvCfg<L>;
   using F = typename C::F;
-  __shared__ double lds[C::BR * lds_len(L)];
+  __shared__ double lds[C::BR * lds_len(L, C::CX)];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     z += mo;
@@ -78,15 +82,15 @@ __global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu
       reg[e].im = (vb && in) ? z[ib0 + p] : 0.0;
     }
   });
-  double* my = lds + b * lds_len(L);
-  fft_forward<double, F>(reg, tau, tw, my);
+  double* my = lds + b * lds_len(L, C::CX);
+  fft_forward<double, F, true, 1, C::CX>(reg, tau, tw, my);
   static_for<F::PP>([&](auto ee) {
     constexpr int e = decltype(ee)::value;
     const double s = sym[F::pos(F::NS - 1, tau, e)] * coef;
     reg[e].re *= s;
     reg[e].im *= s;
   });
-  fft_inverse<double, F>(reg, tau, tw, my);
+  fft_inverse<double, F, true, 1, C::CX>(reg, tau, tw, my);
   const int hp = (n2 + 1) >> 1;
   // epilogue in groups of G registers: the group's loads (clamped addresses)
   // all in flight at once, then its stores
@@ -335,8 +339,8 @@ static hipError_t mv_cols_impl(const void* z, const double* t, double* out, cons
       return mv_cols_bc<L, C::BCS, C::CXS>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride,
                                    tiled, mb, mk, z32);
   }
-  return mv_cols_bc<L, C::BCL, false>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride, tiled,
-                               mb, mk, z32);
+  return mv_cols_bc<L, C::BCL, C::CX>(z, t, out, sym, twc, n1, n2, coef, mode, s, batch, bstride, tiled,
+                                      mb, mk, z32);
 }
 
 #define RSFDE_L_CASES(X) \
