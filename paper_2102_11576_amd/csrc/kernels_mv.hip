@@ -35,8 +35,13 @@ struct MvCfg {
   // at 255^3 93 -> 96 us, column passes 302 -> 317 us a product).
   static constexpr bool CXS = fft_cx(L);
   static constexpr bool CX = L <= 256;
-  static constexpr int BR = row_ffts(TPF);  // FFTs per row block
-  static constexpr int THR_R = BR * TPF;
+  // FFTs per row block; BR2 where one per block would number more blocks than the
+  // GPU has CUs and two per block would not (L = 2048): every CU then runs one
+  // block instead of some of them two.  Product, one / two per block: 600 x 513 20.1
+  // / 20.6 us, 600 x 530 21.6 / 20.8, 1000 x 700 25.8 / 24.5, 1000 x 1000 29.1 / 28.5;
+  // outside 1000 x 500 18.7 / 20.1, 1000 x 1500 35.7 / 37.3.
+  static constexpr int BR = row_ffts(TPF);
+  static constexpr int BR2 = L == 2048 ? 2 : BR;
   // column pairs per column block: two at L = 1024 and 2048 (two-dimensional
   // grids of 511 or 1023 columns: more, smaller blocks spread them over more
   // CUs); up to L = 512 by the size of the view
@@ -48,15 +53,15 @@ struct MvCfg {
 // Row pass.  Block = BR FFTs, FFT b handles rows 2*pair and 2*pair+1.
 // TO: out in the strip-tiled layout.
 // --------------------------------------------------------------------------
-template <int L, bool TO>
-__global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_rows(
+template <int L, int BR, bool TO>
+__global__ __launch_bounds__(MvCfg<L>::TPF* BR) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_rows(
     const double* __restrict__ z, const uint8_t* __restrict__ mask, double* __restrict__ out,
     const double* __restrict__ sym, const cpx<double>* __restrict__ tw, int n1, int n2,
     double coef, double dpen, int mode, const double* __restrict__ sub, double theta,
     const Members mb, const double* __restrict__ mk) {
   using C = MvCfg<L>;
   using F = typename C::F;
-  __shared__ double lds[C::BR * lds_len(L, C::CX)];
+  __shared__ double lds[BR * lds_len(L, C::CX)];
   {  // member of a batched launch (grid dimension z)
     const size_t mo = mb.off(blockIdx.z);
     z += mo;
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(MvCfg<L>::THR_R) __attribute__((amdgpu_waves_per_eu
   }
   const int tid = threadIdx.x;
   const int b = tid / F::TPF, tau = tid % F::TPF;
-  const int pair = blockIdx.x * C::BR + b;
+  const int pair = blockIdx.x * BR + b;
   const int ra = 2 * pair, rb = 2 * pair + 1;
   const bool va = ra < n2, vb = rb < n2;
   const size_t ia0 = (size_t)(va ? ra : 0) * n1, ib0 = (size_t)(vb ? rb : 0) * n1;
@@ -287,15 +292,20 @@ static hipError_t mv_rows_impl(const double* z, const uint8_t* mask, double* out
                                const Members& mb, const double* mk) {
   using C = MvCfg<L>;
   const int pairs = (n2 + 1) / 2;
-  const int blocks = (pairs + C::BR - 1) / C::BR;
   if (mb.n < 1 || mb.n > kMaxBatch) return hipErrorInvalidValue;
-  const dim3 grid(blocks, 1, mb.n);
-  if (tiled)
-    hipLaunchKernelGGL((k_mv_rows<L, true>), grid, dim3(C::THR_R), 0, s, z, mask, out, sym,
-                       (const cpx<double>*)tw, n1, n2, coef, dpen, mode, sub, theta, mb, mk);
-  else
-    hipLaunchKernelGGL((k_mv_rows<L, false>), grid, dim3(C::THR_R), 0, s, z, mask, out,
-                       sym, (const cpx<double>*)tw, n1, n2, coef, dpen, mode, sub, theta, mb, mk);
+  auto go = [&](auto br) {
+    constexpr int BR = decltype(br)::value;
+    const dim3 grid((pairs + BR - 1) / BR, 1, mb.n), thr(BR * C::TPF);
+    if (tiled)
+      hipLaunchKernelGGL((k_mv_rows<L, BR, true>), grid, thr, 0, s, z, mask, out, sym,
+                         (const cpx<double>*)tw, n1, n2, coef, dpen, mode, sub, theta, mb, mk);
+    else
+      hipLaunchKernelGGL((k_mv_rows<L, BR, false>), grid, thr, 0, s, z, mask, out, sym,
+                         (const cpx<double>*)tw, n1, n2, coef, dpen, mode, sub, theta, mb, mk);
+  };
+  const long one = (long)pairs * mb.n, two = (long)((pairs + 1) / 2) * mb.n;
+  if (C::BR2 != C::BR && one > kSmallGridBlocks && two <= kSmallGridBlocks) go(std::integral_constant<int, C::BR2>{});
+  else go(std::integral_constant<int, C::BR>{});
   return hipGetLastError();
 }
 

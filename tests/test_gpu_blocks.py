@@ -155,3 +155,18 @@ def test_sine_transform_of_many_lines(n1, n2):
     assert_precond(z32, ref, p, "fp32")
     for u in outs:
         assert np.linalg.norm(b - O.matvec_fast(p, u)) <= (1e-8 + 1e-12) * np.linalg.norm(b)
+
+
+# Row pass of the product with 2048 points: one transform per block up to 256 row
+# pairs and beyond 512, two between
+@pytest.mark.parametrize("n1,n2", [(520, 512), (1023, 513), (520, 515), (520, 1024), (520, 1025)])
+def test_matvec_row_blocks(n1, n2):
+    box = (0.0, 1.0, 0.0, 1.0)
+    mask = domain_mask(n1, n2, box, SHAPES["disk"](0.5, 0.5, 0.4))
+    p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+    V = np.random.default_rng(n1 + n2).standard_normal((n2, n1))
+    nm = 1.0 + p.d + 2 * np.abs(p.cx * O.toeplitz_first_column(p.alpha1, n1)).sum() \
+        + 2 * np.abs(p.cy * O.toeplitz_first_column(p.alpha2, n2)).sum()
+    with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2) as pl:
+        w = pl.matvec(_t(V)).cpu().numpy().reshape(n2, n1)
+    assert np.abs(w - O.matvec(p, V)).max() <= 1e-13 * nm * np.abs(V).max()
