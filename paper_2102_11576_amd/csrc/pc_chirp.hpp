@@ -40,6 +40,17 @@ struct CdCfg {
   static constexpr int BCL = (256 / TPF) > 16 ? 16 : ((256 / TPF) > 0 ? (256 / TPF) : 1);
   static constexpr int BCS = L <= 512 && col_ffts_small(TPF) < BCL ? col_ffts_small(TPF) : BCL;
   static constexpr int THR_R = BR * TPF;
+  // The column pass's three transforms written out instead of in a loop: where the
+  // loop's reloads of the tables cost more than the shorter code gives.  Whole
+  // preconditioner, loop / written out: FP64 1000^2 90.4 / 89.0 us, 2000 x 700 129.8
+  // / 128.0 (L = 2048), 64 x 2049 61.1 / 59.9 (L = 8192); FP32 1400^2 128.5 / 125.2,
+  // 2000^2 183.4 / 176.6 (L = 4096).  Elsewhere the loop: FP64 600 x 1800 132.9 /
+  // 135.7 (L = 4096), FP32 2000 x 700 80.7 / 85.3 (L = 2048), 20 x 20 x 2100 122 /
+  // 138 (L = 8192), and every tiled form (FP32 4000 x 1500 295 / 306).
+  template <typename T, bool TL>
+  static constexpr bool unrolled() {
+    return !TL && (sizeof(T) == 8 ? L == 2048 || L == 8192 : L == 4096);
+  }
   // A view that the large column blocks cannot spread over the CUs.
   static bool small_cols(long cols, long copies) {
     return BCS < BCL && (cols + BCL - 1) / BCL * copies < kSmallGridBlocks;
@@ -127,6 +138,34 @@ __global__ __launch_bounds__(CdCfg<L>::TPF* BC) void k_cd_cols(
     reg[e].re = (vc && p < n2) ? in[TL ? tile_index(p, c, hp) : (size_t)p * n1 + c] : T(0);
     reg[e].im = T(0);
   });
+  if constexpr (C::template unrolled<T, TL>()) {
+    // (the denominators are formed before w: the other order held 256 VGPRs and
+    // more at L = 2048 in FP64 where this one takes 218)
+    chirp_dst<T, F, C::CX, BC>(reg, tau, chn, khat, tw, my, n2);
+    const double ax = 1.0 - kx * (vc ? lamx[c] : 0.0);
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const int p = F::pos(0, tau, e);
+      const T e1 = (T)(ax - ky * (p < n2 ? lamy[p] : 0.0));
+      w[e] = p < n2 ? reg[e].re : T(0);
+      reg[e].re = w[e] / e1;
+    });
+    chirp_dst<T, F, C::CX, BC>(reg, tau, chn, khat, tw, my, n2);
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const int p = F::pos(0, tau, e);
+      if (vc && p < n2) Y1[TL ? tile_index(p, c, hp) : (size_t)p * n1 + c] = reg[e].re;
+      const T e2 = (T)(ax + dpen - ky * (p < n2 ? lamy[p] : 0.0));
+      reg[e].re = w[e] / e2;
+    });
+    chirp_dst<T, F, C::CX, BC>(reg, tau, chn, khat, tw, my, n2);
+    static_for<F::PP>([&](auto ee) {
+      constexpr int e = decltype(ee)::value;
+      const int p = F::pos(0, tau, e);
+      if (vc && p < n2) Y2[TL ? tile_index(p, c, hp) : (size_t)p * n1 + c] = reg[e].re;
+    });
+    return;
+  }
   const double ax = 1.0 - kx * (vc ? lamx[c] : 0.0);
   // The three transforms by one copy of the code (half the instructions to
   // fetch; 256^2 13.9 -> 13.4 us): the forward one, then w / E1 and w / E2.
