@@ -133,8 +133,8 @@ typedef struct {
  * powers of two the FP64 / FP32 preconditioner runs its sine transforms as
  * FFTs of the odd extension (length 2(n+1)); otherwise as chirp convolutions
  * (Bluestein) on power-of-two FFTs of length >= 2n-1 (symmetric sweeps of
- * length >= 4n for n > 2048), about four times the arithmetic for the same
- * result.
+ * length >= 4n for axes of n > 2048 points and enough lines), about four times
+ * the arithmetic for the same result.
  * Errors: EINVAL, ENOMEM, EHIP, EUNSUPPORTED.
  */
 int rsfde_setup(rsfde_plan* out, const rsfde_grid* grid, double alpha1, double alpha2,

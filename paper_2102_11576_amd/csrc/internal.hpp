@@ -203,14 +203,31 @@ struct CdDir {
   int L;
   const void *chn, *khat, *tw, *twS;
 };
-// Length L of the symmetric form for lines of n points where it is used, 0 where
-// the plain form is: lines of more than 2048 points, whose plain transform is one
-// 8192-point FFT per block and reads single columns.  Whole preconditioner, plain
-// -> symmetric: 4000^2 FP64 1859 -> 1122 us, FP32 1092 -> 738; 3000 x 1000 FP64
-// 317 -> 247.  Below, the symmetric form has no lead: 2000^2 (L = 8192) 305 -> 313
-// us, 1000 x 700 (L = 4096) 82 -> 77 in FP64 and a larger FP32 error, 300 x 200 27
-// -> 32.
-constexpr int cd_sym_length(int n) { return n > 2048 ? 16384 : 0; }
+// Length L of the symmetric form for an axis of n points and `lines` lines where it
+// is used, 0 where the plain form is.
+//
+// Axes of at most 2048 points take the plain form.  In FP64 the symmetric one is the
+// faster there by some per cent at L = 4096 (1000 x 700 82 -> 77 us when both were
+// measured, the plain one 74 since) and not at the neighbouring lengths (2000^2, L =
+// 8192, 305 -> 313; 300 x 200, L = 2048, 27 -> 32); in FP32 its error is the larger.
+//
+// Beyond, the plain transform is one 8192-point FFT per block and reads single
+// columns: 4000^2 FP64 1859 -> 1122 us, FP32 1092 -> 738; 3000 x 1000 FP64 317 -> 247.
+// But two lines in one transform halve the blocks and lengthen each, which pays
+// only where the plain form's blocks outnumber what runs at once: one per CU in
+// FP64 and three in FP32, two lines per row in the last row pass, one per column.
+// Plain / symmetric: rows, FP64 4000 x 128 58.9 / 66.5 us, 4000 x 150 84.2 / 78.6;
+// FP32 3000 x 300 77.9 / 82.1, 3000 x 400 86.9 / 84.3.  Columns, FP64 256 x 2049
+// 73.2 / 85.1, 300 x 2049 137 / 99; in FP32 the symmetric column pass is level with
+// the plain one at 16 columns (44.5 / 44.4) and ahead of it from there.
+//
+// Error of the symmetric form against FP64 products, plain form = 1: FP32 0.7 to 0.95
+// over the whole result, on the penalty region alone (values dt/eta smaller) 1.05 to
+// 1.6, as two lines share a transform; FP64 1.00 and 1.0 to 1.15.
+constexpr int cd_sym_length(int n, int lines, bool rows, bool fp32) {
+  const int least = rows ? (fp32 ? 385 : 129) : (fp32 ? 1 : 257);
+  return n > 2048 && lines >= least ? 16384 : 0;
+}
 // W1, Y1, Y2: [n2][n1] arrays, or strip-tiled (tile_index).
 template <typename T>
 hipError_t launch_cd_rows_fwd(const CdDir& d, const double* v, const double* sig, T* W1, int n1,

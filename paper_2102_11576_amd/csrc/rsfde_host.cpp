@@ -373,37 +373,39 @@ hipError_t ensure_twiddles(Plan* P, int L, hipStream_t s) {
   return hipSuccess;
 }
 
-// The chirp tables of an axis of n points in both precisions: the symmetric
-// form where it is allowed (two-dimensional plans) and used (cd_sym_length),
-// the plain form of length L elsewhere.
-hipError_t chirp_dir(Plan* P, int n, int L, bool sym, CdDir (&d)[2], hipStream_t s) {
+// The chirp tables of an axis of n points and `lines` lines in both precisions: the
+// symmetric form where it is allowed (two-dimensional plans) and used
+// (cd_sym_length), the plain form of length L elsewhere.
+hipError_t chirp_dir(Plan* P, int n, int lines, bool rows, int L, bool sym, CdDir (&d)[2],
+                     hipStream_t s) {
   const std::vector<double> ch = chirp_values(n);
-  const std::vector<float> chf(ch.begin(), ch.end());
-  double* c64 = nullptr;
-  float* c32 = nullptr;
+  std::vector<double> kh;
   hipError_t e;
-  if ((e = upload(P, &c64, ch, s)) != hipSuccess || (e = upload(P, &c32, chf, s)) != hipSuccess)
-    return e;
-  const int Ls = sym ? cd_sym_length(n) : 0;
-  const int Lt = Ls ? Ls : L;
-  const std::vector<double> kh = Ls ? chirp_sym_khat(n, Ls) : chirp_khat(n, L);
-  if (kh.empty()) return hipErrorInvalidValue;
-  if ((e = ensure_twiddles(P, Lt, s)) != hipSuccess) return e;
-  if (Ls && (e = ensure_twiddles(P, Ls / 16, s)) != hipSuccess) return e;
-  for (int t = 0; t < 2; ++t) {
-    auto& tw = t == 0 ? P->tw64 : P->tw32;
-    void* k = nullptr;
-    if (t == 0) {
-      double* k64 = nullptr;
-      if ((e = upload(P, &k64, kh, s)) != hipSuccess) return e;
-      k = k64;
-    } else {
-      float* k32 = nullptr;
-      if ((e = upload(P, &k32, std::vector<float>(kh.begin(), kh.end()), s)) != hipSuccess) return e;
-      k = k32;
-    }
-    d[t] = CdDir{Lt, t == 0 ? (const void*)c64 : (const void*)c32, k, tw[Lt],
-                 Ls ? tw[Ls / 16] : nullptr};
+  for (int t = 0; t < 2; ++t) {  // FP64, FP32
+    const bool fp32 = t == 1;
+    const int Ls = sym ? cd_sym_length(n, lines, rows, fp32) : 0;
+    const int Lt = Ls ? Ls : L;
+    if (t == 0 || Lt != d[0].L) kh = Ls ? chirp_sym_khat(n, Ls) : chirp_khat(n, L);
+    if (kh.empty()) return hipErrorInvalidValue;
+    if ((e = ensure_twiddles(P, Lt, s)) != hipSuccess) return e;
+    if (Ls && (e = ensure_twiddles(P, Ls / 16, s)) != hipSuccess) return e;
+    auto& tw = fp32 ? P->tw32 : P->tw64;
+    auto put = [&](const std::vector<double>& v, const void*& out) {
+      hipError_t rc;
+      if (fp32) {
+        float* q = nullptr;
+        rc = upload(P, &q, std::vector<float>(v.begin(), v.end()), s);
+        out = q;
+      } else {
+        double* q = nullptr;
+        rc = upload(P, &q, v, s);
+        out = q;
+      }
+      return rc;
+    };
+    const void *chn = nullptr, *khat = nullptr;
+    if ((e = put(ch, chn)) != hipSuccess || (e = put(kh, khat)) != hipSuccess) return e;
+    d[t] = CdDir{Lt, chn, khat, tw[Lt], Ls ? tw[Ls / 16] : nullptr};
   }
   return hipSuccess;
 }
@@ -1566,8 +1568,8 @@ int rsfde_setup(rsfde_plan* out, const rsfde_grid* grid, double alpha1, double a
     const std::vector<double> lx = tau_eigs(tx), ly = tau_eigs(ty);
     if (upload(P, &P->lamx_n, lx, s) != hipSuccess || upload(P, &P->lamy_n, ly, s) != hipSuccess)
       return failx(__LINE__, RSFDE_ENOMEM);
-    if (chirp_dir(P, n1, P->Lgx, true, P->cdx, s) != hipSuccess ||
-        chirp_dir(P, n2, P->Lgy, true, P->cdy, s) != hipSuccess)
+    if (chirp_dir(P, n1, n2, true, P->Lgx, true, P->cdx, s) != hipSuccess ||
+        chirp_dir(P, n2, n1, false, P->Lgy, true, P->cdy, s) != hipSuccess)
       return failx(__LINE__, RSFDE_ENOMEM);
   }
   // BF16 / MFMA preconditioner: padded sine matrices, natural-order eigenvalues
@@ -1689,9 +1691,9 @@ int rsfde_setup3(rsfde_plan* out, const rsfde_grid3* grid, double alpha1, double
   for (int L : {P->Lcx, P->Lcy, P->Lcz, P->Ldx, P->Ldy, P->Ldz, P->Lgx, P->Lgy, P->Lgz})
     if (ensure_twiddles(P, L, s) != hipSuccess) return fail(RSFDE_ENOMEM);
   if (!pow2) {  // chirp tables per axis (FP64 and FP32)
-    if (chirp_dir(P, n[0], P->Lgx, false, P->cdx, s) != hipSuccess ||
-        chirp_dir(P, n[1], P->Lgy, false, P->cdy, s) != hipSuccess ||
-        chirp_dir(P, n[2], P->Lgz, false, P->cdz, s) != hipSuccess)
+    if (chirp_dir(P, n[0], 0, true, P->Lgx, false, P->cdx, s) != hipSuccess ||
+        chirp_dir(P, n[1], 0, false, P->Lgy, false, P->cdy, s) != hipSuccess ||
+        chirp_dir(P, n[2], 0, false, P->Lgz, false, P->cdz, s) != hipSuccess)
       return fail(RSFDE_ENOMEM);
   }
   // Section 4.1's eigenvalues: x in slot order folded with y into one value per

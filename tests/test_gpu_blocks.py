@@ -170,3 +170,21 @@ def test_matvec_row_blocks(n1, n2):
     with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2) as pl:
         w = pl.matvec(_t(V)).cpu().numpy().reshape(n2, n1)
     assert np.abs(w - O.matvec(p, V)).max() <= 1e-13 * nm * np.abs(V).max()
+
+
+# Axes of more than 2048 points on both sides of the number of lines from which the
+# symmetric form is used: rows 129 (FP64) and 385 (FP32), columns 257 (FP64; any in
+# FP32), with 4n = L in both directions and one direction in each form
+@pytest.mark.parametrize("n1,n2", [(2050, 128), (2049, 129), (2051, 384), (4096, 385), (256, 2049),
+                                   (257, 4096), (1, 2050), (2049, 1), (2049, 2050)])
+def test_chirp_forms_across_line_rule(n1, n2):
+    box = (0.0, 1.0, 0.0, 1.0)
+    mask = domain_mask(n1, n2, box, SHAPES["ellipse"](0.5, 0.5, 0.45, 0.3, 20.0))
+    p = O.Problem(n1, n2, box, 1.4, 1.7, 1.0, 0.6, 1e-6, 1.0 / 16, mask)
+    V = np.random.default_rng(n1 + 5 * n2).standard_normal((n2, n1))
+    with RsfdePlan(n1, n2, box, 1.4, 1.7, 1.0, 0.6, torch.as_tensor(mask), 1e-6, 1.0 / 16, 2) as pl:
+        z64 = pl.precond(_t(V)).cpu().numpy().reshape(n2, n1)
+        z32 = pl.precond(_t(V), precision="fp32").cpu().numpy().reshape(n2, n1)
+    ref = O.precond_apply_fft(p, V)
+    assert_precond(z64, ref, p, "fp64")
+    assert_precond(z32, ref, p, "fp32")
