@@ -96,10 +96,19 @@ struct KrylovState {
 };
 constexpr int kLdH = kMaxRestart + 1;
 
-// Reduction workspace: per-block partial sums [value][block], read by the
-// single-block finishing kernel launched after each streaming kernel.
+// Largest number of basis vectors one streaming launch handles; longer
+// restarts are processed in chunks of this size.
+constexpr int kChunk = 32;
+
+// Reduction workspace: rows of per-block partial sums [value][block], written by a
+// streaming kernel and read by the finishing kernel launched after it, or by the
+// kernel that uses the sums.  The orthogonalisation needs two regions of kChunk
+// rows, one per Gram-Schmidt pass, since one kernel reads the first pass's while
+// it writes the second's; they start at rows 0 and kRedSecond.
+constexpr int kRedSecond = kChunk + 1;
+constexpr int kRedRows = kRedSecond + kChunk + 1;
 struct RedWork {
-  double* partial;     // [kMaxRestart + 2][kMaxRedBlocks]
+  double* partial;     // [kRedRows][kMaxRedBlocks]
 };
 
 // ----------------------------- FFT kernels --------------------------------

@@ -11,10 +11,6 @@
 
 namespace rsfde {
 
-// Largest number of basis vectors one streaming launch handles; longer
-// restarts are processed in chunks of this size.
-constexpr int kChunk = 32;
-
 // ------------------------------ helpers -----------------------------------
 
 __device__ __forceinline__ double wave_sum(double v) {

@@ -25,10 +25,11 @@ inline int orth_blocks(size_t N) {
   return b < 1 ? 1 : (b > (size_t)kOrthSmallBlocks ? kOrthSmallBlocks : (int)b);
 }
 
-// Partials of the two Gram-Schmidt passes: apart, since one kernel reads the
-// first pass's while it writes the second's.
+// Partials of the two Gram-Schmidt passes.
+static_assert(kRedSecond >= kChunk && kRedRows >= kRedSecond + kChunk,
+              "two regions of kChunk rows in the reduction workspace");
 __device__ __forceinline__ double* orth_partials(const RedWork& rw, bool second) {
-  return rw.partial + (second ? (size_t)(kChunk + 1) * kMaxRedBlocks : 0);
+  return rw.partial + (second ? (size_t)kRedSecond * kMaxRedBlocks : 0);
 }
 
 // W consecutive values of a vector.

@@ -1312,7 +1312,7 @@ int alloc_common(Plan* P, const uint8_t* mask_dev, size_t slots, hipStream_t s,
     AL(P->t3, ld);
   }
   AL(P->ks, 1);
-  AL(P->rw.partial, (size_t)(kMaxRestart + 2) * kMaxRedBlocks);
+  AL(P->rw.partial, (size_t)kRedRows * kMaxRedBlocks);
   AL(P->gpart, (size_t)16 * 16 * kGramMaxTiles * kGramBlocks);
   AL(P->coef_d, (size_t)16 * 16 * kGramMaxTiles + 256);
 #undef AL
@@ -2243,7 +2243,7 @@ int rsfde_batch_setup(rsfde_batch* out, const rsfde_grid* grid, double alpha1, d
     o += r64(count_d);
   };
   take(Bt->o_ks, (sizeof(KrylovState) + 7) / 8);
-  take(Bt->o_part, (size_t)(kMaxRestart + 2) * kMaxRedBlocks);
+  take(Bt->o_part, (size_t)kRedRows * kMaxRedBlocks);
   take(Bt->o_k, 2);
   take(Bt->o_V, (size_t)(max_restart + 1) * ld);
   take(Bt->o_Z, (size_t)max_restart * ld);
