@@ -164,3 +164,27 @@ def test_batch_options_and_shapes_rejected():
             with pytest.raises(rsfde.RsfdeError) as ei:
                 bt.step(u, None, w.f_kind, make_opts(30, 100, 1e-8, sstep=0, **kw))
             assert ei.value.code == rsfde._lib.RSFDE_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("max_iters", [1, 5, 6, 7, 13, 24])
+def test_batched_iteration_cap(max_iters):
+    """Caps of one step, inside a cycle, at its end and in the next ones, with
+    members that converge after about 5, 10, 21 and 45 steps: each member's count,
+    status and iterate are the single plan's with the same options."""
+    w = make_config("c1", n=63, m=1)
+    ks = [1e-4, 1e-3, 1e-2, 1.0]
+    opts = make_opts(6, max_iters, 1e-8, sstep=0)
+    u0 = _t(np.stack([w.u0] * len(ks)))
+    with RsfdeBatch.from_workload(w, ks, ks) as bt:
+        u, sts = bt.step(u0, None, w.f_kind, opts, check=False)
+        u = u.cpu().numpy().reshape(len(ks), w.n2, w.n1)
+    for i, k in enumerate(ks):
+        with RsfdePlan.from_workload(w, kx=k, ky=k) as pl:
+            us, st = pl.step(_t(w.u0), None, w.f_kind, opts, check=False)
+            us = us.cpu().numpy().reshape(w.n2, w.n1)
+        assert (sts[i].iters, sts[i].restarts, sts[i].status) == (st.iters, st.restarts, st.status), i
+        assert sts[i].iters <= max_iters
+        assert np.abs(u[i] - us).max() <= 1e-12 * np.abs(us).max(), i
+    assert sts[3].iters == max_iters and sts[3].status == rsfde._lib.RSFDE_ENOTCONV
+    if max_iters >= 6:
+        assert sts[0].status == 0

@@ -80,3 +80,17 @@ def test_one_vector_step_around_the_length_limit(n1, n2):
     r = np.linalg.norm(b - O.matvec_fast(p, out)) / np.linalg.norm(b)
     assert r <= tol + 1e-12, r
     assert abs(st.iters - it_ref) <= 2, (st.iters, it_ref)
+
+
+# N = 1046529 (odd): 256 blocks, chunks of 32 and 16 vectors, and the one-pass form
+@pytest.mark.parametrize("reorth", [0, -1])
+def test_long_vectors_in_two_chunks(reorth):
+    w = make_config("c2", n=1023)
+    p = O.problem_from_workload(w)
+    tol = 1e-8
+    with RsfdePlan.from_workload(w, max_restart=48) as pl:
+        out, st = pl.step(_t(w.u0), None, w.f_kind, make_opts(48, 1000, tol, sstep=0, reorth=reorth))
+        out = out.cpu().numpy().reshape(w.n2, w.n1)
+    b = O.rhs(p, w.u0, w.f_kind)
+    assert np.linalg.norm(b - O.matvec_fast(p, out)) <= (tol + 1e-12) * np.linalg.norm(b)
+    assert st.iters > 32 and st.status == 0
