@@ -604,12 +604,15 @@ static hipError_t pc_cols_impl(const T* Q, T* P1, T* P2, const T* lamx, const T*
   auto go = [&](auto bc) {
     constexpr int BC = decltype(bc)::value;
     const dim3 g((pairs + BC - 1) / BC, 1, mb.n), t(BC * C::TPF);
-    if (tiled)
-      hipLaunchKernelGGL((k_pc_cols<T, L, BC>), g, t, 0, s, Q, P1, lamx, lamy, (const cpx<T>*)tw, n1,
-                         n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
-    else
-      hipLaunchKernelGGL((k_pc_cols_nat<T, L, BC>), g, t, 0, s, Q, P1, P2, lamx, lamy,
-                         (const cpx<T>*)tw, n1, n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac));
+    if constexpr (L < kSdMinL) {
+      if (tiled) {
+        hipLaunchKernelGGL((k_pc_cols<T, L, BC>), g, t, 0, s, Q, P1, lamx, lamy, (const cpx<T>*)tw,
+                           n1, n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_pc_cols_nat<T, L, BC>), g, t, 0, s, Q, P1, P2, lamx, lamy,
+                       (const cpx<T>*)tw, n1, n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac));
   };
   if (small_cols<L>(pairs, mb.n)) go(std::integral_constant<int, C::BCS>{});
   else go(std::integral_constant<int, C::BCL>{});
@@ -724,28 +727,30 @@ static hipError_t sd_rows_inv_mv_impl(const T* P, const uint8_t* mask, void* z, 
   return hipGetLastError();
 }
 
-// Pass selection: the symmetric form for the tiled layouts when its tables are
-// given and L >= kSdMinL, the plain FFT form otherwise.
+// Pass selection: natural layouts take the plain FFT form at every length, tiled
+// ones below kSdMinL; from there on tiled layouts take the symmetric form, whose
+// tables every plan of such lengths has.
 // f(Sd<L, points per thread>) for the points that the tables were made for.
 template <int L, class Fn>
 static hipError_t sd_form(const SdTabs& sd, Fn&& f) {
+  if (!sd.twS) return hipErrorInvalidValue;
   if constexpr (L == kSdManyL) {
     if (sd.many) return f(Sd<L, 16>{});
   }
   return f(Sd<L>{});
 }
+
 template <typename T, int L>
 static hipError_t rows_fwd_any(const double* v, const double* sig, T* Q, const void* tw, int n1,
                                int n2, bool tiled, hipStream_t s, const Members& mb,
                                const SdTabs& sd) {
-  if constexpr (L >= kSdMinL) {
-    if (tiled && sd.twS)
-      return sd_form<L>(sd, [&](auto f) {
-        return sd_rows_fwd_impl<T, decltype(f)>(v, sig, Q, tw, sd.twS, n1, n2, s, mb);
-      });
-  }
-  return tiled ? pc_rows_fwd_impl<T, L, true>(v, sig, Q, tw, n1, n2, s, mb)
-               : pc_rows_fwd_impl<T, L, false>(v, sig, Q, tw, n1, n2, s, mb);
+  if (!tiled) return pc_rows_fwd_impl<T, L, false>(v, sig, Q, tw, n1, n2, s, mb);
+  if constexpr (L >= kSdMinL)
+    return sd_form<L>(sd, [&](auto f) {
+      return sd_rows_fwd_impl<T, decltype(f)>(v, sig, Q, tw, sd.twS, n1, n2, s, mb);
+    });
+  else
+    return pc_rows_fwd_impl<T, L, true>(v, sig, Q, tw, n1, n2, s, mb);
 }
 
 template <typename T, int L>
@@ -754,7 +759,7 @@ static hipError_t cols_any(const T* Q, T* P1, T* P2, const T* lamx, const T* lam
                            bool tiled, hipStream_t s, const Members& mb, const double* mk,
                            const SdTabs& sd) {
   if constexpr (L >= kSdMinL) {
-    if (tiled && sd.twS)
+    if (tiled)
       return sd_form<L>(sd, [&](auto f) {
         return sd_cols_impl<T, decltype(f)>(Q, P1, lamx, lamy, tw, sd.twS, n1, n2, kx, ky, dpen,
                                             Kfac, s, mb, mk);
@@ -767,14 +772,13 @@ template <typename T, int L>
 static hipError_t rows_inv_any(const T* P1, const T* P2, const uint8_t* mask, double* z,
                                const void* tw, int n1, int n2, bool tiled, hipStream_t s,
                                const Members& mb, const SdTabs& sd) {
-  if constexpr (L >= kSdMinL) {
-    if (tiled && sd.twS)
-      return sd_form<L>(sd, [&](auto f) {
-        return sd_rows_inv_impl<T, decltype(f)>(P1, mask, z, tw, sd.twS, sd.msl, n1, n2, s, mb);
-      });
-  }
-  return tiled ? pc_rows_inv_impl<T, L, true>(P1, P2, mask, z, tw, n1, n2, s, mb)
-               : pc_rows_inv_impl<T, L, false>(P1, P2, mask, z, tw, n1, n2, s, mb);
+  if (!tiled) return pc_rows_inv_impl<T, L, false>(P1, P2, mask, z, tw, n1, n2, s, mb);
+  if constexpr (L >= kSdMinL)
+    return sd_form<L>(sd, [&](auto f) {
+      return sd_rows_inv_impl<T, decltype(f)>(P1, mask, z, tw, sd.twS, sd.msl, n1, n2, s, mb);
+    });
+  else
+    return pc_rows_inv_impl<T, L, true>(P1, P2, mask, z, tw, n1, n2, s, mb);
 }
 
 template <typename T, int L>
@@ -783,17 +787,17 @@ static hipError_t rows_inv_mv_any(const T* P1, const T* P2, const uint8_t* mask,
                                   const double* sym, double coef, double dpen, const double* sub,
                                   double theta, int n1, int n2, bool tiled, hipStream_t s,
                                   const Members& mb, const double* mk, const SdTabs& sd) {
-  if constexpr (L >= kSdMinL) {
-    if (tiled && sd.twS)
-      return sd_form<L>(sd, [&](auto f) {
-        return sd_rows_inv_mv_impl<T, decltype(f)>(P1, mask, z, z32, t, twT, sd.twS, sd.msl, tw64, sym,
-                                                   coef, dpen, sub, theta, n1, n2, s, mb, mk);
-      });
-  }
-  return tiled ? pc_rows_inv_mv_impl<T, L, true>(P1, P2, mask, z, z32, t, twT, tw64, sym, coef,
-                                                 dpen, sub, theta, n1, n2, s, mb, mk)
-               : pc_rows_inv_mv_impl<T, L, false>(P1, P2, mask, z, z32, t, twT, tw64, sym, coef,
-                                                  dpen, sub, theta, n1, n2, s, mb, mk);
+  if (!tiled)
+    return pc_rows_inv_mv_impl<T, L, false>(P1, P2, mask, z, z32, t, twT, tw64, sym, coef, dpen, sub,
+                                            theta, n1, n2, s, mb, mk);
+  if constexpr (L >= kSdMinL)
+    return sd_form<L>(sd, [&](auto f) {
+      return sd_rows_inv_mv_impl<T, decltype(f)>(P1, mask, z, z32, t, twT, sd.twS, sd.msl, tw64, sym,
+                                                 coef, dpen, sub, theta, n1, n2, s, mb, mk);
+    });
+  else
+    return pc_rows_inv_mv_impl<T, L, true>(P1, P2, mask, z, z32, t, twT, tw64, sym, coef, dpen, sub,
+                                           theta, n1, n2, s, mb, mk);
 }
 
 #define RSFDE_LD_CASES(X) \
