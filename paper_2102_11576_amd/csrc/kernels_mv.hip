@@ -35,11 +35,12 @@ struct MvCfg {
   // at 255^3 93 -> 96 us, column passes 302 -> 317 us a product).
   static constexpr bool CXS = fft_cx(L);
   static constexpr bool CX = L <= 256;
-  // FFTs per row block; BR2 where one per block would number more blocks than the
-  // GPU has CUs and two per block would not (L = 2048): every CU then runs one
-  // block instead of some of them two.  Product, one / two per block: 600 x 513 20.1
-  // / 20.6 us, 600 x 530 21.6 / 20.8, 1000 x 700 25.8 / 24.5, 1000 x 1000 29.1 / 28.5;
-  // outside 1000 x 500 18.7 / 20.1, 1000 x 1500 35.7 / 37.3.
+  // FFTs per row block; BR2 (L = 2048) where one per block would give half of the
+  // eight XCDs or more a block beyond one per CU (kSmallGridBlocks + 4) and two per
+  // block would not: every CU then runs one block instead of some of them two.
+  // Product, one / two per block: 600 x 530 21.6 / 20.8 us, 1000 x 700 25.8 / 24.5, 1000
+  // x 1000 29.1 / 28.5; outside 1000 x 513 21.6 / 23.0 (257 blocks), 1000 x 500 18.7 /
+  // 20.1, 1000 x 1500 35.7 / 37.3.
   static constexpr int BR = row_ffts(TPF);
   static constexpr int BR2 = L == 2048 ? 2 : BR;
   // column pairs per column block: two at L = 1024 and 2048 (two-dimensional
@@ -304,8 +305,10 @@ static hipError_t mv_rows_impl(const double* z, const uint8_t* mask, double* out
                          (const cpx<double>*)tw, n1, n2, coef, dpen, mode, sub, theta, mb, mk);
   };
   const long one = (long)pairs * mb.n, two = (long)((pairs + 1) / 2) * mb.n;
-  if (C::BR2 != C::BR && one > kSmallGridBlocks && two <= kSmallGridBlocks) go(std::integral_constant<int, C::BR2>{});
-  else go(std::integral_constant<int, C::BR>{});
+  if (C::BR2 != C::BR && one > kSmallGridBlocks + 4 && two <= kSmallGridBlocks)
+    go(std::integral_constant<int, C::BR2>{});
+  else
+    go(std::integral_constant<int, C::BR>{});
   return hipGetLastError();
 }
 

@@ -157,9 +157,10 @@ def test_sine_transform_of_many_lines(n1, n2):
         assert np.linalg.norm(b - O.matvec_fast(p, u)) <= (1e-8 + 1e-12) * np.linalg.norm(b)
 
 
-# Row pass of the product with 2048 points: one transform per block up to 256 row
+# Row pass of the product with 2048 points: one transform per block up to 260 row
 # pairs and beyond 512, two between
-@pytest.mark.parametrize("n1,n2", [(520, 512), (1023, 513), (520, 515), (520, 1024), (520, 1025)])
+@pytest.mark.parametrize("n1,n2", [(520, 512), (1023, 513), (520, 520), (520, 521), (1023, 531),
+                                   (520, 1024), (520, 1025)])
 def test_matvec_row_blocks(n1, n2):
     box = (0.0, 1.0, 0.0, 1.0)
     mask = domain_mask(n1, n2, box, SHAPES["disk"](0.5, 0.5, 0.4))
