@@ -78,7 +78,8 @@ __device__ __forceinline__ void cd_sd_conv(cpx<T>* v, bool g, int p, int r, int 
 
 // A zero that the optimiser cannot see through, added to a table's pointer where
 // the table is read again later: the values are then loaded again instead of
-// being held in registers across a transform (k_cds_cols spilled 360 registers; an opaque pointer would lose its global address space).
+// being held in registers across a transform (k_cds_cols spilled 360 registers; an
+// opaque pointer would lose its global address space).
 __device__ __forceinline__ int opaque_zero() {
   int z = 0;
   asm volatile("" : "+s"(z));

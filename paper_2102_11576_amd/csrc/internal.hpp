@@ -49,9 +49,10 @@ constexpr int fft_pts(int L) { return L <= 8 ? L : (L <= 256 ? 4 : (L <= 1024 ? 
 // 8 points per thread twice the LDS still leaves 16 wavefronts per CU.  Used where
 // registers or the grid hold a kernel to that anyway: pass B of 3-D plans (169 ->
 // 148 us at 255^3) and their raw sine transforms (91 -> 88), the convolution of the
-// fused pass, the chirp passes (200^2 22.5 -> 21.8 us) and the product's column
-// pass on small views.  The row passes lose wavefronts by it (255^3: pass A 66 ->
-// 77 us, pass C 101 -> 121).
+// fused pass, the chirp passes (200^2 22.5 -> 21.8 us), the product's column pass on
+// small views and all of its passes up to L = 256.  The row passes of the
+// preconditioner lose wavefronts by it at L = 512 (255^3: pass A 66 -> 77 us, pass
+// C 101 -> 121).
 constexpr bool fft_cx(int L) { return L <= 1024; }
 
 // Transforms per block of the row passes: one wavefront's worth, or one

@@ -55,7 +55,8 @@ struct MvCfg {
 // TO: out in the strip-tiled layout.
 // --------------------------------------------------------------------------
 template <int L, int BR, bool TO>
-__global__ __launch_bounds__(MvCfg<L>::TPF* BR) __attribute__((amdgpu_waves_per_eu(4))) void k_mv_rows(
+__global__ __launch_bounds__(MvCfg<L>::TPF* BR) __attribute__((amdgpu_waves_per_eu(4)))
+void k_mv_rows(
     const double* __restrict__ z, const uint8_t* __restrict__ mask, double* __restrict__ out,
     const double* __restrict__ sym, const cpx<double>* __restrict__ tw, int n1, int n2,
     double coef, double dpen, int mode, const double* __restrict__ sub, double theta,

@@ -2,8 +2,9 @@
 // unnormalised) in one pass over the basis, with what the step needs next in
 // the same pass: the dots <V_i, V_{j+1}> of the second Gram-Schmidt pass
 // (k_axpy_dot), or ||V_{j+1}||^2 (k_axpy_givens, FINAL).  The Givens kernel then
-// sets H[j+1][j] = beta, vscale[j+1] = 1/beta, applies the previous Givens
-// rotations to column j, forms rotation j (Section 5: GMRES) and publishes the
+// sets vscale[j+1] = 1/beta (beta = ||V_{j+1}||), applies the previous Givens
+// rotations to column j, forms rotation j from its last entry and beta (Section 5:
+// GMRES), stores the rotated column with 0 below the diagonal and publishes the
 // residual estimate |g_{j+1}| for the host.
 //
 // All are bound by reading the basis; on short vectors, by the launches and
@@ -31,11 +32,10 @@ __device__ __forceinline__ void coefs(double* c, const RedWork& rw, int nb, bool
 // to 202; the counts between lose 2 to 3 %: 20 136 -> 140, 28 186 -> 191).
 template <int NV, int W, bool FINAL, bool GATHER>
 __global__ __launch_bounds__(kRedThreads)
-__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8))) void k_axpy_givens(const double* __restrict__ V,
-                                                             size_t ldv, const double* win,
-                                                             double* vout, size_t N, RedWork rw,
-                                                             double* coef, const double* vscale,
-                                                             bool second, const Members mb) {
+__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8)))
+void k_axpy_givens(const double* __restrict__ V, size_t ldv, const double* win, double* vout,
+                   size_t N, RedWork rw, double* coef, const double* vscale, bool second,
+                   const Members mb) {
   __shared__ double sh[16], c[NV];
   {  // member of a batched launch (grid dimension y)
     const size_t mo = mb.off(blockIdx.y);
@@ -143,8 +143,8 @@ __global__ __launch_bounds__(kRedThreads) void k_axpy_dot(const double* __restri
   publish_partials<NV>(acc, orth_partials(rw, true), sh);
 }
 
-// beta = ||V_{j+1}||, H[j+1][j] = beta, vscale[j+1] = 1/beta, the previous
-// Givens rotations applied to column j, rotation j, and |g_{j+1}| for the host.
+// beta = ||V_{j+1}||, vscale[j+1] = 1/beta, the previous Givens rotations applied
+// to column j, rotation j of (H[j][j], beta) to (den, 0), and |g_{j+1}| for the host.
 // One wavefront: the column and the rotations are loaded at once (one lane per
 // entry) and the recurrence runs from LDS; reading them one dependent global
 // load after the other took 6.2 us at j = 20.

@@ -14,10 +14,9 @@ namespace rsfde {
 // vectors 213 -> 158 us, 32 vectors 283 -> 206 us, 5.4 TB/s; up to 16 the same).
 template <int NV, int W>
 __global__ __launch_bounds__(kRedThreads)
-__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8))) void k_multidot(const double* __restrict__ V, size_t ldv,
-                                                          const double* __restrict__ w, size_t N,
-                                                          RedWork rw, bool second,
-                                                          const Members mb) {
+__attribute__((amdgpu_waves_per_eu(W == 2 ? 2 : 1, W == 2 ? 2 : 8)))
+void k_multidot(const double* __restrict__ V, size_t ldv, const double* __restrict__ w, size_t N,
+                RedWork rw, bool second, const Members mb) {
   __shared__ double sh[16 * NV];
   {  // member of a batched launch (grid dimension y)
     const size_t mo = mb.off(blockIdx.y);

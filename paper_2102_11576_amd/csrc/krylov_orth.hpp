@@ -14,8 +14,9 @@ namespace rsfde {
 //   beyond: two values per load, up to kMaxRedBlocks blocks, and a finishing
 //     kernel sums the partials once (512 blocks each reading 512 partials per
 //     coefficient cost 19 us a step at 2047^2).
-// At 63^2 a two-pass step took seven launches and 48 us of kernel time, now four
-// and 22 us; one implicit step there 2.75 -> 2.08 ms.
+// A two-pass step takes four launches in the first shape and six in the second
+// (seven before, with one more read of the basis).  At 63^2 its kernel time went
+// from 48 to 22 us, one implicit step there 2.75 -> 2.08 ms.
 constexpr size_t kOrthSmallN = (size_t)1 << 18;
 constexpr int kOrthSmallBlocks = 128;
 inline bool orth_small(size_t N) { return N <= kOrthSmallN; }

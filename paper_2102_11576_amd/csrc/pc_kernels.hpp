@@ -20,12 +20,13 @@
 // output vectors are always FP64).
 //
 // Layout of the intermediates.  Natural (TL = false; three-dimensional plans,
-// pass B is k_pc_cols_nat): Q, P1, P2 are [rows][n+1] arrays.  Two-dimensional plans (TL = true): Q is strip-tiled
-// (tile_index: [2 rows][4 slots] tiles, strip after strip), and the P1/P2
-// pairs are interleaved in one array of row segments (pair_index).  Pass B
-// then reads Q in whole strips and writes whole 32-byte sectors, where the
-// natural layout gives it 32-byte pieces of rows 8 (n+1) bytes apart; pass A
-// writes 64-byte pieces of Q and pass C reads whole 128-byte lines of pairs.
+// pass B is k_pc_cols_nat): Q, P1, P2 are [rows][n+1] arrays.  Two-dimensional
+// plans (TL = true): Q is strip-tiled (tile_index: [2 rows][4 slots] tiles, strip
+// after strip), and the P1/P2 pairs are interleaved in one array of row segments
+// (pair_index).  Pass B then reads Q in whole strips and writes whole 32-byte
+// sectors, where the natural layout gives it 32-byte pieces of rows 8 (n+1) bytes
+// apart; pass A writes 64-byte pieces of Q and pass C reads whole 128-byte lines
+// of pairs.  Tiled passes of kSdMinL points and more are in sd_kernels.hpp.
 #pragma once
 #include "sd_kernels.hpp"
 
@@ -246,7 +247,8 @@ __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols(
 // and 2c + 1 share every transform, the forward one and one inverse per field,
 // so each load and store moves both columns and a wavefront whole lines (one
 // inverse per column, with its (P1, P2) pair, wrote half-lines at two times: 213
-// -> 169 us at 255^3, 3.1 TB/s of its 24 bytes a slot).  ld = n1 + 1 is even.
+// -> 169 us at 255^3, 148 with both parts per exchange, 2.7 TB/s of its 24 bytes a
+// slot).  ld = n1 + 1 is even.
 // --------------------------------------------------------------------------
 template <typename T, int L, int BC>
 __global__ __launch_bounds__(PcColCfg<L>::TPF* BC) void k_pc_cols_nat(
@@ -692,8 +694,8 @@ static hipError_t sd_cols_impl(const T* Q, T* P, const T* lamx, const T* lamy, c
                                const double* mk) {
   using C = SdCols<S>;
   hipLaunchKernelGGL((k_sd_cols<T, S>), dim3(((n1 + 1) / 2 + C::BC - 1) / C::BC, 1, mb.n),
-                     dim3(C::THR), 0, s, Q, P, lamx, lamy, (const cpx<T>*)twL, (const cpx<T>*)twS, n1, n2, (T)kx, (T)ky, (T)dpen,
-                     (T)(0.5 * Kfac), mb, mk);
+                     dim3(C::THR), 0, s, Q, P, lamx, lamy, (const cpx<T>*)twL,
+                     (const cpx<T>*)twS, n1, n2, (T)kx, (T)ky, (T)dpen, (T)(0.5 * Kfac), mb, mk);
   return hipGetLastError();
 }
 

@@ -253,14 +253,12 @@ void fft_host(std::vector<std::complex<double>>& a) {
   }
 }
 
-// Tables of the chirp form of the length-n orthonormal DST-I (M = n + 1):
-//   chn[p]  = exp(i pi (p+1)^2 / (2M)), p < n (interleaved re, im);
-//   khat[p] = sqrt(2/M) / L * K_f at f = freq(p), K = DFT_L of the even kernel
-//             k[m mod L] = exp(-i pi m^2 / (2M)), |m| < n.
-// Phases are reduced exactly: m^2 mod 4M in integers.
+// Tables of the chirp form of the length-n orthonormal DST-I (M = n + 1).  Their
+// phases pi j^2 / (2M) are reduced exactly: j^2 mod 4M in integers.
 double chirp_angle(int n, long long j) {
   return kPi * (double)((j * j) % (4LL * (n + 1))) / (2.0 * (double)(n + 1));
 }
+// chn[p] = exp(i pi (p+1)^2 / (2M)), p < n (interleaved re, im).
 std::vector<double> chirp_values(int n) {
   std::vector<double> chn(2 * (size_t)n);
   for (int p = 0; p < n; ++p) {
@@ -270,6 +268,8 @@ std::vector<double> chirp_values(int n) {
   }
   return chn;
 }
+// khat[p] = sqrt(2/M) / L * K_f at f = freq(p), K = DFT_L of the even kernel
+// k[m mod L] = exp(-i pi m^2 / (2M)), |m| < n.
 std::vector<double> chirp_khat(int n, int L) {
   std::vector<std::complex<double>> k(L, {0.0, 0.0});
   for (int m = 0; m < n; ++m) {

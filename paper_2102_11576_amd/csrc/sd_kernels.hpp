@@ -253,7 +253,7 @@ __device__ __forceinline__ void sd_store_z(const cpx<T>* v, int q, int row, bool
 }
 
 // --------------------------------------------------------------------------
-// Pass A: row pairs (ra, rb) -> Q (strip-tiled), one row pair per block.
+// Pass A: row pairs (ra, rb) -> Q (strip-tiled), sd_per_block row pairs per block.
 // --------------------------------------------------------------------------
 template <typename T, class S>
 __global__ __launch_bounds__(sd_per_block<S>() * S::TPD) void k_sd_rows_fwd(
@@ -314,8 +314,8 @@ __global__ __launch_bounds__(sd_per_block<S>() * S::TPD) void k_sd_rows_fwd(
 }
 
 // --------------------------------------------------------------------------
-// Pass B: slot-column pairs (2c, 2c+1) of Q -> (P1, P2) pairs, one column pair
-// per block.
+// Pass B: slot-column pairs (2c, 2c+1) of Q -> (P1, P2) pairs, sd_per_block column
+// pairs per block, interleaved (column pair fastest in the thread index).
 // --------------------------------------------------------------------------
 template <typename T, class S>
 __global__ __launch_bounds__(SdCols<S>::THR) __attribute__((amdgpu_waves_per_eu(3))) void k_sd_cols(
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(SdCols<S>::THR) __attribute__((amdgpu_waves_per_eu(
 }
 
 // --------------------------------------------------------------------------
-// Pass C: one row per transform and block; the inverse sweep of
+// Pass C: one row per transform, sd_per_block per block; the inverse sweep of
 // P2/2 - i P1/2 gives (P1 S_x) + i (P2 S_x), combined by the mask into z.
 // --------------------------------------------------------------------------
 template <typename T, class S>
