@@ -285,7 +285,8 @@ struct Fft {
   // loads: 63^2 2.0e-7 / 2.9e-7 / 1.3e-7, 50^3 2.5e-7 / 4.2e-7 / 1.8e-7).  At L =
   // 256 the products are the closer ones (127^2 0.7 of the 16 points' error), and
   // the loads would take FP32 at 100^3 from 80 to 106 us; at L = 128 they take it
-  // from 22.0 to 22.6 us at 63^3 and from 28 to 30 at 50^3.
+  // from 22.0 to 22.6 us at 63^3, 28 to 30 at 50^3 and, the most, 54 to 60 at 511 x
+  // 63 x 63 (42, 63 with 16 points for the last two).
   template <typename T>
   static constexpr int NR = PP == 4 && L <= (sizeof(T) == 4 ? 128 : 16) ? 3 : 1;
   template <typename T>
